@@ -18,25 +18,12 @@
 
 #include <hipcub/hipcub.hpp>
 
+#include "rdos_cell.h"
 #include "rdos_internal.h"
-#include "rdos_sampling.h"
 
 #pragma clang fp contract(off)
 
 namespace rdos {
-
-typedef int32_t v4i __attribute__((ext_vector_type(4)));
-
-// A pointer into device (global) memory.  Accesses through generic pointers
-// become flat instructions, which also count against the scalar-load wait
-// counter, so a wait for a scalar load would wait for them too.
-template <typename T>
-using gptr = __attribute__((address_space(1))) T *;
-template <typename T>
-__device__ __forceinline__ gptr<T> global(T *p)
-{
-    return (gptr<T>)p;
-}
 
 // ---------------------------------------------------------------------------
 // Set-up (Sec. II.A): volumes, face areas, barycentres, then per face
@@ -403,40 +390,12 @@ __device__ __forceinline__ void tally_count(unsigned long long *work, int which)
 
 struct LaneState {
     int32_t *N;     // counts during the period
-    double *occ;    // occupancy integral since the start of the period
-    double *last;   // time of the last change
+    double *occv;   // occupancy integral since the start of the period
+    double *lastv;  // time of the last change
     __device__ __forceinline__ int32_t &n(int s) const { return N[s * kBlock]; }
+    __device__ __forceinline__ double &occ(int s) const { return occv[s * kBlock]; }
+    __device__ __forceinline__ double &last(int s) const { return lastv[s * kBlock]; }
 };
-
-// propensity a_r = c_r h_r of reaction q with the tet's counts (mass action);
-// zero where the reaction is not allowed in tet t (bit q of its `allowed`
-// word).  The counts are tested first, and the tet's N_A V and allowed word
-// are read from memory only when they matter: most tets hold no reactant
-// pair, and then their update does not wait for those loads.
-__device__ __forceinline__ double propensity(const DevSim &sm, int q, const LaneState &ls, const MeshRec *mr,
-                                             int32_t t)
-{
-    const int order = sm.rn[q];
-    double h;
-    if (order == 0) {
-        h = 1.0;
-    } else {
-        const int32_t na = ls.n(sm.r0[q]);
-        if (order == 1) {
-            h = (double)na;
-        } else if (sm.r0[q] == sm.r1[q]) {
-            h = (double)na * (double)(na - 1);
-        } else {
-            h = (double)na * (double)ls.n(sm.r1[q]);
-        }
-    }
-    if (h == 0.0) return 0.0;  // c_r * 0 == 0 for every finite c_r
-    if (sm.allowed && !((sm.allowed[t] >> q) & 1u)) return 0.0;
-    if (order == 1) return sm.k[q] * h;
-    const double nav = mr->nav;
-    const double c = order == 0 ? sm.k[q] * nav : sm.k[q] / nav;
-    return c * h;
-}
 
 // nxt and mnxt point at one realization's counts and occupancy rows; the
 // offsets into them are 32-bit (finalize keeps S Tp below 2^29), which keeps
@@ -449,78 +408,13 @@ __device__ __forceinline__ void update_tet(const DevSim &sm, int32_t t, int64_t 
 {
     const bool tally = work != nullptr;
     const int S = sm.S;
-    const int R = sm.R;
     const uint32_t period32 = (uint32_t)period;
     // a pointer, not a reference: a reference would tell the compiler the
     // record may be read anywhere, and the SSA's conditional read of N_A V
     // would then be made for every tet
     const MeshRec *mr = sm.mesh + t;
-
-    // Step 2: Gillespie direct method over [0, tau_k); the first event at or
-    // past tau_k is discarded.  Step 2.1: on each event the occupancy
-    // integral of every reactant and product is brought up to the event time.
-    // occ/last of species s are meaningful once bit s of `touched` is set;
-    // before that they stand for 0 (no stores for tets without events).
     uint32_t touched = 0;
-    if (R > 0) {
-        Stream ssa(sm.key0, key1, kSsaStream, (uint32_t)t, period32);
-        double now = 0.0;
-        for (uint32_t events = 0;; ++events) {
-            if (events >= kMaxEventsPerPeriod) {  // runaway rates: stop and report, never hang
-                atomicOr(sm.flags, 2);
-                break;
-            }
-            double a0 = 0.0;
-            for (int q = 0; q < R; ++q) a0 = a0 + propensity(sm, q, ls, mr, t);
-            if (!(a0 > 0.0)) break;
-            const double dt = -log_basic(1.0 - ssa.uniform()) / a0;
-            if (now + dt >= tau_k) break;
-            now = now + dt;
-            const double x = ssa.uniform() * a0;
-            int chosen = -1;
-            double cum = 0.0;
-            for (int q = 0; q < R; ++q) {
-                cum = cum + propensity(sm, q, ls, mr, t);
-                if (x < cum) {
-                    chosen = q;
-                    break;
-                }
-            }
-            if (chosen < 0) {  // x rounded up to a0: the last reaction able to fire
-                for (int q = R - 1; q >= 0; --q)
-                    if (propensity(sm, q, ls, mr, t) > 0.0) {
-                        chosen = q;
-                        break;
-                    }
-            }
-            // the chosen reaction's fields, read with a wavefront-uniform index
-            // (scalar loads) and selected per lane
-            uint32_t inv = 0;
-            int a = -1, b = -1, c0 = -1, c1 = -1, c2 = -1;
-            for (int q = 0; q < R; ++q) {
-                const int rn = sm.rn[q], pn = sm.pn[q];
-                const bool is = q == chosen;
-                inv = is ? sm.involved[q] : inv;
-                a = is && rn > 0 ? sm.r0[q] : a;
-                b = is && rn > 1 ? sm.r1[q] : b;
-                c0 = is && pn > 0 ? sm.p0[q] : c0;
-                c1 = is && pn > 1 ? sm.p1[q] : c1;
-                c2 = is && pn > 2 ? sm.p2[q] : c2;
-            }
-            for (int s = 0; s < S; ++s) {
-                if (!((inv >> s) & 1u)) continue;
-                const bool seen = (touched >> s) & 1u;
-                const double o = seen ? ls.occ[s * kBlock] : 0.0;
-                const double l = seen ? ls.last[s * kBlock] : 0.0;
-                int32_t &ns = ls.n(s);
-                ls.occ[s * kBlock] = o + (double)ns * (now - l);
-                ls.last[s * kBlock] = now;
-                ns += (int)(s == c0) + (int)(s == c1) + (int)(s == c2) - (int)(s == a) - (int)(s == b);
-                if (ns > 0x3fffffff) atomicOr(sm.flags, 1);
-            }
-            touched |= inv;
-        }
-    }
+    if (sm.R > 0) touched = cell_ssa(sm, mr, t, period32, tau_k, key1, ls);
 
     // Step 3, per diffusing species: mean occupancy (eq. 2), stochastic
     // rounding to an integer population, n = binomial(Nbar, zeta) (eq. 3)
@@ -541,8 +435,7 @@ __device__ __forceinline__ void update_tet(const DevSim &sm, int32_t t, int64_t 
         const int32_t Ns = ls.n(s);
         if ((sm.diff_mask >> s) & 1u) {  // Ns == 0 never gets here: n = min(binomial(.), 0) = 0
             const bool hit = ((touched >> s) & 1u) && !sm.first_order;
-            const double nbar = hit ? (ls.occ[s * kBlock] + (double)Ns * (tau_k - ls.last[s * kBlock])) / tau_k
-                                    : (double)Ns;
+            const double nbar = hit ? mean_occupancy(ls, s, Ns, tau_k) : (double)Ns;
             Stream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
             int32_t ni = (int32_t)floor(nbar);
             const double frac = nbar - (double)ni;
@@ -566,32 +459,9 @@ __device__ __forceinline__ void update_tet(const DevSim &sm, int32_t t, int64_t 
                 if (k < S) Ds = k == s ? sm.D[k] : Ds;
             double zeta = (tau_k * Ds) * g;
             if (zeta > 1.0) zeta = 1.0;
-            // Step 3.2-3.3: n = min(binomial(SR(Nbar), zeta), N) split over the
-            // faces; or (transfer form 1) SR(Nbar) split at once with weights
-            // zeta w_f, and if more would leave than are present, those
-            // present split as in Step 3.3.  The second form is compiled only
-            // into the kernel instance launched when some simulation uses it,
-            // so the first keeps its registers.
             int32_t out[4];
-            int32_t n;
-            if constexpr (ANY_SCALED) {
-                bool scaled = sm.transfer_form == 1;
-                int32_t pop = ni;
-                if (!scaled) {
-                    pop = binomial(ni, zeta, rng);
-                    if (pop > Ns) pop = Ns;
-                }
-                for (;;) {
-                    n = split_faces(pop, nb, w, scaled ? zeta : 1.0, scaled, sm.split_threshold, rng, out);
-                    if (!(scaled && n > Ns)) break;
-                    pop = Ns;
-                    scaled = false;
-                }
-            } else {
-                n = binomial(ni, zeta, rng);
-                if (n > Ns) n = Ns;
-                if (n > 0) split_over_faces(n, nb, w, sm.split_threshold, rng, out);
-            }
+            const int32_t n = leave_and_split<ANY_SCALED>(ni, Ns, zeta, sm.transfer_form == 1, nb, w,
+                                                              sm.split_threshold, rng, out);
             if (n > 0) {
 #pragma unroll
                 for (int f = 0; f < 4; ++f)
@@ -1634,7 +1504,7 @@ __global__ __launch_bounds__(256) void split_cost_kernel(int64_t n, int32_t reps
     for (int32_t r = 0; r < reps; ++r) {
         Stream rng(0x2545F491u, 0x9E3779B9u, 0x80000001u, lane, (uint32_t)r);
         int32_t out[4];
-        split_over_faces((int32_t)n, nbr, w, ONE_BY_ONE ? (int32_t)(n + 1) : 1, rng, out);
+        leave_and_split<false>((int32_t)n, (int32_t)n, 1.0, false, nbr, w, ONE_BY_ONE ? (int32_t)(n + 1) : 1, rng, out);
         acc += out[0] + 2 * out[1] + 3 * out[2] + 4 * out[3];
     }
     sink[lane] = acc;

@@ -23,11 +23,9 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 x, uint32_t k0, uint32_t k1
 {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint32_t lo0 = 0xD2511F53u * x.x;
-        const uint32_t hi0 = __umulhi(0xD2511F53u, x.x);
-        const uint32_t lo1 = 0xCD9E8D57u * x.z;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, x.z);
-        x = make_uint4(hi1 ^ x.y ^ k0, lo1, hi0 ^ x.w ^ k1, lo0);
+        const uint64_t p0 = (uint64_t)0xD2511F53u * x.x;
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * x.z;
+        x = make_uint4((uint32_t)(p1 >> 32) ^ x.y ^ k0, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ x.w ^ k1, (uint32_t)p0);
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -53,10 +51,32 @@ struct Stream {
     __device__ __forceinline__ double uniform()
     {
         if (!(j & 1u)) words = philox4x32_10(make_uint4(j >> 1, id, tet, period), k0, k1);
+        return take();
+    }
+
+    __device__ __forceinline__ double take()
+    {
         const uint32_t hi = (j & 1u) ? words.z : words.x;
         const uint32_t lo = (j & 1u) ? words.w : words.y;
         ++j;
         return ((double)(hi >> 5) * 67108864.0 + (double)(lo >> 6)) * 0x1p-53;
+    }
+};
+
+// The same stream with its first block generated at construction, for callers
+// that always draw and have loads in flight meanwhile.
+struct PrimedStream : Stream {
+    __device__ __forceinline__ PrimedStream(uint32_t key0, uint32_t key1, uint32_t stream_id, uint32_t tet_id,
+                                            uint32_t period_id)
+        : Stream(key0, key1, stream_id, tet_id, period_id)
+    {
+        words = philox4x32_10(make_uint4(0, id, tet, period), k0, k1);
+    }
+
+    __device__ __forceinline__ double uniform()
+    {
+        if (!(j & 1u) && j != 0) words = philox4x32_10(make_uint4(j >> 1, id, tet, period), k0, k1);
+        return take();
     }
 };
 
@@ -105,19 +125,50 @@ __device__ __forceinline__ double log_basic(double x)
 //         otherwise;
 // p > 1/2 is sampled as n - Binomial(n, 1 - p).
 // ---------------------------------------------------------------------------
+
+// a / x for a whole x below 2^31, y = 1 / x to within a few ulp: the product
+// a y corrected once by its exact residual.  A quotient by such an x lies at
+// least 2^-32 ulp from the midpoint of two doubles (or is one of them), far
+// more than the correction's own error, so the result is the correctly
+// rounded quotient, as a / x is; it needs 3 operations beside y where the
+// division takes 11.  For quotients clear of under- and overflow.
+__device__ __forceinline__ double divide_by_whole(double a, double x, double y)
+{
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-x, q, a), y, q);
+}
+
+// 1 / x to within a few ulp (the hardware estimate and two Newton steps).
+__device__ __forceinline__ double reciprocal_near(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+
+// q^n by squaring, low bits first, two bits a pass; the lanes of a wavefront
+// share the passes (products past a lane's highest bit are not kept).
 __device__ __forceinline__ double pow_by_squaring(double q, int32_t n)
 {
     double acc = 1.0;
-    double sq = q;
-    while (n > 0) {
-        if (n & 1) acc = acc * sq;
-        n >>= 1;
-        if (n > 0) sq = sq * sq;
+    while (__ballot(n > 0) != 0) {
+        acc = n & 1 ? acc * q : acc;
+        q = q * q;
+        acc = n & 2 ? acc * q : acc;
+        q = q * q;
+        n >>= 2;
     }
     return acc;
 }
 
-__device__ inline int32_t binomial_inversion(int32_t n, double p, Stream &rng)
+// The walk u -= P(x), P(x + 1) = P(x) ((n + 1) p / (q (x + 1)) - p / q) runs
+// four steps at a time: the four ratios do not depend on the walk, so their
+// latencies overlap, and only a compare, a subtraction and a product per
+// step are serial.  The lanes of a wavefront walk in step, so x + 1 .. x + 4
+// are uniform.  A lane whose walk has ended keeps its values, since u <= P
+// stays true.  Ratios past x = n are never kept: x > n starts again.
+template <class Rng>
+__device__ __forceinline__ int32_t binomial_inversion(int32_t n, double p, Rng &rng)
 {
     const double q = 1.0 - p;
     const double odds = p / q;
@@ -127,17 +178,29 @@ __device__ inline int32_t binomial_inversion(int32_t n, double p, Stream &rng)
         double u = rng.uniform();
         double pk = p_zero;
         int32_t x = 0;
-        bool restart = false;
-        while (u > pk) {
-            u = u - pk;
-            ++x;
-            if (x > n) {
-                restart = true;
-                break;
+        for (int32_t base = 1; __ballot(u > pk && x <= n) != 0; base += 4) {
+            double ratio[4];
+            if (base == 1) {
+                ratio[0] = np1_odds - odds;
+                ratio[1] = np1_odds * 0.5 - odds;
+                ratio[2] = divide_by_whole(np1_odds, 3.0, 1.0 / 3.0) - odds;
+                ratio[3] = np1_odds * 0.25 - odds;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double xj = (double)(base + j);
+                    ratio[j] = divide_by_whole(np1_odds, xj, reciprocal_near(xj)) - odds;
+                }
             }
-            pk = pk * (np1_odds / (double)x - odds);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool go = u > pk;
+                u = go ? u - pk : u;
+                pk = go ? pk * ratio[j] : pk;
+                x += go ? 1 : 0;
+            }
         }
-        if (!restart) return x;
+        if (x <= n) return x;
     }
 }
 
@@ -158,234 +221,215 @@ __device__ __forceinline__ double stirling_tail(int32_t k)
     return (1.0 / 12.0 - (1.0 / 360.0 - (1.0 / 1260.0) * v2) * v2) * v;
 }
 
-// The set-up values are recomputed on every pass of the rejection loop
-// instead of being held across it: `carry` is +0 after a rejected pass (0
-// times a finite uniform), so p + carry == p and every value is bit for bit
-// the same, but the compiler cannot hoist them out of the loop, which keeps
-// them out of the registers the callers need.  Most draws take one pass.
-__device__ inline int32_t binomial_btrd(int32_t n, double p_in, Stream &rng)
+// One pass of BTRD's rejection: true and *x on acceptance.
+template <class Rng>
+__device__ __forceinline__ bool btrd_pass(int32_t n, double p, Rng &rng, int32_t *x)
 {
     const double nd = (double)n;
-    double carry = 0.0;
-    for (;;) {
-        const double p = p_in + carry;
-        const double q = 1.0 - p;
-        const double npq = (nd * p) * q;
-        const double spq = sqrt(npq);
-        const double b = 1.15 + 2.53 * spq;
-        const double a = (-0.0873 + 0.0248 * b) + 0.01 * p;
-        const double c = nd * p + 0.5;
-        const double vr = 0.92 - 4.2 / b;
-        const double urvr = 0.86 * vr;
-        double v = rng.uniform();
-        carry = 0.0 * v;
-        double u;
-        if (v <= urvr) {  // inside the box: accept at once
-            u = v / vr - 0.43;
-            const double kd = floor(((2.0 * a) / (0.5 - fabs(u)) + b) * u + c);
-            if (kd < 0.0 || kd > nd) continue;
-            return (int32_t)kd;
-        }
+    const double q = 1.0 - p;
+    const double npq = (nd * p) * q;
+    const double spq = sqrt(npq);
+    const double b = 1.15 + 2.53 * spq;
+    const double a = (-0.0873 + 0.0248 * b) + 0.01 * p;
+    const double c = nd * p + 0.5;
+    const double vr = 0.92 - 4.2 / b;
+    const double urvr = 0.86 * vr;
+    double v = rng.uniform();
+    const bool box = v <= urvr;  // inside the box: accept at once
+    double u;
+    if (box) {
+        u = v / vr - 0.43;
+    } else {
+        const double draw = rng.uniform();
         if (v >= vr) {
-            u = rng.uniform() - 0.5;
+            u = draw - 0.5;
         } else {
             u = v / vr - 0.93;
             u = (u < 0.0 ? -0.5 : 0.5) - u;
-            v = rng.uniform() * vr;
+            v = draw * vr;
         }
-        const double us = 0.5 - fabs(u);
-        const double kd = floor(((2.0 * a) / us + b) * u + c);
-        if (kd < 0.0 || kd > nd) continue;
-        const double alpha = (2.83 + 5.1 / b) * spq;
-        v = v * alpha / (a / (us * us) + b);
-        const double mode = floor((nd + 1.0) * p);
-        const double r = p / q;
-        const double km = fabs(kd - mode);
-        if (km <= 15.0) {
-            // ratio f(k)/f(mode) by the recurrence f(i)/f(i-1) = nr/i - r
-            const double nr = (nd + 1.0) * r;
-            double f = 1.0;
-            if (mode < kd) {
-                double i = mode;
-                do {
-                    i += 1.0;
-                    f = f * (nr / i - r);
-                } while (i != kd);
-            } else if (mode > kd) {
-                double i = kd;
-                do {
-                    i += 1.0;
-                    v = v * (nr / i - r);
-                } while (i != mode);
-            }
-            if (v <= f) return (int32_t)kd;
-            continue;
-        }
-        v = log_basic(v);
-        const double rho = (km / npq) * (((km / 3.0 + 0.625) * km + 1.0 / 6.0) / npq + 0.5);
-        const double t = -(km * km) / (2.0 * npq);
-        if (v < t - rho) return (int32_t)kd;
-        if (v > t + rho) continue;
-        const int32_t m_i = (int32_t)mode, k_i = (int32_t)kd;
-        const double nm = nd - mode + 1.0;
-        const double h = (mode + 0.5) * log_basic((mode + 1.0) / (r * nm)) + stirling_tail(m_i) +
-                         stirling_tail(n - m_i);
-        const double nk = nd - kd + 1.0;
-        if (v <= h + (nd + 1.0) * log_basic(nm / nk) + (kd + 0.5) * log_basic(nk * r / (kd + 1.0)) -
-                     stirling_tail(k_i) - stirling_tail(n - k_i))
-            return k_i;
     }
-}
-
-__device__ inline int32_t binomial(int32_t n, double p, Stream &rng)
-{
-    if (n <= 0 || p <= 0.0) return 0;
-    if (p >= 1.0) return n;
-    const bool reflect = p > 0.5;
-    const double pp = reflect ? 1.0 - p : p;
-    const int32_t x = ((double)n * pp < 10.0) ? binomial_inversion(n, pp, rng) : binomial_btrd(n, pp, rng);
-    return reflect ? n - x : x;
+    const double us = 0.5 - fabs(u);
+    const double kd = floor(((2.0 * a) / us + b) * u + c);
+    if (kd < 0.0 || kd > nd) return false;
+    *x = (int32_t)kd;
+    if (box) return true;
+    const double alpha = (2.83 + 5.1 / b) * spq;
+    v = v * alpha / (a / (us * us) + b);
+    const double mode = floor((nd + 1.0) * p);
+    const double r = p / q;
+    const double km = fabs(kd - mode);
+    if (km <= 15.0) {
+        // ratio f(k)/f(mode) by the recurrence f(i)/f(i-1) = nr/i - r: from
+        // the mode up, multiplied up from 1, or from k up to the mode,
+        // multiplied into v.  Four ratios at a time (they are independent).
+        const double nr = (nd + 1.0) * r;
+        const bool up = mode < kd;
+        const double low = up ? mode : kd;
+        const int32_t steps = (int32_t)km;
+        double f = up ? 1.0 : v;
+        for (int32_t i = 0; __ballot(i < steps) != 0; i += 4) {
+            double ratio[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double ij = low + (double)(i + j + 1);
+                ratio[j] = divide_by_whole(nr, ij, reciprocal_near(ij)) - r;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f = i + j < steps ? f * ratio[j] : f;
+        }
+        return up ? v <= f : f <= 1.0;
+    }
+    v = log_basic(v);
+    const double rho = (km / npq) * (((km / 3.0 + 0.625) * km + 1.0 / 6.0) / npq + 0.5);
+    const double t = -(km * km) / (2.0 * npq);
+    if (v < t - rho) return true;
+    if (v > t + rho) return false;
+    const int32_t m_i = (int32_t)mode, k_i = (int32_t)kd;
+    const double nm = nd - mode + 1.0;
+    const double h = (mode + 0.5) * log_basic((mode + 1.0) / (r * nm)) + stirling_tail(m_i) + stirling_tail(n - m_i);
+    const double nk = nd - kd + 1.0;
+    return v <= h + (nd + 1.0) * log_basic(nm / nk) + (kd + 0.5) * log_basic(nk * r / (kd + 1.0)) -
+                    stirling_tail(k_i) - stirling_tail(n - k_i);
 }
 
 // ---------------------------------------------------------------------------
-// Multinomial split of n leaving molecules over the interior faces
-// (Sec. II.B).  n < threshold (10 in the paper): one categorical draw per
-// molecule against the running sum of the weights (the last interior face
-// closes the interval); otherwise
+// Steps 3.2-3.3 for one species of one tet: n = min(Binomial(ni, zeta), Ns)
+// molecules leave and are split over the interior faces (Sec. II.B).  Below
+// the threshold (10 in the paper): one categorical draw per molecule against
+// the running sum of the weights, the last interior face closing the
+// interval; otherwise
 // n_i = Binomial(n - sum_{j<i} n_j, w_i / (1 - sum_{j<i} w_j)) face by face,
-// the last interior face taking what is left.
+// the last interior face taking what is left (a single interior face takes
+// everything without a draw).
+//
+// scaled (ANY_SCALED instances; the alternative at the end of Sec. II.B): the
+// whole population ni is split at once with weights zeta w_i, and a molecule
+// that draws no face stays; if more than Ns would leave, the Ns present are
+// split as above.  1.0 * w == w exactly, so the plain split is the same there.
+//
+// The thinning and the faces' binomials share one loop: each pass draws once
+// (one inversion, or one attempt of BTRD's rejection) and a lane that accepts
+// goes on to its next binomial in the next pass, whatever the others do.  A
+// wavefront then runs as many passes as its slowest lane needs in all, not
+// the sum over the binomials of each one's slowest lane, and the samplers are
+// in the code once instead of five times (the update kernel 41 -> 21 KB).
+// Bound: the serial chain of one lane.  A bar of 1080 tets holding 93
+// molecules each took 64.7 us per period with one binomial after the other
+// and 41.5 us with this loop (queue-based one-launch path); tets of a few
+// molecules draw once or twice and took the same (the 750-tet cube 14.9 and
+// 14.7 us, the 384,000-tet batch 0.2373 and 0.2373 ms).  Returns n, and
+// out[].
 // ---------------------------------------------------------------------------
-__device__ inline void split_over_faces(int32_t n, const int32_t nbr[4], const double w[4], int32_t threshold,
-                                        Stream &rng, int32_t out[4])
+template <bool ANY_SCALED, class Rng>
+__device__ __forceinline__ int32_t leave_and_split(int32_t ni, int32_t Ns, double zeta, bool scaled,
+                                                   const int32_t nbr[4], const double weights[4],
+                                                   int32_t threshold, Rng &rng, int32_t out[4])
 {
-    out[0] = out[1] = out[2] = out[3] = 0;
-    if (n <= 0) return;
-    int last = -1, interior = 0;
-#pragma unroll
-    for (int f = 0; f < 4; ++f)
-        if (nbr[f] >= 0) {
-            last = f;
-            ++interior;
-        }
-    if (interior == 0) return;
-    if (interior == 1) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f)
-            if (f == last) out[f] = n;
-        return;
-    }
-    if (n < threshold) {
-        for (int32_t i = 0; i < n; ++i) {
-            const double u = rng.uniform();
-            double edge = 0.0;
-            int dest = last;
-#pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                if (f < last && nbr[f] >= 0 && dest == last) {
-                    edge = edge + w[f];
-                    if (u < edge) dest = f;
+    // scalars, selected by face: an index into the arrays would put them in memory
+    const double w0 = weights[0], w1 = weights[1], w2 = weights[2], w3 = weights[3];
+    const uint32_t faces = (nbr[0] >= 0 ? 1u : 0u) | (nbr[1] >= 0 ? 2u : 0u) | (nbr[2] >= 0 ? 4u : 0u) |
+                           (nbr[3] >= 0 ? 8u : 0u);  // the interior ones
+    const int interior = __popc(faces), last = 31 - __clz((int)faces);
+    bool thin = !(ANY_SCALED && scaled);
+    int32_t n = ni;
+    int32_t o0, o1, o2, o3;
+    const auto add = [&](int k, int32_t m) {
+        o0 += k == 0 ? m : 0;
+        o1 += k == 1 ? m : 0;
+        o2 += k == 2 ? m : 0;
+        o3 += k == 3 ? m : 0;
+    };
+    for (;;) {
+        const bool all = !(ANY_SCALED && scaled);  // every molecule of n leaves
+        const double z = all ? 1.0 : zeta;
+        o0 = o1 = o2 = o3 = 0;
+        int f = -1;
+        int32_t left = n;
+        double taken = 0.0;
+        double p = zeta;
+        bool draw = thin || (n >= threshold && n > 0 && interior > (all ? 1 : 0));
+        bool face = !thin;  // the next thing to do is to pick a face
+        while (__ballot(draw) != 0) {
+            if (!draw) continue;
+            if (face) {
+                // the next interior face and its probability
+                const uint32_t rest = f < 0 ? faces : faces & (0xfffffffeu << f);
+                f = rest ? __builtin_ctz(rest) : 4;
+                if (f > last || left == 0 || (all && f == last)) {
+                    if (all) add(last, left);
+                    draw = false;
+                    continue;
+                }
+                const double wf = f == 0 ? w0 : f == 1 ? w1 : f == 2 ? w2 : w3;
+                p = (z * wf) / (1.0 - taken);
+                if (p > 1.0) p = 1.0;
+                taken = taken + z * wf;
+            }
+            int32_t x = 0;
+            bool accepted = true;
+            if (left > 0 && p > 0.0) {
+                if (p >= 1.0) {
+                    x = left;
+                } else {
+                    const bool reflect = p > 0.5;
+                    const double pp = reflect ? 1.0 - p : p;
+                    if ((double)left * pp < 10.0)
+                        x = binomial_inversion(left, pp, rng);
+                    else
+                        accepted = btrd_pass(left, pp, rng, &x);
+                    if (reflect) x = left - x;
                 }
             }
-#pragma unroll
-            for (int f = 0; f < 4; ++f)
-                if (f == dest) out[f] += 1;
-        }
-        return;
-    }
-    int32_t left = n;
-    double taken = 0.0;
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        if (nbr[f] < 0 || left == 0) continue;
-        if (f == last) {
-            out[f] = left;
-            left = 0;
-            continue;
-        }
-        double pf = w[f] / (1.0 - taken);
-        if (pf > 1.0) pf = 1.0;
-        const int32_t nf = binomial(left, pf, rng);
-        out[f] = nf;
-        left -= nf;
-        taken = taken + w[f];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// The same split with both transfer forms in one body (the kernel instance
-// that serves simulations using the second form calls it; the first form
-// alone uses split_over_faces above, which needs fewer registers).
-// n_i = Binomial(n - sum_{j<i} n_j, z w_i / (1 - sum_{j<i} z w_j)) face by
-// face, or one categorical draw per molecule below the threshold:
-//  * Step 3.3 (scaled = false, z = 1): n molecules all leave; the last
-//    interior face closes the interval / takes what is left (a single
-//    interior face takes everything without a draw);
-//  * the alternative at the end of Sec. II.B (scaled = true, z = zeta): the
-//    whole population, weights zeta w_i, and a molecule that draws no face
-//    stays (probability 1 - zeta).
-// 1.0 * w == w exactly, so the first form is bit-identical to the plain
-// weights.  Returns the molecules that leave.
-// ---------------------------------------------------------------------------
-__device__ inline int32_t split_faces(int32_t n, const int32_t nbr[4], const double w[4], double z, bool scaled,
-                                      int32_t threshold, Stream &rng, int32_t out[4])
-{
-    out[0] = out[1] = out[2] = out[3] = 0;
-    if (n <= 0) return 0;
-    int last = -1, interior = 0;
-#pragma unroll
-    for (int f = 0; f < 4; ++f)
-        if (nbr[f] >= 0) {
-            last = f;
-            ++interior;
-        }
-    if (interior == 0) return 0;
-    if (!scaled && interior == 1) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f)
-            if (f == last) out[f] = n;
-        return n;
-    }
-    const int open = scaled ? -1 : last;  // where a molecule goes when no face's interval holds its draw
-    int32_t moved = 0;
-    if (n < threshold) {
-        for (int32_t i = 0; i < n; ++i) {
-            const double u = rng.uniform();
-            double edge = 0.0;
-            int dest = open;
-#pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                if (nbr[f] >= 0 && (scaled || f < last) && dest == open) {
-                    edge = edge + z * w[f];
-                    if (u < edge) dest = f;
-                }
+            face = accepted;
+            if (!accepted) continue;
+            if (f < 0) {  // the thinning
+                n = x < Ns ? x : Ns;
+                left = n;
+                draw = n >= threshold && n > 0 && interior > 1;
+            } else {
+                add(f, x);
+                left -= x;
             }
-#pragma unroll
-            for (int f = 0; f < 4; ++f)
-                if (f == dest) out[f] += 1;
-            moved += dest >= 0 ? 1 : 0;
         }
-        return moved;
-    }
-    int32_t left = n;
-    double taken = 0.0;
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        if (nbr[f] < 0 || left == 0) continue;
-        if (!scaled && f == last) {
-            out[f] = left;
-            moved += left;
-            left = 0;
-            continue;
+        if (n > 0 && all && interior == 1) {
+            add(last, n);
+        } else if (n > 0 && n < threshold && interior > 0) {
+            // a face's interval ends at the running sum of the weights; a draw
+            // past them all closes on the last face, or stays (scaled)
+            const uint32_t drawn = all ? faces & ~(1u << last) : faces;
+            const int open = all ? last : -1;
+            for (int32_t i = 0; i < n; ++i) {
+                const double u = rng.uniform();
+                double edge = 0.0;
+                int dest = open;
+                bool found = false;
+                const auto face_at = [&](int k, double wk) {
+                    if (((drawn >> k) & 1u) && !found) {
+                        edge = edge + z * wk;
+                        if (u < edge) {
+                            dest = k;
+                            found = true;
+                        }
+                    }
+                };
+                face_at(0, w0);
+                face_at(1, w1);
+                face_at(2, w2);
+                face_at(3, w3);
+                add(dest, 1);
+            }
         }
-        double pf = (z * w[f]) / (1.0 - taken);
-        if (pf > 1.0) pf = 1.0;
-        const int32_t nf = binomial(left, pf, rng);
-        out[f] = nf;
-        moved += nf;
-        left -= nf;
-        taken = taken + z * w[f];
+        out[0] = o0;
+        out[1] = o1;
+        out[2] = o2;
+        out[3] = o3;
+        if (all) return n;
+        const int32_t moved = (o0 + o1) + (o2 + o3);
+        if (moved <= Ns) return moved;
+        n = Ns;  // more would leave than are present: those present, split in the plain form
+        scaled = false;
     }
-    return moved;
 }
 
 }  // namespace rdos
