@@ -33,8 +33,11 @@ def kernel_source_hash():
     import re
 
     h = hashlib.sha256()
-    for f in ("rdos_kernels.hip", "rdos_sampling.h", "rdos_internal.h"):
-        with open(os.path.join(ROOT, "paper_1512_03126_amd", "csrc", f)) as fh:
+    for f in ("rdos_kernels.hip", "rdos_cell.h", "rdos_sampling.h", "rdos_internal.h"):
+        path = os.path.join(ROOT, "paper_1512_03126_amd", "csrc", f)
+        if not os.path.exists(path):
+            continue
+        with open(path) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
         text = re.sub(r"//[^\n]*", " ", text)

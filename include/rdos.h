@@ -218,16 +218,20 @@ rdos_status rdos_run_until(rdos_sim *s, double t_end);
 rdos_status rdos_step_static(rdos_sim *s, int64_t n_steps);
 
 /* How rdos_step and rdos_run_until launch the periods (results never depend
- * on it).  0 (default): a work list of at most 8 tiles (1024 tets per
- * realization and tile) runs all its periods in one cooperative launch, the
- * scan and update phases of each period separated by grid-wide barriers;
- * larger ones launch a scan and an update kernel per period.  1: always two
- * launches per period.  2: always one cooperative launch.  3: one fused
- * launch per period (each wavefront scans its tiles and updates the tets it
- * queued, no queue in device memory; simulations of more than 8 species
- * launch two kernels instead).  The one-launch path exists for small meshes,
- * where the gaps between launches dominate a period (the 1 um cube of
- * Sec. II.A's Fig. 2 example: 750 tets).  RDOS_EINVAL for other values. */
+ * on it).  0 (default): all periods of a call in one launch with the counts
+ * held in LDS, where a realization's counts fit the LDS of the device's
+ * compute units divided among the realizations (one block per realization:
+ * about 10,000 tet-species; a single realization: about 2.5 million);
+ * otherwise, for a single period of a larger work list, and on a stream that
+ * is being captured: a work list of at most 8 tiles (1024 tets per
+ * realization and tile) runs its periods in one cooperative launch over the
+ * occupied-tet queue, the scan and update phases of each period separated by
+ * grid-wide barriers, and larger ones launch a scan and an update kernel per
+ * period.  1: always two launches per period.  2: always one cooperative
+ * launch over the queue.  3: one fused launch per period (each wavefront
+ * scans its tiles and updates the tets it queued, no queue in device memory;
+ * simulations of more than 8 species launch two kernels instead).
+ * RDOS_EINVAL for other values. */
 rdos_status rdos_set_launch_mode(rdos_sim *s, int32_t mode);
 
 /* Waits for all queued work; reports RDOS_EOVERFLOW if raised. */

@@ -246,9 +246,9 @@ def rdos_run_until(sim, t_end: float):
 
 
 def rdos_set_launch_mode(sim, mode: int):
-    """0: one cooperative launch for small work lists (default), 1: two
-    launches per period, 2: always one launch, 3: one fused launch per
-    period (up to 8 species)."""
+    """0: the counts in LDS where they fit, all periods in one launch
+    (default), 1: two launches per period, 2: always one launch over the
+    queue, 3: one fused launch per period (up to 8 species)."""
     _check(lib().rdos_set_launch_mode(sim, int(mode)), sim)
 
 

@@ -146,6 +146,116 @@ void free_queue(QueueView *q, hipStream_t st)
     *q = QueueView{};
 }
 
+int32_t compute_units(int device)
+{
+    static std::mutex mu;
+    static std::map<int, int> known;
+    std::lock_guard<std::mutex> g(mu);
+    auto it = known.find(device);
+    if (it != known.end()) return it->second;
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
+    known[device] = n;
+    return n;
+}
+
+ResidentCut resident_cut(int32_t T, int32_t S, int32_t R, int32_t max_blocks)
+{
+    ResidentCut c;
+    // 16 tets: the occupancy bytes of a block's range are whole words
+    const int32_t k = std::max(1, std::min(max_blocks, (T + 15) / 16));
+    const int32_t len = k == 1 ? T : ((T + k - 1) / k + 15) & ~15;
+    const int64_t ls = ((int64_t)len + 3) & ~(int64_t)3;
+    if (S * ls > 0xffff || resident_lds_bytes(S, R, (int32_t)ls, 64) > kResidentLdsMax) return c;
+    c.len = len;
+    c.blocks = (T + len - 1) / len;
+    // a lane per (tet, species) pair, up to a block's limit
+    c.threads = (int32_t)std::min<int64_t>(kResidentMaxThreads, (S * ls + 63) & ~(int64_t)63);
+    c.lds_bytes = std::min(kResidentLdsMax, resident_lds_bytes(S, R, (int32_t)ls, c.threads));
+    return c;
+}
+
+// The cuts of a simulation's realizations for the resident kernel, alone and
+// over the device.  Several blocks per realization wait for each other, so
+// all must be on the device at once: no more than its compute units (a block
+// fills one).  With more blocks than compute units, blocks of half the size
+// share them: on 1000 realizations of the 750-tet cube 512 lanes took 18.0
+// us per period, 1024 lanes 25.5 and 256 lanes 19.8.
+static ResidentCut cut_one(const rdos_sim *s)
+{
+    ResidentCut c = resident_cut(s->T, (int32_t)s->D.size(), (int32_t)s->rx.size(), 1);
+    if (c.blocks && s->Rz > compute_units(s->device) && c.threads > 512) {
+        c.threads = 512;
+        c.lds_bytes = std::min(c.lds_bytes, resident_lds_bytes((int32_t)s->D.size(), (int32_t)s->rx.size(),
+                                                               (s->T + 3) & ~3, 512));
+    }
+    return c;
+}
+static ResidentCut cut_many(const rdos_sim *s)
+{
+    const int32_t k = compute_units(s->device) / s->Rz;
+    ResidentCut c;
+    if (k > 1) c = resident_cut(s->T, (int32_t)s->D.size(), (int32_t)s->rx.size(), k);
+    if (c.blocks < 2) c.blocks = 0;
+    return c;
+}
+
+static size_t resident_bytes(const rdos_sim *s)
+{
+    const int64_t one = cut_one(s).blocks, many = cut_many(s).blocks;
+    return (one ? resident_plan_bytes(s->Rz, 1) : 0) + (many ? resident_plan_bytes(many * s->Rz, many) : 0);
+}
+
+// Lays out the block list of one cut on the device (finalize; the caller has
+// uploaded the descriptor on the same stream).
+static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan *plan)
+{
+    *plan = ResidentPlan{};
+    if (c.blocks == 0) return RDOS_OK;
+    ResidentPlan p{};
+    p.blocks = c.blocks * s->Rz;
+    p.max_parts = c.blocks;
+    p.threads = c.threads;
+    p.lds_bytes = c.lds_bytes;
+    p.scaled = s->transfer_form == 1;
+    void *memory = nullptr;
+    {
+        std::lock_guard<std::mutex> g(device_api_mutex());
+        HIP_TRY(s, dev_alloc(&memory, resident_plan_bytes(p.blocks, p.max_parts), s->stream), "allocate block list");
+    }
+    resident_place(&p, memory);
+    *plan = p;
+    HIP_TRY(s, launch_resident_layout(s->d_desc, p, nullptr, 0, ResidentUnit{0, 0, s->T, 0, c.blocks, c.len},
+                                      s->stream),
+            "block list");
+    return RDOS_OK;
+}
+
+// The resident launch for n periods, or null: the two-launch (or one-launch)
+// path.  Several blocks per realization, unless one does as well: light
+// tets (on average two molecules per pair or fewer, by the counts last set)
+// with a lane each.  Measured: the cube of 750 tets at 1.3 molecules per tet
+// 6.0 us per period with one block, 6.5 with 47; a bar of 1080 tets at 93
+// molecules per tet 64 and 23.5.  A single period of a work list too large
+// for the one-launch path costs the same either way (0.51 ms with the
+// reading of 3 x 384,000 counts), without the cooperative launch.
+static const ResidentPlan *resident_for(const rdos_sim *s, int64_t n)
+{
+    if (s->launch_mode != 0) return nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+        return nullptr;  // the period counters of a replay would start over
+    const ResidentPlan &one = s->resident_one, &many = s->resident_many;
+    if (many.blocks == 0) return one.blocks ? &one : nullptr;
+    if (one.blocks) {
+        int64_t molecules = 0;
+        for (int64_t t : s->totals) molecules += t;
+        const int64_t pairs = (int64_t)s->T * (int64_t)s->D.size();
+        if (pairs <= kResidentMaxThreads && molecules <= 2 * pairs * s->Rz) return &one;
+    }
+    return n > 1 || s->n_tiles <= kPersistTiles ? &many : nullptr;
+}
+
 static int64_t tiles_of(const rdos_sim *s) { return (int64_t)s->Rz * ((s->T + kTetsPerTile - 1) / kTetsPerTile); }
 
 size_t state_bytes(const rdos_sim *s)
@@ -156,7 +266,7 @@ size_t state_bytes(const rdos_sim *s)
     const size_t masks = s->regions.empty() ? 0 : (size_t)s->T * sizeof(uint32_t);
     const size_t occupancy = 2 * (size_t)s->Rz * s->D.size() * mask_stride(Tp);
     return (size_t)s->T * sizeof(MeshRec) + 2 * counts + tiles + queue_bytes(tiles_of(s), (int32_t)s->D.size()) +
-           masks + occupancy + sizeof(DevSim) + 64;
+           masks + occupancy + resident_bytes(s) + sizeof(DevSim) + 64;
 }
 
 // Face-matching results are cached by mesh connectivity (the cell array):
@@ -450,6 +560,20 @@ int32_t persist_grid(rdos_sim *s)
 rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
 {
     if (n <= 0) return RDOS_OK;
+    if (const ResidentPlan *plan = resident_for(s, n)) {
+        const int64_t partial_index = partial ? s->step + n - 1 : -1;
+        s->mask_dirty = false;  // the kernel reads the counts and writes the occupancy bytes
+        while (n > 0) {
+            const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
+            HIP_TRY(s, launch_resident(s->d_desc, *plan, s->step, len, partial_index, tau_last, s->resident_epoch,
+                                       s->stream),
+                    "launch periods");
+            s->resident_epoch += len;
+            s->step += len;
+            n -= len;
+        }
+        return RDOS_OK;
+    }
     const int32_t grid = persist_grid(s);
     if (grid <= 0) {
         for (int64_t i = 0; i < n; ++i) {
@@ -485,8 +609,17 @@ void free_device(rdos_sim *s)
     (void)hipSetDevice(s->device);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     std::lock_guard<std::mutex> g(device_api_mutex());
-    void *ptrs[] = {s->d_mesh, s->d_buf[0], s->d_buf[1], s->d_mask[0], s->d_mask[1], s->d_flags, s->d_desc,
-                    s->d_tiles, s->d_allowed};
+    void *ptrs[] = {s->d_mesh,
+                    s->d_buf[0],
+                    s->d_buf[1],
+                    s->d_mask[0],
+                    s->d_mask[1],
+                    s->d_flags,
+                    s->d_desc,
+                    s->d_tiles,
+                    s->d_allowed,
+                    s->resident_one.done,
+                    s->resident_many.done};
     for (void *p : ptrs) dev_free(p, s->stream);
     free_queue(&s->queue, s->stream);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
@@ -496,6 +629,7 @@ void free_device(rdos_sim *s)
     s->d_buf[0] = s->d_buf[1] = s->d_flags = nullptr;
     s->d_desc = nullptr;
     s->d_tiles = nullptr;
+    s->resident_one = s->resident_many = ResidentPlan{};
     if (s->stream && s->own_stream) (void)hipStreamDestroy(s->stream);
     s->stream = nullptr;
 }
@@ -919,6 +1053,8 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
         return hip_fail(s, e, "queue header");
     }
     st = upload_desc(s);
+    if (st == RDOS_OK) st = plan_resident(s, cut_one(s), &s->resident_one);
+    if (st == RDOS_OK) st = plan_resident(s, cut_many(s), &s->resident_many);
     if (st != RDOS_OK) {
         free_device(s);
         return st;
@@ -928,12 +1064,14 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
     s->step = 0;
     s->anchor_step = 0;
     s->anchor_t = 0.0;
+    s->totals.assign((size_t)s->Rz * S, 0);
     // counts staged before finalize
     for (auto &kv : s->staged) {
         const int32_t r = kv.first / kMaxSpecies, m = kv.first % kMaxSpecies;
         int32_t *dst = s->d_buf[0] + ((int64_t)r * S + m) * Tp;
         HIP_TRY(s, hipMemcpyAsync(dst, kv.second.data(), (size_t)T * sizeof(int32_t), hipMemcpyHostToDevice, s->stream),
                 "upload counts");
+        for (int32_t c : kv.second) s->totals[(size_t)r * S + m] += c;
     }
     HIP_TRY(s, hipStreamSynchronize(s->stream), "upload counts");
     s->mask_dirty = true;
@@ -967,6 +1105,7 @@ rdos_status rdos_set_counts(rdos_sim *s, int32_t realization, int32_t species, c
             "upload counts");
     HIP_TRY(s, hipStreamSynchronize(s->stream), "upload counts");
     s->mask_dirty = true;
+    s->totals[(size_t)realization * s->D.size() + species] = total;
     return RDOS_OK;
 }
 

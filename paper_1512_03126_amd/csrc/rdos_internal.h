@@ -207,6 +207,73 @@ int32_t persist_grid_limit(const QueueView &q);
 hipError_t launch_persist(const DevSim *sims, const Tile *tiles, int64_t iter0, int32_t n_periods, int32_t phase,
                           int64_t partial, double tau_last, const QueueView &q, int32_t grid, uint32_t *sync,
                           hipStream_t st);
+// State held in LDS (rdos_resident.hip).  A realization is cut into `parts`
+// ranges of consecutive tets, one block each; a block keeps its range's
+// counts in LDS for a whole run of periods.
+struct ResidentPart {
+    int32_t sim;
+    int32_t realization;
+    int32_t t0, len;      // its tets; t0 a multiple of 16, len too except at the end of the mesh
+    int32_t part, parts;  // its place among the realization's blocks
+    int32_t stride;       // tets per block of the realization (the last may hold fewer)
+    int32_t flag0;        // the realization's first block
+    int32_t neighbours;   // blocks it exchanges molecules with
+    int32_t pad[3];
+};
+// One realization of a work list, for building the parts on the device.
+struct ResidentUnit {
+    int32_t sim;
+    int32_t realization;
+    int32_t T;
+    int32_t first;   // its first block
+    int32_t blocks;
+    int32_t len;     // tets per block
+};
+struct ResidentPlan {
+    unsigned long long *done;   // [blocks][kResidentFlagStride] last period finished by each block, then the
+                                // failure word (device)
+    ResidentPart *parts;        // [blocks] (device)
+    uint16_t *neighbours;       // [blocks][max_parts] (device; max_parts > 1)
+    int32_t blocks;
+    int32_t max_parts;          // blocks of the realization with the most; above 1 the launches are cooperative
+    int32_t threads;
+    int32_t lds_bytes;
+    int32_t scaled;             // some simulation uses transfer form 1
+};
+constexpr int kResidentMaxThreads = 1024;
+constexpr int kResidentMaxParts = 1024;
+constexpr int32_t kResidentLdsMax = 160 * 1024;
+constexpr int kResidentFlagStride = 16;  // 128 bytes between blocks' period counters
+constexpr int32_t kResidentHeadBytes = kMaxSpecies * 8 + kMaxReactions * 16 + 16;
+// LDS of a block whose species rows hold `ls` tets (a multiple of 4): two
+// count buffers, the list of pairs, and with reactions the rounded mean
+// populations and the list of tets for the SSA.
+__host__ __device__ inline int32_t resident_state_bytes(int32_t S, int32_t R, int32_t ls)
+{
+    const int32_t P = S * ls;
+    return kResidentHeadBytes + ((10 * P + (R > 0 ? 4 * P + 2 * ls : 0) + 15) & ~15);
+}
+// A lane's share in the SSA: occupancy integrals, times, constants and
+// propensities.
+__host__ __device__ inline int32_t resident_lane_bytes(int32_t S, int32_t R) { return 16 * (S + R); }
+// Both, for `lanes` lanes in the SSA (64 at least).
+__host__ __device__ inline int32_t resident_lds_bytes(int32_t S, int32_t R, int32_t ls, int32_t lanes)
+{
+    return resident_state_bytes(S, R, ls) + (R > 0 ? resident_lane_bytes(S, R) * lanes : 0);
+}
+// Device memory of a plan, and its arrays' places in it (16-byte aligned).
+size_t resident_plan_bytes(int64_t blocks, int64_t max_parts);
+void resident_place(ResidentPlan *plan, void *memory);
+// Fills the arrays of a plan: its blocks are those of n_units units whose
+// `first` fields ascend from 0 without gaps, or (units null) of the
+// realizations of one simulation, each cut like `same`.
+hipError_t launch_resident_layout(const DevSim *sims, const ResidentPlan &plan, const ResidentUnit *units,
+                                  int32_t n_units, const ResidentUnit &same, hipStream_t st);
+// n_periods periods of every part: the iterations iter0 .. of its simulation
+// (the period equal to `partial` lasts tau_last).  `epoch` is at least every
+// value in plan.done; the launch raises them to at most epoch + n_periods.
+hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t iter0, int32_t n_periods,
+                           int64_t partial, double tau_last, unsigned long long epoch, hipStream_t st);
 // Rebuilds the occupancy bytes of buf[parity] from the counts of every
 // realization and species and clears those of the other buffer (after
 // counts were set from the host).

@@ -1,0 +1,652 @@
+// Periods of Algorithm 1 with the state held in LDS: one launch runs a whole
+// run of periods, each block keeping the counts of its own tets in LDS.
+//
+// What bounds it: the serial chain of a period in one block, about ten cycles
+// per instruction with a wavefront or two per SIMD.  The two-launch path pays
+// two launches and five dependent trips to memory on top of the same chain,
+// and one lane per tet works its species in turn; here the counts never leave
+// LDS, a lane takes a (tet, species) pair (the SSA, which couples the
+// species, runs before, one lane per tet), and only molecules that cross into
+// another block's tets go through memory.
+//   * Split.  A realization is cut into as many blocks as the device holds at
+//     once (16 tets at least): crowded tets gain from every split (1080 tets
+//     of 93 molecules: 64, 33, 27, 23.5 us per period with 1, 8, 34 and 68
+//     blocks), sparse ones hardly lose (the 750-tet cube 6.0 us with one
+//     block, 6.5 with 47; 384,000 tets at 2% occupancy 10.2 us with 128
+//     blocks, 9.4 with 256).  Realizations beyond that run one block each.
+//   * Exchange.  Arrivals from other blocks are added to the realization's
+//     own count buffer of the next period (all zero until then) by agent-scope
+//     atomics; a block publishes the period it has finished, waits for the
+//     blocks that share a face with it only, and moves what arrived into LDS.
+//     Waiting for every block cost 4.1 us per period on the 384,000-tet mesh,
+//     waiting for neighbours 2.5.  Nothing else is written during a run, so
+//     no cache has to be written back: all shared words are read and written
+//     by agent-scope atomics.
+//   * Two count buffers alternate by parity, as in memory.  A neighbour adds
+//     to the buffer of period k + 2 only after this block has published
+//     period k + 1, by when it has emptied that buffer of period k's arrivals.
+// Measured, us per period, two launches (or the queue-based one launch) and
+// this kernel: 750-tet cube 14.4 and 6.0; 1080-tet bar at 93 molecules per
+// tet 41.5 and 23.5; ten species on that bar 105 and 25; 1000 realizations of
+// the cube with production 33 and 18; 384,000 tets at 2% 14.8 and 8.9, with a
+// fourth species and jitter 20.3 and 11.7; 162,000 tets at 30 molecules per
+// species and tet 292 and 115.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "rdos_cell.h"
+#include "rdos_internal.h"
+
+#pragma clang fp contract(off)
+
+namespace rdos {
+
+namespace {
+
+// A reaction as the SSA reads it: one 16-byte LDS load.
+struct alignas(16) ResidentReaction {
+    double k;
+    uint32_t shape;   // order, then five bits each: r0, r1, p0, p1, p2 (kNoSpecies: none)
+    uint32_t masks;   // low half: species involved; high half: species that must be present
+    static constexpr uint32_t kNoSpecies = 31;
+    __device__ __forceinline__ int order() const { return (int)(shape & 3u); }
+    __device__ __forceinline__ int species(int i) const { return (int)((shape >> (2 + 5 * i)) & 31u); }
+    __device__ __forceinline__ uint32_t involved() const { return masks & 0xffffu; }
+    __device__ __forceinline__ uint32_t needed() const { return masks >> 16; }
+};
+
+// Block-wide LDS words before the arrays (see resident_lds_bytes).
+struct ResidentHead {
+    double D[kMaxSpecies];
+    ResidentReaction rx[kMaxReactions];
+    int32_t n_ssa;    // tets listed for the SSA
+    int32_t n_pairs;  // (tet, species) pairs listed for Step 3
+    int32_t stop;     // a wait for other blocks failed
+    int32_t pad;
+};
+static_assert(sizeof(ResidentHead) == kResidentHeadBytes, "LDS head");
+
+__device__ __forceinline__ uint32_t pack_species(int32_t n, int i, int32_t id)
+{
+    return (i < n ? (uint32_t)id : ResidentReaction::kNoSpecies);
+}
+
+__device__ __forceinline__ ResidentReaction pack_reaction(const DevSim &sm, int q)
+{
+    ResidentReaction r;
+    const int32_t rn = sm.rn[q], pn = sm.pn[q];
+    const uint32_t a = pack_species(rn, 0, sm.r0[q]), b = pack_species(rn, 1, sm.r1[q]);
+    r.k = sm.k[q];
+    r.shape = (uint32_t)rn | (a << 2) | (b << 7) | (pack_species(pn, 0, sm.p0[q]) << 12) |
+              (pack_species(pn, 1, sm.p1[q]) << 17) | (pack_species(pn, 2, sm.p2[q]) << 22);
+    r.masks = sm.involved[q] | ((rn > 0 ? 1u << a : 0u) | (rn > 1 ? 1u << b : 0u)) << 16;
+    return r;
+}
+
+// One lane's tet in the SSA: its counts are the block's own, the rest belongs
+// to the lane.
+struct ResidentCell {
+    int32_t *N;
+    double *lane;      // occ[S], last[S], c[R], a[R], `lanes` apart
+    int32_t stride;    // between species of N
+    int32_t lanes;
+    int32_t S, R;
+    __device__ __forceinline__ int32_t &n(int s) const { return N[s * stride]; }
+    __device__ __forceinline__ double &occ(int s) const { return lane[s * lanes]; }
+    __device__ __forceinline__ double &last(int s) const { return lane[(S + s) * lanes]; }
+    __device__ __forceinline__ double &c(int q) const { return lane[(2 * S + q) * lanes]; }
+    __device__ __forceinline__ double &a(int q) const { return lane[(2 * S + R + q) * lanes]; }
+};
+
+// Step 2 for one tet (as cell_ssa, the same operations in the same order):
+// the constants c_r are computed once for the tet, the propensities of an
+// event are kept for the choice of its reaction, and a reaction's fields come
+// from LDS in one load.  Returns the species some event touched.
+__device__ __forceinline__ uint32_t resident_ssa(const DevSim &sm, const ResidentHead &head, int32_t t,
+                                                 uint32_t period32, double tau_k, uint32_t key1,
+                                                 const ResidentCell &cell)
+{
+    const int R = cell.R;
+    const double nav = sm.mesh[t].nav;
+    const uint32_t allowed = sm.allowed ? sm.allowed[t] : 0xffffffffu;
+    for (int q = 0; q < R; ++q) {
+        const ResidentReaction x = head.rx[q];
+        const int order = x.order();
+        const double c = order == 1 ? x.k : (order == 0 ? x.k * nav : x.k / nav);
+        cell.c(q) = (allowed >> q) & 1u ? c : 0.0;
+    }
+    uint32_t touched = 0;
+    Stream ssa(sm.key0, key1, kSsaStream, (uint32_t)t, period32);
+    double now = 0.0;
+    for (uint32_t events = 0;; ++events) {
+        if (events >= kMaxEventsPerPeriod) {  // runaway rates: stop and report, never hang
+            atomicOr(sm.flags, 2);
+            break;
+        }
+        double a0 = 0.0;
+        for (int q0 = 0; q0 < R; q0 += 2) {  // two at a time, their loads in flight together
+            double a[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int q = min(q0 + j, R - 1);
+                const ResidentReaction x = head.rx[q];
+                const int order = x.order();
+                const int32_t na = cell.n(order > 0 ? x.species(0) : 0);
+                const int32_t nb = cell.n(order > 1 ? x.species(1) : 0);
+                double h = order > 0 ? (double)na : 1.0;
+                if (order == 2) h = h * (double)(x.species(0) == x.species(1) ? na - 1 : nb);
+                a[j] = h == 0.0 ? 0.0 : cell.c(q) * h;
+                cell.a(q) = a[j];
+            }
+            a0 = a0 + a[0];
+            if (q0 + 1 < R) a0 = a0 + a[1];
+        }
+        if (!(a0 > 0.0)) break;
+        const double dt = -log_basic(1.0 - ssa.uniform()) / a0;
+        if (now + dt >= tau_k) break;
+        now = now + dt;
+        const double x = ssa.uniform() * a0;
+        int chosen = -1;
+        double cum = 0.0;
+        for (int q = 0; q < R; ++q) {
+            cum = cum + cell.a(q);
+            if (x < cum) {
+                chosen = q;
+                break;
+            }
+        }
+        if (chosen < 0) {  // x rounded up to a0: the last reaction able to fire
+            for (int q = R - 1; q >= 0; --q)
+                if (cell.a(q) > 0.0) {
+                    chosen = q;
+                    break;
+                }
+        }
+        const ResidentReaction r = head.rx[chosen];
+        for (uint32_t inv = r.involved(); inv; inv &= inv - 1u) {
+            const int s = __builtin_ctz(inv);
+            const bool seen = (touched >> s) & 1u;
+            const double o = seen ? cell.occ(s) : 0.0;
+            const double l = seen ? cell.last(s) : 0.0;
+            int32_t ns = cell.n(s);
+            cell.occ(s) = o + (double)ns * (now - l);
+            cell.last(s) = now;
+            ns += (int)(s == r.species(2)) + (int)(s == r.species(3)) + (int)(s == r.species(4)) -
+                  (int)(s == r.species(0)) - (int)(s == r.species(1));
+            cell.n(s) = ns;
+            if (ns > 0x3fffffff) atomicOr(sm.flags, 1);
+        }
+        touched |= r.involved();
+    }
+    return touched;
+}
+
+// The lanes' exclusive prefix sum of v (v < 2^bits), and the total.
+__device__ __forceinline__ int32_t wave_prefix(uint32_t v, int bits, int32_t *total)
+{
+    int32_t before = 0, sum = 0;
+    for (int k = 0; k < bits; ++k) {
+        const uint64_t plane = __ballot((v >> k) & 1u);
+        before += (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(plane >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)plane, 0u))
+                  << k;
+        sum += __popcll(plane) << k;
+    }
+    *total = sum;
+    return before;
+}
+
+// Room for `total` entries of a block's list (one LDS atomic per wavefront).
+__device__ __forceinline__ int32_t reserve(int32_t *count, int32_t total)
+{
+    int32_t base = 0;
+    if (__lane_id() == 0) base = atomicAdd(count, total);
+    return __builtin_amdgcn_readfirstlane(base);
+}
+
+// Moves what other blocks added to four tets into the block's counts d.
+__device__ __forceinline__ void take_arrivals(gptr<unsigned long long> p, int32_t *d)
+{
+    const unsigned long long lo = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long hi = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((lo | hi) == 0) return;
+    __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    d[0] += (int32_t)(uint32_t)lo;
+    d[1] += (int32_t)(uint32_t)(lo >> 32);
+    d[2] += (int32_t)(uint32_t)hi;
+    d[3] += (int32_t)(uint32_t)(hi >> 32);
+}
+
+// Blocks of up to this many four-tet groups (over all species) read every
+// group for arrivals; larger ones read the occupancy bytes first.
+constexpr int32_t kDirectGroups = 2048;
+
+// Waits until every neighbouring block has published `target` (first
+// wavefront; each lane watches one of them, mine, and any beyond 64 in turn).
+// Bounded: a wait past its limit raises *fail, which ends every other wait.
+constexpr uint32_t kWaitSpins = 1u << 28;  // minutes: a neighbour may be deep in a long SSA
+__device__ __forceinline__ bool wait_neighbours(const unsigned long long *done, const uint16_t *list, int32_t n,
+                                                int32_t mine, unsigned long long target, uint32_t *fail)
+{
+    const int32_t lane = (int32_t)__lane_id();
+    for (uint32_t spins = 0;; ++spins) {
+        bool all = lane >= n || __hip_atomic_load(&done[(int64_t)mine * kResidentFlagStride], __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT) >= target;
+        for (int32_t j = lane + 64; j < n; j += 64)
+            all &= __hip_atomic_load(&done[(int64_t)list[j] * kResidentFlagStride], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT) >= target;
+        if (__ballot(!all) == 0) return true;
+        if ((spins & 63u) == 63u) {
+            if (__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return false;
+            if (spins > kWaitSpins) {
+                if (lane == 0) atomicOr(fail, 1u);
+                return false;
+            }
+        }
+    }
+}
+
+}  // namespace
+
+// Fills parts[blockIdx.x] from the realization it belongs to, its list of
+// neighbours (the blocks that hold a face neighbour of one of its tets: their
+// places among the realization's blocks, plan.max_parts entries per block)
+// and its period counter.
+__global__ __launch_bounds__(256) void resident_layout_kernel(const DevSim *__restrict__ sims,
+                                                              const ResidentUnit *__restrict__ units,
+                                                              int32_t n_units, ResidentUnit same, ResidentPlan plan)
+{
+    __shared__ uint32_t seen[kResidentMaxParts / 32];
+    __shared__ int32_t n;
+    const int32_t b = (int32_t)blockIdx.x;
+    ResidentUnit u = same;  // one simulation: its realizations are cut alike
+    if (units) {            // the last unit that starts at or before this block
+        int32_t lo = 0, hi = n_units - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (units[mid].first <= b)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        u = units[lo];
+    } else {
+        u.realization = b / u.blocks;
+        u.first = u.realization * u.blocks;
+    }
+    ResidentPart pt{};
+    pt.sim = u.sim;
+    pt.realization = u.realization;
+    pt.part = b - u.first;
+    pt.parts = u.blocks;
+    pt.stride = u.len;
+    pt.t0 = pt.part * u.len;
+    pt.len = min(u.len, u.T - pt.t0);
+    pt.flag0 = u.first;
+    for (int k = threadIdx.x; k < kResidentMaxParts / 32; k += blockDim.x) seen[k] = 0;
+    if (threadIdx.x == 0) n = 0;
+    __syncthreads();
+    if (u.blocks > 1) {
+        const MeshRec *mesh = sims[u.sim].mesh;
+        for (int32_t i = threadIdx.x; i < pt.len; i += blockDim.x) {
+            const int4 nb = *reinterpret_cast<const int4 *>(mesh[pt.t0 + i].nbr);
+            const int32_t other[4] = {nb.x, nb.y, nb.z, nb.w};
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                if (other[f] < 0 || (uint32_t)(other[f] - pt.t0) < (uint32_t)pt.len) continue;
+                const int32_t q = other[f] / u.len;
+                atomicOr(&seen[q >> 5], 1u << (q & 31));
+            }
+        }
+        __syncthreads();
+        for (int32_t q = threadIdx.x; q < u.blocks; q += blockDim.x)
+            if ((seen[q >> 5] >> (q & 31)) & 1u)
+                plan.neighbours[(int64_t)b * plan.max_parts + atomicAdd(&n, 1)] = (uint16_t)q;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        pt.neighbours = n;
+        plan.parts[b] = pt;
+        plan.done[(int64_t)b * kResidentFlagStride] = 0;
+        if (b == 0) plan.done[(int64_t)plan.blocks * kResidentFlagStride] = 0;
+    }
+}
+
+hipError_t launch_resident_layout(const DevSim *sims, const ResidentPlan &plan, const ResidentUnit *units,
+                                  int32_t n_units, const ResidentUnit &same, hipStream_t st)
+{
+    if (plan.blocks < 1) return hipErrorInvalidValue;
+    resident_layout_kernel<<<plan.blocks, 256, 0, st>>>(sims, units, n_units, same, plan);
+    return hipGetLastError();
+}
+
+size_t resident_plan_bytes(int64_t blocks, int64_t max_parts)
+{
+    return (size_t)blocks * (sizeof(ResidentPart) + kResidentFlagStride * sizeof(unsigned long long)) + 128 +
+           (max_parts > 1 ? (size_t)blocks * max_parts * sizeof(uint16_t) : 0);
+}
+
+void resident_place(ResidentPlan *plan, void *memory)
+{
+    char *p = static_cast<char *>(memory);
+    plan->done = reinterpret_cast<unsigned long long *>(p);  // the counters, then the failure word
+    p += (size_t)plan->blocks * kResidentFlagStride * sizeof(unsigned long long) + 128;
+    plan->parts = reinterpret_cast<ResidentPart *>(p);
+    p += (size_t)plan->blocks * sizeof(ResidentPart);
+    plan->neighbours = plan->max_parts > 1 ? reinterpret_cast<uint16_t *>(p) : nullptr;
+}
+
+// n_periods periods of the block's part (parts[blockIdx.x]) of one
+// realization, the iterations iter0 .. of its simulation.
+template <bool ANY_SCALED>
+__global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
+    const DevSim *__restrict__ sims, const ResidentPart *__restrict__ parts,
+    const uint16_t *__restrict__ neighbours, int32_t max_parts, int64_t iter0, int32_t n_periods, int64_t partial,
+    double tau_last, unsigned long long *done_all, unsigned long long epoch, uint32_t *fail, int32_t lds_bytes)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    ResidentHead &head = *reinterpret_cast<ResidentHead *>(lds);
+    const int32_t tid = (int32_t)threadIdx.x, nt = (int32_t)blockDim.x;
+    const ResidentPart pt = parts[blockIdx.x];
+    using ConstSim = const __attribute__((address_space(4))) DevSim;
+    ConstSim *desc = (ConstSim *)sims + pt.sim;
+    const DevSim &sm = *(const DevSim *)desc;
+    const int32_t S = sm.S, R = sm.R;
+    const int64_t first = sm.step0 + iter0;
+    const int64_t left = sm.step_end - first;
+    if (left <= 0) return;  // uniform over the unit's blocks
+    if (left < n_periods) n_periods = (int32_t)left;
+
+    const int32_t len = pt.len, t0 = pt.t0;
+    const int32_t ls = (len + 3) & ~3;  // stride between species rows
+    const int32_t P = S * ls;
+    const uint32_t per_species = (uint32_t)(0xffffffffu / (uint32_t)ls + 1u);  // e / ls == umulhi(e, per_species)
+    int32_t *counts = reinterpret_cast<int32_t *>(lds + kResidentHeadBytes);   // [2][P]
+    int32_t *pop = counts + 2 * P;                                             // [P] when R > 0
+    uint16_t *list = reinterpret_cast<uint16_t *>(pop + (R > 0 ? P : 0));      // [P]
+    uint16_t *ssa_list = list + P;                                             // [ls] when R > 0
+    const int32_t used = resident_state_bytes(S, R, ls);
+    double *lane_state = reinterpret_cast<double *>(lds + used);
+    const int32_t lanes = R > 0 ? min(nt, ((lds_bytes - used) / resident_lane_bytes(S, R)) & ~63) : 0;
+
+    const int64_t Tp = ((int64_t)sm.T + 3) & ~(int64_t)3;
+    const int64_t base = (int64_t)pt.realization * S * Tp;
+    const int64_t mbase = (int64_t)pt.realization * S * sm.mstride;
+    const uint32_t key1 = sm.key1 ^ (uint32_t)pt.realization;
+    const bool alone = pt.parts == 1;
+    const bool direct = S * ((pt.stride + 3) / 4) <= kDirectGroups;
+    unsigned long long *done = done_all + (int64_t)pt.flag0 * kResidentFlagStride;
+    const uint16_t *nlist = neighbours + (int64_t)blockIdx.x * max_parts;
+    const int32_t my_neighbour = !alone && tid < 64 && tid < pt.neighbours ? nlist[tid] : 0;
+
+    if (tid < S) head.D[tid] = sm.D[tid];
+    if (tid < R) head.rx[tid] = pack_reaction(sm, tid);
+    if (tid == 0) head.n_ssa = head.n_pairs = head.stop = 0;
+    {
+        const gptr<int32_t> src = global(sm.buf[first & 1]) + base + t0;
+        for (int32_t v = tid; v < P / 4; v += nt) {
+            const int32_t s = (int32_t)__umulhi(4u * (uint32_t)v, per_species);
+            const gptr<v4i> p = (gptr<v4i>)(src + s * Tp + (4 * v - s * ls));
+            *reinterpret_cast<v4i *>(counts + 4 * v) = *p;
+            *reinterpret_cast<v4i *>(counts + P + 4 * v) = v4i{0, 0, 0, 0};
+            if (!alone) {  // neighbours add to this buffer from the second period on
+                const gptr<unsigned long long> z = (gptr<unsigned long long>)p;
+                __hip_atomic_store(z, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(z + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    __syncthreads();
+
+    // the species each reaction needs, reaction q's in lane q
+    const uint32_t need_of_lane = (int32_t)__lane_id() < R ? head.rx[__lane_id()].needed() : 0u;
+
+    for (int32_t k = 0; k < n_periods; ++k) {
+        // read the descriptor's fields in the period that uses them: held
+        // across the loop they are more than the scalar registers hold
+        ConstSim *now = desc;
+        asm volatile("" : "+s"(now));
+        const DevSim &sm = *(const DevSim *)now;
+        const int64_t period = first + k;
+        const uint32_t period32 = (uint32_t)period;
+        const double tau_k = period == partial ? tau_last : sm.tau;
+        int32_t *cur = counts + (k & 1) * P, *nxt = counts + ((k & 1) ^ 1) * P;
+
+        // List the (tet, species) pairs that hold molecules, and the tets
+        // where a reaction's reactants are all present.  A lane takes the
+        // four tets of a group, every species (one 16-byte LDS load each).
+        for (int32_t g0 = 0; g0 < ls / 4; g0 += nt) {
+            const int32_t i = 4 * (g0 + tid);
+            uint32_t held[4] = {0, 0, 0, 0};
+            if (i < ls) {
+                int32_t sign = 0;
+                for (int s0 = 0; s0 < S; s0 += 4) {  // four loads in flight; past the last species it repeats
+                    v4i c[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        c[j] = *reinterpret_cast<const v4i *>(cur + min(s0 + j, S - 1) * ls + i);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int s = min(s0 + j, S - 1);
+                        sign |= c[j].x | c[j].y | c[j].z | c[j].w;
+                        held[0] |= (uint32_t)(c[j].x != 0) << s;
+                        held[1] |= (uint32_t)(c[j].y != 0) << s;
+                        held[2] |= (uint32_t)(c[j].z != 0) << s;
+                        held[3] |= (uint32_t)(c[j].w != 0) << s;
+                    }
+                }
+                if (sign < 0) {  // a count wrapped by an overflowing addition: reported, and dropped
+                    atomicOr(sm.flags, 1);
+                    for (int s = 0; s < S; ++s)
+                        for (int b = 0; b < 4; ++b) cur[s * ls + i + b] = max(cur[s * ls + i + b], 0);
+                }
+            }
+            int32_t total;
+            const uint32_t n = __popc(held[0]) + __popc(held[1]) + __popc(held[2]) + __popc(held[3]);
+            int32_t at = wave_prefix(n, 32 - __builtin_clz(4 * S), &total);
+            if (total > 0) {
+                at += reserve(&head.n_pairs, total);
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    for (uint32_t m = held[b]; m; m &= m - 1u) list[at++] = (uint16_t)(__builtin_ctz(m) * ls + i + b);
+            }
+            if (R > 0 && (total > 0 || sm.zeroth)) {
+                uint32_t can[4] = {0, 0, 0, 0};
+                for (int q = 0; q < R; ++q) {
+                    const uint32_t need = __builtin_amdgcn_readlane(need_of_lane, q);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) can[b] |= (uint32_t)((held[b] & need) == need) << q;
+                }
+                uint32_t fire = 0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    if (i + b >= len) can[b] = 0;
+                    if (can[b] && sm.allowed) can[b] &= sm.allowed[t0 + i + b];
+                    fire |= (uint32_t)(can[b] != 0) << b;
+                }
+                at = wave_prefix(__popc(fire), 3, &total);
+                if (total > 0) {
+                    at += reserve(&head.n_ssa, total);
+                    for (; fire; fire &= fire - 1u) ssa_list[at++] = (uint16_t)(i + __builtin_ctz(fire));
+                }
+            }
+        }
+        __syncthreads();
+
+        // Step 2
+        if (R > 0) {
+            const int32_t n_ssa = head.n_ssa;
+            if (n_ssa > 0) {  // uniform over the block
+                for (int32_t j = tid; j < n_ssa && tid < lanes; j += lanes) {
+                    const int32_t i = ssa_list[j], t = t0 + i;
+                    const ResidentCell cell{cur + i, lane_state + tid, ls, lanes, S, R};
+                    uint32_t held = 0;
+                    for (int s = 0; s < S; ++s) held |= (uint32_t)(cell.n(s) != 0) << s;
+                    uint32_t touched = resident_ssa(sm, head, t, period32, tau_k, key1, cell);
+                    // the touched species that still hold molecules: eq. 2
+                    // and the stochastic rounding; bit 31 of the count tells
+                    // Step 3 to take them from pop[]
+                    for (; touched; touched &= touched - 1u) {
+                        const int s = __builtin_ctz(touched);
+                        const int32_t Ns = cell.n(s);
+                        if (Ns <= 0) continue;
+                        if (!((held >> s) & 1u)) list[atomicAdd(&head.n_pairs, 1)] = (uint16_t)(s * ls + i);
+                        if (sm.first_order || !((sm.diff_mask >> s) & 1u)) continue;
+                        const double nbar = mean_occupancy(cell, s, Ns, tau_k);
+                        int32_t ni = (int32_t)floor(nbar);
+                        const double frac = nbar - (double)ni;
+                        uint32_t drew = 0;
+                        if (frac > 0.0) {
+                            Stream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
+                            if (rng.uniform() < frac) ni += 1;
+                            drew = 0x80000000u;
+                        }
+                        pop[s * ls + i] = (int32_t)((uint32_t)ni | drew);
+                        cell.n(s) = (int32_t)((uint32_t)Ns | 0x80000000u);
+                    }
+                }
+                __syncthreads();
+                if (tid == 0) head.n_ssa = 0;
+            }
+        }
+
+        // Step 3: one lane per pair
+        const int32_t n_pairs = head.n_pairs;
+        for (int32_t j = tid; j < n_pairs; j += nt) {
+            const uint32_t e = list[j];
+            const int32_t s = (int32_t)__umulhi(e, per_species);
+            const int32_t t = t0 + (int32_t)e - s * ls;
+            const uint32_t raw = (uint32_t)cur[e];
+            cur[e] = 0;
+            const int32_t Ns = (int32_t)(raw & 0x7fffffffu);
+            int32_t stay = Ns;
+            if (Ns > 0 && ((sm.diff_mask >> s) & 1u)) {
+                const MeshRec *mr = sm.mesh + t;
+                const int4 n4 = *reinterpret_cast<const int4 *>(mr->nbr);
+                const int32_t nb[4] = {n4.x, n4.y, n4.z, n4.w};
+                const double w[4] = {mr->w[0], mr->w[1], mr->w[2], mr->w[3]};
+                const double g = mr->g;
+                PrimedStream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
+                int32_t ni = Ns;
+                if (raw >> 31) {
+                    const uint32_t code = (uint32_t)pop[e];
+                    ni = (int32_t)(code & 0x7fffffffu);
+                    if (code >> 31) (void)rng.uniform();  // the rounding's draw
+                }
+                double zeta = (tau_k * head.D[s]) * g;
+                if (zeta > 1.0) zeta = 1.0;
+                int32_t out[4];
+                const int32_t n = leave_and_split<ANY_SCALED>(ni, Ns, zeta, sm.transfer_form == 1, nb, w,
+                                                              sm.split_threshold, rng, out);
+                if (n > 0) {
+                    stay = Ns - n;
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) {
+                        if (out[f] <= 0) continue;
+                        const int32_t i = nb[f] - t0;
+                        if ((uint32_t)i < (uint32_t)len) {
+                            atomicAdd(&nxt[s * ls + i], out[f]);
+                        } else {  // another block's tet
+                            const gptr<int32_t> next = global(sm.buf[(period + 1) & 1]) + base;
+                            __hip_atomic_fetch_add(next + (uint32_t)(s * (int32_t)Tp + nb[f]), out[f],
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if (!direct) {
+                                const gptr<uint8_t> marks = global(sm.mask[(period + 1) & 1]) + mbase;
+                                __hip_atomic_store(marks + (uint32_t)(s * sm.mstride + (nb[f] >> 2)),
+                                                   occupancy_tag(period + 1), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                            }
+                        }
+                    }
+                }
+            }
+            if (stay > 0) atomicAdd(&nxt[e], stay);
+        }
+        // additions for other blocks' tets reach memory before this block
+        // publishes the period
+        if (!alone) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) head.n_pairs = 0;
+        if (!alone) {
+            const unsigned long long target = epoch + (unsigned long long)k + 1ull;
+            if (tid < 64) {
+                if (tid == 0)
+                    __hip_atomic_store(&done[(int64_t)pt.part * kResidentFlagStride], target, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                if (!wait_neighbours(done, nlist, pt.neighbours, my_neighbour, target, fail) && tid == 0)
+                    head.stop = 1;
+            }
+            __syncthreads();
+            // what other blocks added to this block's tets
+            const gptr<int32_t> next = global(sm.buf[(period + 1) & 1]) + base + t0;
+            if (direct) {
+                for (int32_t v = tid; v < P / 4; v += nt) {
+                    const int32_t s = (int32_t)__umulhi(4u * (uint32_t)v, per_species);
+                    take_arrivals((gptr<unsigned long long>)(next + s * Tp + (4 * v - s * ls)), nxt + 4 * v);
+                }
+            } else {
+                const gptr<uint8_t> marks = global(sm.mask[(period + 1) & 1]) + mbase + (t0 >> 2);
+                const uint32_t mark = occupancy_tag(period + 1);
+                const int32_t words = (len + 15) >> 4;
+                for (int32_t v = tid; v < S * words; v += nt) {
+                    const int32_t s = v / words, wd = v - s * words;
+                    const uint32_t m =
+                        __hip_atomic_load((gptr<uint32_t>)(marks + (int64_t)s * sm.mstride + 4 * wd),
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        if (((m >> (8 * b)) & 0xffu) != mark) continue;
+                        const int32_t i = 16 * wd + 4 * b;
+                        take_arrivals((gptr<unsigned long long>)(next + s * Tp + i), nxt + s * ls + i);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (head.stop) break;  // uniform over the block
+    }
+
+    // the state of the next period, its occupancy bytes, and an empty other buffer
+    const int64_t end = first + n_periods;
+    const int32_t *fin = counts + (n_periods & 1) * P;
+    const gptr<int32_t> dst = global(sm.buf[end & 1]) + base + t0;
+    const gptr<int32_t> other = global(sm.buf[(end & 1) ^ 1]) + base + t0;
+    const gptr<uint8_t> mdst = global(sm.mask[end & 1]) + mbase + (t0 >> 2);
+    const uint8_t mark = occupancy_tag(end);
+    for (int32_t v = tid; v < P / 4; v += nt) {
+        const int32_t s = (int32_t)__umulhi(4u * (uint32_t)v, per_species);
+        const int32_t i = 4 * v - s * ls;
+        const v4i c = *reinterpret_cast<const v4i *>(fin + 4 * v);
+        *(gptr<v4i>)(dst + s * Tp + i) = c;
+        mdst[(int64_t)s * sm.mstride + (i >> 2)] = (c.x | c.y | c.z | c.w) != 0 ? mark : (uint8_t)0;
+        if (alone && (n_periods & 1)) *(gptr<v4i>)(other + s * Tp + i) = v4i{0, 0, 0, 0};
+    }
+    if (head.stop && tid == 0) atomicOr(sm.flags, 8);
+}
+
+hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t iter0, int32_t n_periods,
+                           int64_t partial, double tau_last, unsigned long long epoch, hipStream_t st)
+{
+    if (n_periods <= 0) return hipSuccess;
+    if (plan.blocks < 1 || plan.threads < 64 || plan.threads > kResidentMaxThreads ||
+        plan.lds_bytes > kResidentLdsMax)
+        return hipErrorInvalidValue;
+    const void *fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true>)
+                                 : reinterpret_cast<const void *>(&resident_kernel<false>);
+    uint32_t *fail = reinterpret_cast<uint32_t *>(plan.done + (int64_t)plan.blocks * kResidentFlagStride);
+    const uint16_t *neighbours = plan.neighbours;
+    int32_t max_parts = plan.max_parts;
+    unsigned long long *done = plan.done;
+    const ResidentPart *parts = plan.parts;
+    int32_t lds = plan.lds_bytes;
+    void *args[] = {(void *)&sims,      (void *)&parts,   (void *)&neighbours, (void *)&max_parts,
+                    (void *)&iter0,     (void *)&n_periods, (void *)&partial,  (void *)&tau_last,
+                    (void *)&done,      (void *)&epoch,   (void *)&fail,       (void *)&lds};
+    if (plan.max_parts > 1)
+        return hipLaunchCooperativeKernel(fn, dim3(plan.blocks), dim3(plan.threads), args, (unsigned)lds, st);
+    return hipLaunchKernel(fn, dim3(plan.blocks), dim3(plan.threads), args, (size_t)lds, st);
+}
+
+}  // namespace rdos

@@ -69,8 +69,12 @@ struct rdos_sim {
     rdos::QueueView queue{};      // occupied tets of one period (tet ids + counts + segment lengths)
     int64_t launches = 0;         // periods launched on this handle (selects the queue length half)
     int32_t update_bps = 1;       // update blocks per queue segment
-    int32_t launch_mode = 0;      // 0: one launch for small work lists, two per period otherwise; 1: always two
+    int32_t launch_mode = 0;      // as rdos_set_launch_mode takes it
     int32_t persist_limit = -1;   // blocks a cooperative launch of the one-launch kernel may have (-1: not asked)
+    rdos::ResidentPlan resident_one{};   // state-in-LDS launches with one block per realization, and with
+    rdos::ResidentPlan resident_many{};  // as many as the device holds (blocks 0: does not apply)
+    uint64_t resident_epoch = 0;         // periods launched with several blocks (their counters' value)
+    std::vector<int64_t> totals;         // molecules last set, per realization and species
     rdos::DevSim desc{};
 };
 
@@ -86,6 +90,14 @@ void free_queue(rdos::QueueView *q, hipStream_t st);
 // Device memory from the per-device stream-ordered pool (ordered on st).
 hipError_t dev_alloc(void **p, size_t bytes, hipStream_t st);
 void dev_free(void *p, hipStream_t st);
+// How one realization is cut for the resident kernel (blocks 0: it does not
+// fit): at most max_blocks blocks of `len` tets (the last may hold fewer).
+struct ResidentCut {
+    int32_t blocks = 0, len = 0, threads = 0, lds_bytes = 0;
+};
+ResidentCut resident_cut(int32_t T, int32_t S, int32_t R, int32_t max_blocks);
+// Compute units of a device (0 when it cannot be asked).
+int32_t compute_units(int device);
 rdos_status match_parity(rdos_sim *s);
 rdos_status ensure_mask(rdos_sim *s);
 rdos_status check_flags(rdos_sim *s);

@@ -1,0 +1,146 @@
+"""Periods with the state held in LDS (one block per realization, or several
+that exchange molecules) against the oracle, every count: sizes at the edges
+of the cut (16 tets per block, a last block of a few tets, one block, more
+realizations than blocks fit), every species and reaction bound of the lane
+state, odd and even runs, and runs that alternate with the other launch
+paths, which must find the counts, the empty buffer and the occupancy bytes
+as they leave them."""
+import sys
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def note(msg):
+    print(f"[gpu-case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_1512_03126_amd as mod
+
+    mod.lib()
+    return mod
+
+
+def chemistry(S, R):
+    """S species, R reactions of every order: bindings, decays, pair
+    annihilations and (from four reactions on) a production."""
+    D = [1e-12 * (0.3 + 0.2 * s) for s in range(S)]
+    D[S // 2] = 0.0 if S > 2 else D[S // 2]
+    rx = []
+    for q in range(R):
+        a, b, c = q % S, (q + 1) % S, (q + 2) % S
+        kind = q % 4
+        if kind == 0 and S > 1:
+            rx.append(([a, b], [c], 2e8))
+        elif kind == 1:
+            rx.append(([a], [b, c], 60.0))
+        elif kind == 2:
+            rx.append(([a, a], [b], 1e8))
+        else:
+            rx.append(([], [a], 2e-4))
+    return D, rx
+
+
+def both(P, orc, shape, S, R, Rz, mean, seed=5, **method):
+    xyz, tets = W.kuhn_box(*shape, 0.2e-6)
+    T = tets.shape[0]
+    D, rx = chemistry(S, R)
+    rng = np.random.default_rng(seed)
+    init = rng.poisson(mean, (Rz, S, T)).astype(np.int32)
+    init[:, 0, ::11] += 12
+    g = P.Simulation(xyz, tets, D, rx, seed=seed, n_realizations=Rz, **method)
+    refs = {}
+    for r in range(Rz):
+        for s in range(S):
+            g.set_counts(s, init[r, s], realization=r)
+    for r in sorted({0, Rz // 2, Rz - 1}):
+        o = orc.OracleSim(xyz, tets, D, rx, seed=seed, realization=r)
+        for s in range(S):
+            o.set_counts(s, init[r, s])
+        refs[r] = o
+    return g, refs
+
+
+def check(g, refs, what):
+    for r, o in refs.items():
+        got, want = g.get_counts(None, realization=r), o.get_counts()
+        assert np.array_equal(got, want), (what, r, int((got != want).sum()))
+
+
+@pytest.mark.parametrize("shape,S,R,Rz,mean", [
+    ((1, 1, 1), 1, 0, 1, 3.0),      # 6 tets: one block of less than a wavefront
+    ((1, 1, 3), 2, 2, 1, 3.0),      # 18 tets: a second block of 2 tets
+    ((2, 2, 2), 3, 3, 1, 2.0),      # 48 tets: three full blocks
+    ((5, 5, 5), 1, 0, 1, 0.5),      # 750 tets, light: one block
+    ((5, 5, 5), 1, 2, 1, 60.0),     # the same, crowded: 47 blocks, rejection sampler
+    ((5, 5, 5), 2, 4, 100, 0.2),    # two blocks per realization
+    ((3, 3, 3), 2, 4, 300, 0.5),    # more realizations than compute units
+    ((7, 5, 4), 10, 8, 1, 1.5),     # ten species
+    ((4, 4, 3), 16, 32, 1, 0.7),    # the most species and reactions: 64 lanes in the SSA at a time
+    ((17, 16, 15), 4, 5, 1, 0.05),  # 24,480 tets, sparse: arrivals found by the occupancy bytes or directly
+])
+def test_resident_runs_match_the_oracle(P, orc, shape, S, R, Rz, mean):
+    note(f"resident: {shape} cells, {S} species, {R} reactions, {Rz} realizations, mean {mean}")
+    g, refs = both(P, orc, shape, S, R, Rz, mean)
+    for n in (1, 2, 3, 6):
+        g.step(n)
+        for o in refs.values():
+            o.run_steps(n)
+        check(g, refs, n)
+    t = g.time()[0] + 2.4 * g.tau  # a shortened last period
+    g.run_until(t)
+    for o in refs.values():
+        o.run_until(t)
+    check(g, refs, "run_until")
+    g.close()
+
+
+@pytest.mark.parametrize("method", [{"transfer_form": 1}, {"occupancy_correction": False, "split_threshold": 3}])
+def test_resident_method_options(P, orc, method):
+    note(f"resident: method options {method}")
+    xyz, tets = W.kuhn_box(6, 5, 5, 0.2e-6)
+    D, rx = chemistry(3, 4)
+    rng = np.random.default_rng(9)
+    init = rng.poisson(8.0, (3, tets.shape[0])).astype(np.int32)
+    g = P.Simulation(xyz, tets, D, rx, seed=9, **method)
+    o = orc.OracleSim(xyz, tets, D, rx, seed=9)
+    if method.get("transfer_form"):
+        o.set_transfer_form(1)
+    else:
+        o.set_first_order(True)
+        o.set_split_threshold(3)
+    for s in range(3):
+        g.set_counts(s, init[s])
+        o.set_counts(s, init[s])
+    for n in (2, 5):
+        g.step(n)
+        o.run_steps(n)
+        check(g, {0: o}, (method, n))
+    g.close()
+
+
+def test_resident_runs_alternate_with_the_other_paths(P, orc):
+    note("resident: alternating with two launches, the fused launch and the queue-based one-launch path")
+    g, refs = both(P, orc, (9, 9, 9), 3, 4, 2, 0.3)
+    for mode, n in ((0, 3), (1, 2), (0, 2), (3, 3), (0, 1), (2, 2), (0, 5), (1, 1), (0, 4)):
+        P.rdos_set_launch_mode(g.h, mode)
+        g.step(n)
+        for o in refs.values():
+            o.run_steps(n)
+        check(g, refs, (mode, n))
+    g.set_state(1001, 0.5)  # another parity
+    for o in refs.values():
+        o.set_state(1001, 0.5)
+    P.rdos_set_launch_mode(g.h, 0)
+    g.step(3)
+    for o in refs.values():
+        o.run_steps(3)
+    check(g, refs, "set_state")
+    g.close()
