@@ -12,12 +12,12 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librdos.so")
-SOURCES = ["rdos_kernels.hip", "rdos_resident.hip", "rdos_api.cpp", "rdos_engine.cpp", "rdos_static.hip", "rdos_probes.hip"]
+SOURCES = ["rdos_kernels.hip", "rdos_resident.hip", "rdos_sparse.hip", "rdos_api.cpp", "rdos_engine.cpp", "rdos_static.hip", "rdos_probes.hip"]
 # Flags of single sources.  The step kernels' many 64-bit constants, hoisted
 # out of the period loop, overflow the scalar registers into vector lanes: on
 # the resident kernel 345 lane reads against 195 (abc, 384,000 tets: 10.05
 # against 9.65 us per period).
-SOURCE_FLAGS = {"rdos_resident.hip": ["-mllvm", "-disable-machine-licm"]}
+SOURCE_FLAGS = {f: ["-mllvm", "-disable-machine-licm"] for f in ("rdos_resident.hip", "rdos_sparse.hip")}
 ARCH = os.environ.get("RDOS_OFFLOAD_ARCH", "gfx950")
 
 

@@ -1239,7 +1239,7 @@ rdos_status rdos_get_geometry(rdos_sim *s, int32_t *nbr, double *w, double *g, d
     for (int32_t t = 0; t < s->T; ++t) {
         for (int f = 0; f < 4; ++f) {
             if (nbr) nbr[4 * (size_t)t + f] = m[t].nbr[f];
-            if (w) w[4 * (size_t)t + f] = m[t].w[f];
+            if (w) w[4 * (size_t)t + f] = f < 3 ? m[t].w[f] : m[t].w3;
         }
         if (g) g[t] = m[t].g;
         if (nav) nav[t] = m[t].nav;

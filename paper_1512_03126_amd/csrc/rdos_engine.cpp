@@ -67,6 +67,9 @@ struct Shape {
 constexpr int32_t kSmallWorkTiles = 1024;
 constexpr Shape kSmallWorkShape{32, 2048, 1, 1};
 
+// How the current work list may run with its state in LDS.
+enum class LdsPath { None, Resident, Sparse };
+
 // Tuning results shared by every engine of the process, by work-list size
 // bucket: an engine that meets a bucket another engine has tuned starts
 // with its shape instead of tuning again.
@@ -134,9 +137,22 @@ struct rdos_engine {
     std::map<std::array<int32_t, 5>, hipGraphExec_t> graphs;
     int32_t grid_tiles = 1;        // launch grids serve work lists of up to this many tiles (size bucket)
     double last_chunk_ms = 0.0;    // device time of the last full chunk
-    double last_period_ms = 0.0;   // device time per period of the last one-launch run
-    int32_t persist_limit = -1;    // blocks of a cooperative one-launch kernel (-1: not asked)
-    int32_t persist_key = -1;      // queue species bound and transfer form it was asked for
+    // The state-in-LDS paths of the current work list (build_work): used once
+    // the list's size bucket has its launch shape, unless the shape was fixed.
+    LdsPath lds_path = LdsPath::None;
+    ResidentPlan resident{};
+    SparsePlan sparse{};
+    char *d_resident = nullptr;    // the resident plan's arrays
+    int64_t cap_resident = 0;
+    ResidentUnit *d_runits = nullptr;
+    int64_t cap_runits = 0;
+    WorkUnit *d_sunits = nullptr;  // the sparse kernel's units, largest first
+    int64_t cap_sunits = 0;
+    char *d_sparse = nullptr;      // its scratch, counts and failure word
+    int64_t cap_sparse = 0;
+    uint32_t *h_fail = nullptr;    // pinned copy of the failure word
+    uint64_t resident_epoch = 0;
+    double lds_period_ms = 0.0;    // device time per period of the last run on such a path
     int32_t qphase = 0;            // queue half (qsel) of the next period; graphs start at 0
     bool graph_stale = true;  // a buffer the graphs name was reallocated
     bool rebuild = true;      // the slot set changed
@@ -222,6 +238,117 @@ size_t tune_candidate(const rdos_engine *e)
     return e->trial < 2 * m ? e->trial / 2 : e->trial - 2 * m;
 }
 
+// Cuts every realization of the slots for the resident kernel, or returns
+// false where their counts do not fit the device's LDS.  Each gets the blocks
+// it needs, the rest of the compute units are shared out by tet-species.
+bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, ResidentPlan &plan)
+{
+    const int32_t cus = compute_units(e->device);
+    struct Sim {
+        const rdos_sim *s;
+        int32_t least, blocks;
+        double pairs;
+    };
+    std::vector<Sim> sims;
+    int64_t need = 0, n_units = 0;
+    double all = 0.0;
+    for (uint64_t id : e->slots) {
+        const rdos_sim *s = e->tickets.at(id).sim;
+        const int32_t S = (int32_t)s->D.size(), R = (int32_t)s->rx.size();
+        int32_t lo = 1;
+        while (lo <= cus && resident_cut(s->T, S, R, lo).blocks == 0) lo += lo < 16 ? 1 : 4;
+        if (lo > cus) return false;
+        sims.push_back({s, lo, lo, (double)s->T * S});
+        need += (int64_t)lo * s->Rz;
+        n_units += s->Rz;
+        all += (double)s->T * S * s->Rz;
+    }
+    const bool alone = need > cus;  // one block each, in turn
+    if (alone && (need > n_units || n_units > kResidentMaxUnits)) return false;
+    const int64_t spare = cus - need;
+    units.clear();
+    plan = ResidentPlan{};
+    for (size_t i = 0; i < sims.size(); ++i) {
+        Sim &m = sims[i];
+        const int32_t S = (int32_t)m.s->D.size(), R = (int32_t)m.s->rx.size();
+        if (!alone) m.blocks += (int32_t)((double)spare * m.pairs / all);
+        const ResidentCut c = resident_cut(m.s->T, S, R, m.blocks);
+        if (c.blocks == 0) return false;
+        plan.threads = std::max(plan.threads, alone ? std::min(c.threads, 512) : c.threads);
+        plan.max_parts = std::max(plan.max_parts, c.blocks);
+        if (m.s->desc.transfer_form == 1) plan.scaled = 1;
+        for (int32_t r = 0; r < m.s->Rz; ++r) {
+            units.push_back(ResidentUnit{(int32_t)i, r, m.s->T, plan.blocks, c.blocks, c.len});
+            plan.blocks += c.blocks;
+        }
+    }
+    for (const ResidentUnit &u : units) {
+        const rdos_sim *s = sims[u.sim].s;
+        plan.lds_bytes = std::max(plan.lds_bytes, resident_lds_bytes((int32_t)s->D.size(), (int32_t)s->rx.size(),
+                                                                     (u.len + 3) & ~3, plan.threads));
+    }
+    plan.lds_bytes = std::min(plan.lds_bytes, kResidentLdsMax);
+    return true;
+}
+
+// The sparse kernel for the slots: every realization's occupied pairs, as
+// expected from the molecules last set, must fit its table with room, and the
+// batch must be expected to run faster than over the queue.  Per period, by
+// the kernel's own measurements: about 7 us and 5.5 ns per pair of the
+// fullest compute unit, and 8 ns more per pair of a species with a
+// first-order reaction, whose tets all draw the time of their first event;
+// over the queue 12 us, 0.33 ps per tet-species (the scan) and 76 ps per pair
+// (the update).  A+B<->C at 2% occupancy, sparse and queue: 24 realizations
+// of 162,000 tets 22 and 20 us, 64 of them 22 and 31, 128 of 384,000 tets 46
+// and 109, the batch of 256 + 64 realizations 63 and 228; 64 realizations of
+// 162,000 tets with a decaying fourth species 64 and 49.
+bool plan_sparse(const rdos_engine *e, std::vector<WorkUnit> &units, SparsePlan &plan)
+{
+    const int32_t cus = std::max(compute_units(e->device), 1);
+    plan = SparsePlan{};
+    int32_t S = 1, R = 0;
+    for (uint64_t id : e->slots) {
+        const rdos_sim *s = e->tickets.at(id).sim;
+        if (s->desc.zeroth) return false;
+        S = std::max(S, (int32_t)s->D.size());
+        R = std::max(R, (int32_t)s->rx.size());
+        if (s->desc.transfer_form == 1) plan.scaled = 1;
+    }
+    units.clear();
+    double all = 0.0, most = 0.0, all_load = 0.0, most_load = 0.0, cells = 0.0;
+    for (size_t i = 0; i < e->slots.size(); ++i) {
+        const rdos_sim *s = e->tickets.at(e->slots[i]).sim;
+        const size_t n = s->D.size();
+        uint32_t alone = 0;  // species with a first-order reaction
+        for (const Reaction &r : s->rx)
+            if (r.rn == 1) alone |= 1u << r.r[0];
+        if (s->totals.size() != n * s->Rz || s->T >= (1 << kSparseTetBits) - 1) return false;
+        for (int32_t r = 0; r < s->Rz; ++r) {
+            double pairs = 0.0, load = 0.0;
+            for (size_t m = 0; m < n; ++m) {
+                const double p = s->T * -std::expm1(-(double)s->totals[(size_t)r * n + m] / s->T);
+                pairs += p;
+                load += p * ((alone >> m) & 1u ? 13.5e-3 : 5.5e-3);
+            }
+            all += pairs;
+            most = std::max(most, pairs);
+            all_load += load;
+            most_load = std::max(most_load, load);
+            units.push_back({(int32_t)i, r, s->T, 0});
+        }
+        cells += (double)s->T * n * s->Rz;
+    }
+    if (units.size() > kSparseMaxUnits ||
+        !sparse_shape(S, R, (int64_t)most + 1, (int64_t)units.size() > 2 * cus, &plan) || most > 0.6 * plan.slots)
+        return false;
+    plan.units = (int32_t)units.size();
+    const double sparse_us = 7.0 + std::max(most_load, all_load / cus);
+    const double queue_us = 12.0 + 0.33e-6 * cells + 76e-6 * all;
+    if (sparse_us > queue_us) return false;
+    std::stable_sort(units.begin(), units.end(), [](const WorkUnit &a, const WorkUnit &b) { return a.T > b.T; });
+    return true;
+}
+
 // Rewrites the device work list for the current slots (lock held).
 rdos_status build_work(rdos_engine *e)
 {
@@ -293,6 +420,40 @@ rdos_status build_work(rdos_engine *e)
                    "upload work units");
         ENGINE_HIP(e, launch_expand_tiles(e->d_units, (int32_t)units.size(), (int32_t)n_tiles, e->d_tiles, e->stream),
                    "expand tiles");
+    }
+    e->lds_path = LdsPath::None;
+    e->lds_period_ms = 0.0;
+    std::vector<ResidentUnit> runits;
+    std::vector<WorkUnit> sunits;
+    if (!sims.empty() && cut_resident(e, runits, e->resident)) {
+        st = ensure(e, &e->d_runits, &e->cap_runits, (int64_t)runits.size(), "engine block units");
+        if (st != RDOS_OK) return st;
+        st = ensure(e, &e->d_resident, &e->cap_resident,
+                    (int64_t)resident_plan_bytes(e->resident.blocks, e->resident.max_parts), "engine blocks");
+        if (st != RDOS_OK) return st;
+        resident_place(&e->resident, e->d_resident);
+        ENGINE_HIP(e, hipMemcpyAsync(e->d_runits, runits.data(), runits.size() * sizeof(ResidentUnit),
+                                     hipMemcpyHostToDevice, e->stream),
+                   "upload block units");
+        ENGINE_HIP(e, launch_resident_layout(e->d_sims, e->resident, e->d_runits, (int32_t)runits.size(),
+                                             ResidentUnit{}, e->stream),
+                   "engine blocks");
+        e->lds_path = LdsPath::Resident;
+    } else if (!sims.empty() && plan_sparse(e, sunits, e->sparse)) {
+        SparsePlan &p = e->sparse;
+        st = ensure(e, &e->d_sunits, &e->cap_sunits, (int64_t)sunits.size(), "engine sparse units");
+        if (st != RDOS_OK) return st;
+        const int64_t scratch = (int64_t)p.units * p.unit_bytes, counts = ((int64_t)p.units * 8 + 255) & ~(int64_t)255;
+        st = ensure(e, &e->d_sparse, &e->cap_sparse, scratch + counts + 256, "engine sparse scratch");
+        if (st != RDOS_OK) return st;
+        p.scratch = e->d_sparse;
+        p.counts = reinterpret_cast<int32_t *>(e->d_sparse + scratch);
+        p.fail = reinterpret_cast<uint32_t *>(e->d_sparse + scratch + counts);
+        ENGINE_HIP(e, hipMemsetAsync(p.fail, 0, sizeof(uint32_t), e->stream), "clear failure word");
+        ENGINE_HIP(e, hipMemcpyAsync(e->d_sunits, sunits.data(), sunits.size() * sizeof(WorkUnit),
+                                     hipMemcpyHostToDevice, e->stream),
+                   "upload sparse units");
+        e->lds_path = LdsPath::Sparse;
     }
     e->n_tiles = (int32_t)n_tiles;
     e->n_sims = (int32_t)sims.size();
@@ -605,20 +766,13 @@ void worker_main(rdos_engine *e)
         bool replay = !timed && (fused || e->qphase == 0) && left_max >= sh.chunk;
         int32_t len = replay ? sh.chunk : (int32_t)std::min<int64_t>(left_max, sh.chunk);
         if (!replay && !timed && !fused && e->qphase == 1 && left_max >= sh.chunk) len = 1;
-        // Small work lists run their periods in one cooperative launch: as
-        // many as the slot nearest its end has left, or (when requests wait
-        // to join) at most a chunk, or about 2 ms of device time.
-        int32_t persist = 0;
-        if (!timed && e->shape_source == RDOS_SHAPE_SMALL_WORK && sh.chains == 1 && e->n_tiles <= kPersistTiles) {
-            const int32_t key = e->queue.species * 2 + e->queue.scaled;
-            if (key != e->persist_key) {
-                e->persist_limit = persist_grid_limit(e->queue);
-                e->persist_key = key;
-            }
-            if (e->persist_limit > 0)
-                persist = std::min(e->persist_limit, std::max(4 * e->queue.nseg, scan_blocks_for(e->n_tiles)));
-        }
-        if (persist > 0) {
+        // With the state in LDS one launch runs as many periods as the slot
+        // nearest its end has left, or (when requests wait to join) at most a
+        // chunk, or some milliseconds of device time: the sparse kernel's
+        // runs are the longer ones, since each reads the state from memory and
+        // writes it back.
+        const LdsPath lds = !timed && !tuning && !e->fixed_shape ? e->lds_path : LdsPath::None;
+        if (lds != LdsPath::None) {
             replay = false;
             const bool pending = !e->ready.empty() || !e->waiting.empty() || e->admitting > 0;
             int64_t left_min = left_max;
@@ -627,8 +781,8 @@ void worker_main(rdos_engine *e)
                 left_min = std::min<int64_t>(left_min, tk.end_step - tk.sim->step);
             }
             int64_t cap = sh.chunk;
-            if (!pending && e->last_period_ms > 0.0)
-                cap = std::max<int64_t>(cap, (int64_t)(2.0 / e->last_period_ms));
+            if (!pending && e->lds_period_ms > 0.0)
+                cap = std::max<int64_t>(cap, (int64_t)((lds == LdsPath::Sparse ? 6.0 : 2.0) / e->lds_period_ms));
             len = (int32_t)std::max<int64_t>(1, std::min<int64_t>({left_min, cap, kPersistPeriods}));
         }
         // the timing pass launches directly and tallies its work; captured graphs never do
@@ -681,10 +835,15 @@ void worker_main(rdos_engine *e)
         lk.unlock();
         hipError_t err = hipEventRecord(e->ev0, e->stream);
         if (err == hipSuccess) {
-            if (persist > 0) {
-                err = launch_persist(e->d_sims, e->d_tiles, 0, len, phase, -1, 0.0, e->queue, persist, e->queue.sync,
-                                     e->stream);
+            if (lds == LdsPath::Resident) {
+                err = launch_resident(e->d_sims, e->resident, 0, len, -1, 0.0, e->resident_epoch, e->stream);
+                e->resident_epoch += len;
                 if (err == hipSuccess) err = launch_advance(e->d_sims, e->queue.hdr, len, e->stream);
+            } else if (lds == LdsPath::Sparse) {
+                err = launch_sparse(e->d_sims, e->d_sunits, 0, len, e->sparse, e->stream);
+                if (err == hipSuccess)
+                    err = hipMemcpyAsync(e->h_fail, e->sparse.fail, sizeof(uint32_t), hipMemcpyDeviceToHost,
+                                         e->stream);
             } else if (replay) {
                 for (int32_t k = 0; k < reps && err == hipSuccess; ++k) err = hipGraphLaunch(gx, e->stream);
                 if (err == hipSuccess && tail > 0)
@@ -697,13 +856,25 @@ void worker_main(rdos_engine *e)
         if (err == hipSuccess) err = hipEventSynchronize(e->ev1);
         float ms = 0.f;
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, e->ev0, e->ev1);
+        bool moved = true;
+        if (err == hipSuccess && lds == LdsPath::Sparse) {
+            // a table was full: no state moved on, and this work list stays with the queue
+            moved = *e->h_fail == 0u;
+            err = moved ? launch_advance(e->d_sims, e->queue.hdr, len, e->stream)
+                        : hipMemsetAsync(e->sparse.fail, 0, sizeof(uint32_t), e->stream);
+        }
         lk.lock();
         if (err != hipSuccess) {
             e->error = std::string("chunk: ") + hipGetErrorString(err);
             fail_slots(e);
             break;
         }
-        if (!fused || persist > 0) e->qphase = (phase + len) & 1;
+        if (!moved) {
+            e->lds_path = LdsPath::None;
+            e->busy_s += ms * 1e-3;
+            continue;
+        }
+        if (!fused && lds == LdsPath::None) e->qphase = (phase + len) & 1;
         if (timed) {
             for (int32_t i = 0; i < len; ++i) {
                 float a = 0.f, b = 0.f;
@@ -717,7 +888,7 @@ void worker_main(rdos_engine *e)
             }
         }
         if (replay && tail == 0) e->last_chunk_ms = (double)ms / reps;
-        if (persist > 0) e->last_period_ms = (double)ms / len;
+        if (lds != LdsPath::None) e->lds_period_ms = (double)ms / len;
         if (tuning && replay) {  // only full graph-replayed chunks are scored
             const size_t m = e->candidates.size();
             if (e->trial >= 2 * m || (e->trial & 1)) e->trial_ms[e->trial >= 2 * m][tune_candidate(e)] = ms / len;
@@ -791,6 +962,7 @@ rdos_status rdos_engine_create(rdos_engine **out, int device, size_t hbm_budget_
         hipEventCreateWithFlags(&e->fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&e->join, hipEventDisableTiming) != hipSuccess ||
         hipEventCreate(&e->ev0) != hipSuccess || hipEventCreate(&e->ev1) != hipSuccess ||
+        hipHostMalloc((void **)&e->h_fail, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess ||
         hipStreamSynchronize(e->stream) != hipSuccess) {
         delete e;
         return RDOS_EDEVICE;
@@ -1145,9 +1317,10 @@ void rdos_engine_destroy(rdos_engine *e)
         rdos_destroy(kv.second.sim);
     }
     drop_graphs(e);
-    void *p[] = {e->d_sims, e->d_tiles, e->d_units, e->d_work};
+    void *p[] = {e->d_sims, e->d_tiles, e->d_units, e->d_work, e->d_resident, e->d_runits, e->d_sunits, e->d_sparse};
     for (void *q : p)
         if (q) (void)hipFree(q);
+    if (e->h_fail) (void)hipHostFree(e->h_fail);
     free_queue(&e->queue, e->stream);
     free_queue(&e->queue2, e->stream);
     (void)hipStreamSynchronize(e->stream);

@@ -21,8 +21,9 @@ constexpr uint32_t kMaxEventsPerPeriod = 1u << 24;  // SSA events of one tet in 
 // molecules (or has a 0th-order reaction).
 struct alignas(64) MeshRec {
     int32_t nbr[4];   // neighbour across face f (opposite local vertex f), -1 = boundary
-    double w[4];      // direction weights, sum 1 over interior faces
+    double w[3];      // direction weights of faces 0..2; with w3 they sum to 1 over the interior faces
     double g;         // sum_f A_f / (V delta_f), 1/m^2; local rate d = D g
+    double w3;        // face 3, which closes the split when it is interior: only transfer form 1 reads it
     double nav;       // N_A * volume in litres
 };
 static_assert(sizeof(MeshRec) == 64, "MeshRec must be one cache line");
@@ -242,6 +243,7 @@ struct ResidentPlan {
 };
 constexpr int kResidentMaxThreads = 1024;
 constexpr int kResidentMaxParts = 1024;
+constexpr int64_t kResidentMaxUnits = 1 << 16;  // of an engine's work list
 constexpr int32_t kResidentLdsMax = 160 * 1024;
 constexpr int kResidentFlagStride = 16;  // 128 bytes between blocks' period counters
 constexpr int32_t kResidentHeadBytes = kMaxSpecies * 8 + kMaxReactions * 16 + 16;
@@ -274,6 +276,34 @@ hipError_t launch_resident_layout(const DevSim *sims, const ResidentPlan &plan, 
 // value in plan.done; the launch raises them to at most epoch + n_periods.
 hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t iter0, int32_t n_periods,
                            int64_t partial, double tau_last, unsigned long long epoch, hipStream_t st);
+// Batches of sparse realizations (rdos_sparse.hip): one block per unit of the
+// work list keeps its occupied (tet, species) pairs in a hash table in LDS.
+struct SparsePlan {
+    int32_t units;
+    int32_t threads;      // per block
+    int32_t slots;        // of the table: the most pairs a realization may hold (a multiple of 4 threads)
+    int32_t filter_words; // of each of the two filters over tets (a power of two)
+    int32_t lanes;        // in the SSA at a time (a multiple of 64; 0 without reactions)
+    int32_t lds_bytes;
+    int32_t scaled;       // some simulation uses transfer form 1
+    int64_t unit_bytes;   // of scratch per unit
+    char *scratch;        // [units][unit_bytes] (device)
+    int32_t *counts;      // [units][2] pairs before and after the run (device)
+    uint32_t *fail;       // raised when a table was full (device)
+};
+constexpr int kSparseMaxThreads = 1024;
+constexpr int kSparseTetBits = 27;        // tets below 2^27 - 1
+constexpr size_t kSparseMaxUnits = 2048;  // about a gigabyte of scratch
+constexpr int32_t kSparseHeadBytes = kMaxSpecies * 8 + kMaxReactions * 16 + 32;
+// The table and lane state for units of up to S species, R reactions and
+// about `pairs` occupied pairs, and for more or fewer units than the device
+// has compute units; false where they do not fit the LDS.
+bool sparse_shape(int32_t S, int32_t R, int64_t pairs, bool many_units, SparsePlan *plan);
+// n_periods periods of every unit; no simulation ends among them, and none
+// has a reaction without reactants.  All units' states move on, or, when
+// *plan.fail is set (it must be 0 before), none does.
+hipError_t launch_sparse(const DevSim *sims, const WorkUnit *units, int64_t iter0, int32_t n_periods,
+                         const SparsePlan &plan, hipStream_t st);
 // Rebuilds the occupancy bytes of buf[parity] from the counts of every
 // realization and species and clears those of the other buffer (after
 // counts were set from the host).

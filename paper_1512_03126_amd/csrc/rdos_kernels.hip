@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void geometry_pass2(const int32_t *__restrict_
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
         m.nbr[f] = nb[f];
-        m.w[f] = g > 0.0 ? r[f] / g : 0.0;
+        (f < 3 ? m.w[f] : m.w3) = g > 0.0 ? r[f] / g : 0.0;
     }
     m.g = g;
 }
@@ -447,7 +447,8 @@ __device__ __forceinline__ void update_tet(const DevSim &sm, int32_t t, int64_t 
                 nb[2] = n4.z;
                 nb[3] = n4.w;
 #pragma unroll
-                for (int f = 0; f < 4; ++f) w[f] = mr->w[f];
+                for (int f = 0; f < 3; ++f) w[f] = mr->w[f];
+                w[3] = ANY_SCALED ? mr->w3 : 0.0;
                 g = mr->g;
                 have_faces = true;
             }

@@ -35,7 +35,7 @@
 
 #include <cstdint>
 
-#include "rdos_cell.h"
+#include "rdos_block.h"
 #include "rdos_internal.h"
 
 #pragma clang fp contract(off)
@@ -44,166 +44,16 @@ namespace rdos {
 
 namespace {
 
-// A reaction as the SSA reads it: one 16-byte LDS load.
-struct alignas(16) ResidentReaction {
-    double k;
-    uint32_t shape;   // order, then five bits each: r0, r1, p0, p1, p2 (kNoSpecies: none)
-    uint32_t masks;   // low half: species involved; high half: species that must be present
-    static constexpr uint32_t kNoSpecies = 31;
-    __device__ __forceinline__ int order() const { return (int)(shape & 3u); }
-    __device__ __forceinline__ int species(int i) const { return (int)((shape >> (2 + 5 * i)) & 31u); }
-    __device__ __forceinline__ uint32_t involved() const { return masks & 0xffffu; }
-    __device__ __forceinline__ uint32_t needed() const { return masks >> 16; }
-};
-
 // Block-wide LDS words before the arrays (see resident_lds_bytes).
 struct ResidentHead {
     double D[kMaxSpecies];
-    ResidentReaction rx[kMaxReactions];
+    BlockReaction rx[kMaxReactions];
     int32_t n_ssa;    // tets listed for the SSA
     int32_t n_pairs;  // (tet, species) pairs listed for Step 3
     int32_t stop;     // a wait for other blocks failed
     int32_t pad;
 };
 static_assert(sizeof(ResidentHead) == kResidentHeadBytes, "LDS head");
-
-__device__ __forceinline__ uint32_t pack_species(int32_t n, int i, int32_t id)
-{
-    return (i < n ? (uint32_t)id : ResidentReaction::kNoSpecies);
-}
-
-__device__ __forceinline__ ResidentReaction pack_reaction(const DevSim &sm, int q)
-{
-    ResidentReaction r;
-    const int32_t rn = sm.rn[q], pn = sm.pn[q];
-    const uint32_t a = pack_species(rn, 0, sm.r0[q]), b = pack_species(rn, 1, sm.r1[q]);
-    r.k = sm.k[q];
-    r.shape = (uint32_t)rn | (a << 2) | (b << 7) | (pack_species(pn, 0, sm.p0[q]) << 12) |
-              (pack_species(pn, 1, sm.p1[q]) << 17) | (pack_species(pn, 2, sm.p2[q]) << 22);
-    r.masks = sm.involved[q] | ((rn > 0 ? 1u << a : 0u) | (rn > 1 ? 1u << b : 0u)) << 16;
-    return r;
-}
-
-// One lane's tet in the SSA: its counts are the block's own, the rest belongs
-// to the lane.
-struct ResidentCell {
-    int32_t *N;
-    double *lane;      // occ[S], last[S], c[R], a[R], `lanes` apart
-    int32_t stride;    // between species of N
-    int32_t lanes;
-    int32_t S, R;
-    __device__ __forceinline__ int32_t &n(int s) const { return N[s * stride]; }
-    __device__ __forceinline__ double &occ(int s) const { return lane[s * lanes]; }
-    __device__ __forceinline__ double &last(int s) const { return lane[(S + s) * lanes]; }
-    __device__ __forceinline__ double &c(int q) const { return lane[(2 * S + q) * lanes]; }
-    __device__ __forceinline__ double &a(int q) const { return lane[(2 * S + R + q) * lanes]; }
-};
-
-// Step 2 for one tet (as cell_ssa, the same operations in the same order):
-// the constants c_r are computed once for the tet, the propensities of an
-// event are kept for the choice of its reaction, and a reaction's fields come
-// from LDS in one load.  Returns the species some event touched.
-__device__ __forceinline__ uint32_t resident_ssa(const DevSim &sm, const ResidentHead &head, int32_t t,
-                                                 uint32_t period32, double tau_k, uint32_t key1,
-                                                 const ResidentCell &cell)
-{
-    const int R = cell.R;
-    const double nav = sm.mesh[t].nav;
-    const uint32_t allowed = sm.allowed ? sm.allowed[t] : 0xffffffffu;
-    for (int q = 0; q < R; ++q) {
-        const ResidentReaction x = head.rx[q];
-        const int order = x.order();
-        const double c = order == 1 ? x.k : (order == 0 ? x.k * nav : x.k / nav);
-        cell.c(q) = (allowed >> q) & 1u ? c : 0.0;
-    }
-    uint32_t touched = 0;
-    Stream ssa(sm.key0, key1, kSsaStream, (uint32_t)t, period32);
-    double now = 0.0;
-    for (uint32_t events = 0;; ++events) {
-        if (events >= kMaxEventsPerPeriod) {  // runaway rates: stop and report, never hang
-            atomicOr(sm.flags, 2);
-            break;
-        }
-        double a0 = 0.0;
-        for (int q0 = 0; q0 < R; q0 += 2) {  // two at a time, their loads in flight together
-            double a[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int q = min(q0 + j, R - 1);
-                const ResidentReaction x = head.rx[q];
-                const int order = x.order();
-                const int32_t na = cell.n(order > 0 ? x.species(0) : 0);
-                const int32_t nb = cell.n(order > 1 ? x.species(1) : 0);
-                double h = order > 0 ? (double)na : 1.0;
-                if (order == 2) h = h * (double)(x.species(0) == x.species(1) ? na - 1 : nb);
-                a[j] = h == 0.0 ? 0.0 : cell.c(q) * h;
-                cell.a(q) = a[j];
-            }
-            a0 = a0 + a[0];
-            if (q0 + 1 < R) a0 = a0 + a[1];
-        }
-        if (!(a0 > 0.0)) break;
-        const double dt = -log_basic(1.0 - ssa.uniform()) / a0;
-        if (now + dt >= tau_k) break;
-        now = now + dt;
-        const double x = ssa.uniform() * a0;
-        int chosen = -1;
-        double cum = 0.0;
-        for (int q = 0; q < R; ++q) {
-            cum = cum + cell.a(q);
-            if (x < cum) {
-                chosen = q;
-                break;
-            }
-        }
-        if (chosen < 0) {  // x rounded up to a0: the last reaction able to fire
-            for (int q = R - 1; q >= 0; --q)
-                if (cell.a(q) > 0.0) {
-                    chosen = q;
-                    break;
-                }
-        }
-        const ResidentReaction r = head.rx[chosen];
-        for (uint32_t inv = r.involved(); inv; inv &= inv - 1u) {
-            const int s = __builtin_ctz(inv);
-            const bool seen = (touched >> s) & 1u;
-            const double o = seen ? cell.occ(s) : 0.0;
-            const double l = seen ? cell.last(s) : 0.0;
-            int32_t ns = cell.n(s);
-            cell.occ(s) = o + (double)ns * (now - l);
-            cell.last(s) = now;
-            ns += (int)(s == r.species(2)) + (int)(s == r.species(3)) + (int)(s == r.species(4)) -
-                  (int)(s == r.species(0)) - (int)(s == r.species(1));
-            cell.n(s) = ns;
-            if (ns > 0x3fffffff) atomicOr(sm.flags, 1);
-        }
-        touched |= r.involved();
-    }
-    return touched;
-}
-
-// The lanes' exclusive prefix sum of v (v < 2^bits), and the total.
-__device__ __forceinline__ int32_t wave_prefix(uint32_t v, int bits, int32_t *total)
-{
-    int32_t before = 0, sum = 0;
-    for (int k = 0; k < bits; ++k) {
-        const uint64_t plane = __ballot((v >> k) & 1u);
-        before += (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(plane >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)plane, 0u))
-                  << k;
-        sum += __popcll(plane) << k;
-    }
-    *total = sum;
-    return before;
-}
-
-// Room for `total` entries of a block's list (one LDS atomic per wavefront).
-__device__ __forceinline__ int32_t reserve(int32_t *count, int32_t total)
-{
-    int32_t base = 0;
-    if (__lane_id() == 0) base = atomicAdd(count, total);
-    return __builtin_amdgcn_readfirstlane(base);
-}
 
 // Moves what other blocks added to four tets into the block's counts d.
 __device__ __forceinline__ void take_arrivals(gptr<unsigned long long> p, int32_t *d)
@@ -481,10 +331,10 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
             if (n_ssa > 0) {  // uniform over the block
                 for (int32_t j = tid; j < n_ssa && tid < lanes; j += lanes) {
                     const int32_t i = ssa_list[j], t = t0 + i;
-                    const ResidentCell cell{cur + i, lane_state + tid, ls, lanes, S, R};
+                    const BlockCell cell{cur + i, lane_state + tid, ls, lanes, S, R};
                     uint32_t held = 0;
                     for (int s = 0; s < S; ++s) held |= (uint32_t)(cell.n(s) != 0) << s;
-                    uint32_t touched = resident_ssa(sm, head, t, period32, tau_k, key1, cell);
+                    uint32_t touched = block_ssa(sm, head.rx, t, period32, tau_k, key1, cell);
                     // the touched species that still hold molecules: eq. 2
                     // and the stochastic rounding; bit 31 of the count tells
                     // Step 3 to take them from pop[]
@@ -526,7 +376,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
                 const MeshRec *mr = sm.mesh + t;
                 const int4 n4 = *reinterpret_cast<const int4 *>(mr->nbr);
                 const int32_t nb[4] = {n4.x, n4.y, n4.z, n4.w};
-                const double w[4] = {mr->w[0], mr->w[1], mr->w[2], mr->w[3]};
+                const double w[4] = {mr->w[0], mr->w[1], mr->w[2], ANY_SCALED ? mr->w3 : 0.0};
                 const double g = mr->g;
                 PrimedStream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
                 int32_t ni = Ns;

@@ -204,6 +204,26 @@ __device__ __forceinline__ int32_t binomial_inversion(int32_t n, double p, Rng &
     }
 }
 
+// Binomial(1, p) as binomial_inversion (after the reflection) draws it.  Its
+// walk ends at 0 for u <= q and at 1 for u - q <= q RN(p / q), which is p but
+// for rounding: only draws within a few ulp of 1 need the quotient, and start
+// again if they pass it.
+template <class Rng>
+__device__ __forceinline__ bool bernoulli_as_binomial(double p, Rng &rng)
+{
+    if (p <= 0.0) return false;
+    if (p >= 1.0) return true;
+    const bool reflect = p > 0.5;
+    const double pp = reflect ? 1.0 - p : p;
+    const double q = 1.0 - pp;
+    for (;;) {
+        const double u = rng.uniform();
+        if (!(u > q)) return reflect;
+        const double rest = u - q;
+        if (rest <= pp * (1.0 - 0x1p-50) || rest <= q * (pp / q)) return !reflect;
+    }
+}
+
 // Stirling-series remainder ln k! - ((k + 1/2) ln(k + 1) - (k + 1) + ln(2 pi)/2):
 // correctly rounded values for k <= 9, the series 1/12 - 1/360 + 1/1260 in
 // 1/(k+1) beyond.
@@ -301,7 +321,7 @@ __device__ __forceinline__ bool btrd_pass(int32_t n, double p, Rng &rng, int32_t
 // interval; otherwise
 // n_i = Binomial(n - sum_{j<i} n_j, w_i / (1 - sum_{j<i} w_j)) face by face,
 // the last interior face taking what is left (a single interior face takes
-// everything without a draw).
+// everything without a draw), so that weight 3 is read by the scaled form only.
 //
 // scaled (ANY_SCALED instances; the alternative at the end of Sec. II.B): the
 // whole population ni is split at once with weights zeta w_i, and a molecule
@@ -350,6 +370,13 @@ __device__ __forceinline__ int32_t leave_and_split(int32_t ni, int32_t Ns, doubl
         double p = zeta;
         bool draw = thin || (n >= threshold && n > 0 && interior > (all ? 1 : 0));
         bool face = !thin;  // the next thing to do is to pick a face
+        if (thin && __ballot(ni > 1) == 0) {
+            // no lane holds more than one molecule: a single Bernoulli draw
+            n = ni > 0 && Ns > 0 && bernoulli_as_binomial(zeta, rng) ? 1 : 0;
+            draw = n >= threshold && n > 0 && interior > 1;
+            left = n;
+            face = true;
+        }
         while (__ballot(draw) != 0) {
             if (!draw) continue;
             if (face) {
