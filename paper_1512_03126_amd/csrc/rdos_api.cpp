@@ -117,11 +117,10 @@ hipError_t alloc_queue(QueueView *q, int64_t capacity_tiles, int32_t n_species, 
 
 // Points the queue at a work list of n_tiles tiles (<= its capacity) and
 // n_sims descriptors; the kernels read these sizes from q->hdr.
-hipError_t set_queue_work(QueueView *q, int64_t n_tiles, int32_t n_sims, hipStream_t st, int32_t tile0)
+WorkHeader queue_header(QueueView *q, int64_t n_tiles, int32_t n_sims, int32_t tile0)
 {
     int32_t nseg, seg_cap;
     queue_shape(n_tiles, &nseg, &seg_cap);
-    if ((int64_t)nseg * seg_cap > q->qcap) return hipErrorInvalidValue;
     q->nseg = nseg;
     q->seg_cap = seg_cap;
     WorkHeader h{};
@@ -131,6 +130,14 @@ hipError_t set_queue_work(QueueView *q, int64_t n_tiles, int32_t n_sims, hipStre
     h.seg_cap = seg_cap;
     h.qcap = q->qcap;
     h.tile0 = tile0;
+    return h;
+}
+hipError_t set_queue_work(QueueView *q, int64_t n_tiles, int32_t n_sims, hipStream_t st, int32_t tile0)
+{
+    int32_t nseg, seg_cap;
+    queue_shape(n_tiles, &nseg, &seg_cap);
+    if ((int64_t)nseg * seg_cap > q->qcap) return hipErrorInvalidValue;
+    const WorkHeader h = queue_header(q, n_tiles, n_sims, tile0);
     hipError_t e = hipMemcpyAsync(q->hdr, &h, sizeof h, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);  // h lives on this stack frame
     return e;
@@ -144,6 +151,57 @@ void free_queue(QueueView *q, hipStream_t st)
     dev_free(q->hdr, st);
     dev_free(q->sync, st);
     *q = QueueView{};
+}
+
+// Validation scans.  They accumulate over blocks without leaving early, so
+// that they run at memory speed, and name the first offender only when there
+// is one (a million tets set up and read, with the tables taken apart on the
+// device: 32 ms before both, 16.5 after).
+constexpr int64_t kScanBlock = 4096;
+static int64_t first_not_finite(const double *v, int64_t n)
+{
+    for (int64_t b = 0; b < n; b += kScanBlock) {
+        const int64_t e = std::min(n, b + kScanBlock);
+        int bad = 0;
+        for (int64_t i = b; i < e; ++i) bad |= !(std::fabs(v[i]) <= std::numeric_limits<double>::max());
+        if (bad)
+            for (int64_t i = b; i < e; ++i)
+                if (!std::isfinite(v[i])) return i;
+    }
+    return -1;
+}
+static int64_t first_not_below(const int32_t *v, int64_t n, int32_t bound)
+{
+    for (int64_t b = 0; b < n; b += kScanBlock) {
+        const int64_t e = std::min(n, b + kScanBlock);
+        int bad = 0;
+        for (int64_t i = b; i < e; ++i) bad |= (uint32_t)v[i] >= (uint32_t)bound;
+        if (bad)
+            for (int64_t i = b; i < e; ++i)
+                if ((uint32_t)v[i] >= (uint32_t)bound) return i;
+    }
+    return -1;
+}
+// The sum of counts, or the first negative one in *bad.
+static int64_t sum_counts(const int32_t *v, int64_t n, int64_t *bad)
+{
+    int64_t total = 0;
+    *bad = -1;
+    for (int64_t b = 0; b < n; b += kScanBlock) {
+        const int64_t e = std::min(n, b + kScanBlock);
+        int32_t sign = 0;
+        for (int64_t i = b; i < e; ++i) {
+            sign |= v[i];
+            total += v[i];
+        }
+        if (sign < 0)
+            for (int64_t i = b; i < e; ++i)
+                if (v[i] < 0) {
+                    *bad = i;
+                    return total;
+                }
+    }
+    return total;
 }
 
 int32_t compute_units(int device)
@@ -507,19 +565,85 @@ rdos_status ensure_mask(rdos_sim *s)
     return RDOS_OK;
 }
 
+static rdos_status flags_status(rdos_sim *s, int32_t flags)
+{
+    if (flags & 1) return fail(s, RDOS_EOVERFLOW, "a molecule count overflowed int32");
+    if (flags & 4) return fail(s, RDOS_EDEVICE, "occupied-tet queue overflowed (internal error)");
+    if (flags & 8)
+        return fail(s, RDOS_EDEVICE, "a wait between blocks of the one-launch path timed out (internal error)");
+    if (flags & 2)
+        return fail(s, RDOS_EOVERFLOW, "a tet fired more than %u reactions in one period; shorten tau",
+                    kMaxEventsPerPeriod);
+    return RDOS_OK;
+}
+
 rdos_status check_flags(rdos_sim *s)
 {
     int32_t flags = 0;
     HIP_TRY(s, hipMemcpyAsync(&flags, s->d_flags, sizeof flags, hipMemcpyDeviceToHost, s->stream),
             "read flags");
     HIP_TRY(s, hipStreamSynchronize(s->stream), "synchronize");
-    if (flags & 1) return fail(s, RDOS_EOVERFLOW, "a molecule count overflowed int32");
-    if (flags & 4) return fail(s, RDOS_EDEVICE, "occupied-tet queue overflowed (internal error)");
-    if (flags & 8) return fail(s, RDOS_EDEVICE, "a grid barrier of the one-launch path timed out (internal error)");
-    if (flags & 2)
-        return fail(s, RDOS_EOVERFLOW, "a tet fired more than %u reactions in one period; shorten tau",
-                    kMaxEventsPerPeriod);
-    return RDOS_OK;
+    return flags_status(s, flags);
+}
+
+// Pinned buffers for small read-outs: a kernel writes the counts and the flags
+// into one, and a single wait replaces two copies with theirs (the 750-tet
+// cube, one period and its counts: 41 us a pass, 62 with the copies).  At most
+// kReadBuffers of kReadBytes each while simulations are alive, taken and
+// returned under a lock; a caller that finds none free copies instead, as does
+// a simulation in its first reads (making a buffer costs as much as several).
+class ReadBuffers {
+public:
+    static constexpr int kReadBuffers = 16, kFirstReads = 4;
+    static constexpr size_t kReadBytes = size_t(64) << 10;
+    void *take()
+    {
+        std::lock_guard<std::mutex> g(mu_);
+        if (!free_.empty()) {
+            void *p = free_.back();
+            free_.pop_back();
+            return p;
+        }
+        if (made_ >= kReadBuffers) return nullptr;
+        void *p = nullptr;
+        std::lock_guard<std::mutex> dg(device_api_mutex());
+        if (hipHostMalloc(&p, kReadBytes, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        ++made_;
+        return p;
+    }
+    void give(void *p)
+    {
+        std::lock_guard<std::mutex> g(mu_);
+        free_.push_back(p);
+    }
+    void simulation_made()
+    {
+        std::lock_guard<std::mutex> g(mu_);
+        ++alive_;
+    }
+    void simulation_gone()  // with the last one the buffers go back
+    {
+        std::lock_guard<std::mutex> g(mu_);
+        if (--alive_ > 0 || free_.empty()) return;
+        std::lock_guard<std::mutex> dg(device_api_mutex());
+        for (void *p : free_) (void)hipHostFree(p);
+        made_ -= (int)free_.size();
+        free_.clear();
+    }
+
+private:
+    std::mutex mu_;
+    std::vector<void *> free_;
+    int made_ = 0;
+    int64_t alive_ = 0;
+};
+static ReadBuffers &read_buffers()
+{
+    static ReadBuffers b;
+    return b;
 }
 
 rdos_status enqueue_period(rdos_sim *s, int64_t period, int64_t partial, double tau_last)
@@ -609,22 +733,14 @@ void free_device(rdos_sim *s)
     (void)hipSetDevice(s->device);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     std::lock_guard<std::mutex> g(device_api_mutex());
-    void *ptrs[] = {s->d_mesh,
-                    s->d_buf[0],
-                    s->d_buf[1],
-                    s->d_mask[0],
-                    s->d_mask[1],
-                    s->d_flags,
-                    s->d_desc,
-                    s->d_tiles,
-                    s->d_allowed,
-                    s->resident_one.done,
+    void *ptrs[] = {s->d_mesh,           s->d_state, s->d_desc, s->d_tiles, s->d_allowed, s->resident_one.done,
                     s->resident_many.done};
     for (void *p : ptrs) dev_free(p, s->stream);
     free_queue(&s->queue, s->stream);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     s->d_mask[0] = s->d_mask[1] = nullptr;
     s->d_mesh = nullptr;
+    s->d_state = nullptr;
     s->d_allowed = nullptr;
     s->d_buf[0] = s->d_buf[1] = s->d_flags = nullptr;
     s->d_desc = nullptr;
@@ -659,6 +775,7 @@ rdos_status rdos_create(rdos_sim **out, int device, uint64_t seed, int32_t n_rea
     s->device = device;
     s->seed = seed;
     s->Rz = n_realizations;
+    read_buffers().simulation_made();
     *out = s;
     return RDOS_OK;
 }
@@ -670,11 +787,10 @@ rdos_status rdos_set_mesh(rdos_sim *s, int32_t n_verts, const double *xyz, int32
     if (s->state != SimState::Created) return fail(s, RDOS_ESTATE, "set_mesh after the mesh was set");
     if (n_verts < 4 || n_tets < 1 || !xyz || !tet_verts)
         return fail(s, RDOS_EINVAL, "mesh needs >= 4 vertices and >= 1 tetrahedron");
-    for (int64_t i = 0; i < 3 * (int64_t)n_verts; ++i)
-        if (!std::isfinite(xyz[i])) return fail(s, RDOS_EINVAL, "vertex coordinate %lld is not finite", (long long)i);
-    for (int64_t i = 0; i < 4 * (int64_t)n_tets; ++i)
-        if (tet_verts[i] < 0 || tet_verts[i] >= n_verts)
-            return fail(s, RDOS_EINVAL, "vertex id %d out of range at %lld", tet_verts[i], (long long)i);
+    const int64_t off = first_not_finite(xyz, 3 * (int64_t)n_verts);
+    if (off >= 0) return fail(s, RDOS_EINVAL, "vertex coordinate %lld is not finite", (long long)off);
+    const int64_t id = first_not_below(tet_verts, 4 * (int64_t)n_tets, n_verts);
+    if (id >= 0) return fail(s, RDOS_EINVAL, "vertex id %d out of range at %lld", tet_verts[id], (long long)id);
     s->xyz.assign(xyz, xyz + 3 * (size_t)n_verts);
     s->tet_verts = std::make_shared<const std::vector<int32_t>>(tet_verts, tet_verts + 4 * (size_t)n_tets);
     s->n_verts = n_verts;
@@ -690,11 +806,10 @@ rdos_status rdos_set_surface_mesh(rdos_sim *s, int32_t n_verts, const double *xy
     if (s->state != SimState::Created) return fail(s, RDOS_ESTATE, "set_surface_mesh after the mesh was set");
     if (n_verts < 3 || n_tris < 1 || !xyz || !tri_verts)
         return fail(s, RDOS_EINVAL, "surface needs >= 3 vertices and >= 1 triangle");
-    for (int64_t i = 0; i < 3 * (int64_t)n_verts; ++i)
-        if (!std::isfinite(xyz[i])) return fail(s, RDOS_EINVAL, "vertex coordinate %lld is not finite", (long long)i);
-    for (int64_t i = 0; i < 3 * (int64_t)n_tris; ++i)
-        if (tri_verts[i] < 0 || tri_verts[i] >= n_verts)
-            return fail(s, RDOS_EINVAL, "vertex id %d out of range at %lld", tri_verts[i], (long long)i);
+    const int64_t off = first_not_finite(xyz, 3 * (int64_t)n_verts);
+    if (off >= 0) return fail(s, RDOS_EINVAL, "vertex coordinate %lld is not finite", (long long)off);
+    const int64_t id = first_not_below(tri_verts, 3 * (int64_t)n_tris, n_verts);
+    if (id >= 0) return fail(s, RDOS_EINVAL, "vertex id %d out of range at %lld", tri_verts[id], (long long)id);
     s->xyz.assign(xyz, xyz + 3 * (size_t)n_verts);
     s->tet_verts = std::make_shared<const std::vector<int32_t>>(tri_verts, tri_verts + 3 * (size_t)n_tris);
     s->cell_verts = 3;
@@ -823,18 +938,26 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
     const size_t count_bytes = (size_t)s->Rz * S * (size_t)Tp * sizeof(int32_t);
     const size_t mask_bytes = (size_t)s->Rz * S * mask_stride(Tp);
 
-    // temporary set-up buffers
-    double *d_xyz = nullptr, *d_vol = nullptr, *d_bc = nullptr, *d_area = nullptr, *d_D = nullptr;
-    int32_t *d_tv = nullptr, *d_nbr = nullptr, *d_match_err = nullptr;
-    void *d_match = nullptr;
-    unsigned long long *d_tau = nullptr;
+    // temporary set-up buffers, one allocation: each place 256-byte aligned
+    char *setup = nullptr;
+    size_t setup_bytes = 0;
+    const auto place = [&](size_t bytes) {
+        const size_t at = setup_bytes;
+        setup_bytes += (std::max<size_t>(bytes, 1) + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t at_xyz = place(s->xyz.size() * sizeof(double)), at_tv = place(s->tet_verts->size() * sizeof(int32_t)),
+                 at_nbr = place(nbr_n * sizeof(int32_t)), at_vol = place((size_t)T * sizeof(double)),
+                 at_bc = place((size_t)T * 3 * sizeof(double)), at_area = place((size_t)T * 4 * sizeof(double)),
+                 at_D = place((size_t)S * sizeof(double)), at_tau = place(sizeof(unsigned long long)),
+                 at_err = place(sizeof(int32_t)),
+                 at_match = place(on_device ? face_match_scratch_bytes(T, s->cell_verts) : 0);
     std::unique_lock<std::mutex> alloc_lock(device_api_mutex(), std::defer_lock);
     auto cleanup = [&]() {
         if (s->stream) (void)hipStreamSynchronize(s->stream);
         std::unique_lock<std::mutex> g(device_api_mutex(), std::defer_lock);
         if (!alloc_lock.owns_lock()) g.lock();
-        void *p[] = {d_xyz, d_vol, d_bc, d_area, d_D, d_tv, d_nbr, d_tau, d_match_err, d_match};
-        for (void *q : p) dev_free(q, s->stream);
+        dev_free(setup, s->stream);
     };
 #define SETUP_TRY(expr, what)                               \
     do {                                                    \
@@ -848,32 +971,28 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
     } while (0)
     alloc_lock.lock();
     SETUP_TRY(dev_alloc((void **)&s->d_mesh, (size_t)T * sizeof(MeshRec), s->stream), "allocate mesh tables");
-    SETUP_TRY(dev_alloc((void **)&s->d_buf[0], count_bytes, s->stream), "allocate counts");
-    SETUP_TRY(dev_alloc((void **)&s->d_buf[1], count_bytes, s->stream), "allocate counts");
-    SETUP_TRY(dev_alloc((void **)&s->d_mask[0], mask_bytes, s->stream), "allocate occupancy");
-    SETUP_TRY(dev_alloc((void **)&s->d_mask[1], mask_bytes, s->stream), "allocate occupancy");
-    SETUP_TRY(dev_alloc((void **)&s->d_flags, 64, s->stream), "allocate flags");
+    // counts, occupancy maps and flags: one allocation, cleared together
+    const size_t count_room = (count_bytes + 255) & ~(size_t)255, mask_room = (mask_bytes + 255) & ~(size_t)255;
+    SETUP_TRY(dev_alloc((void **)&s->d_state, 2 * (count_room + mask_room) + 64, s->stream), "allocate counts");
+    for (int b = 0; b < 2; ++b) {
+        s->d_buf[b] = reinterpret_cast<int32_t *>(s->d_state + b * count_room);
+        s->d_mask[b] = reinterpret_cast<uint8_t *>(s->d_state + 2 * count_room + b * mask_room);
+    }
+    s->d_flags = reinterpret_cast<int32_t *>(s->d_state + 2 * (count_room + mask_room));
     SETUP_TRY(dev_alloc((void **)&s->d_desc, sizeof(DevSim), s->stream), "allocate descriptor");
+    SETUP_TRY(dev_alloc((void **)&s->d_tiles, (size_t)tiles_of(s) * sizeof(Tile), s->stream), "allocate work list");
     SETUP_TRY(alloc_queue(&s->queue, tiles_of(s), S, s->stream), "allocate queue");
     s->queue.owned = tiles_of(s) <= kMaxSegments ? 1 : 0;  // a segment and a scan wavefront per tile
-    SETUP_TRY(dev_alloc((void **)&d_xyz, s->xyz.size() * sizeof(double), s->stream), "allocate set-up");
-    SETUP_TRY(dev_alloc((void **)&d_tv, s->tet_verts->size() * sizeof(int32_t), s->stream), "allocate set-up");
-    SETUP_TRY(dev_alloc((void **)&d_nbr, nbr_n * sizeof(int32_t), s->stream), "allocate set-up");
-    if (on_device) {
-        SETUP_TRY(dev_alloc((void **)&d_match_err, 64, s->stream), "allocate face matching");
-        SETUP_TRY(dev_alloc(&d_match, face_match_scratch_bytes(T, s->cell_verts), s->stream), "allocate face matching");
-    }
-    SETUP_TRY(dev_alloc((void **)&d_vol, (size_t)T * sizeof(double), s->stream), "allocate set-up");
-    SETUP_TRY(dev_alloc((void **)&d_bc, (size_t)T * 3 * sizeof(double), s->stream), "allocate set-up");
-    SETUP_TRY(dev_alloc((void **)&d_area, (size_t)T * 4 * sizeof(double), s->stream), "allocate set-up");
-    SETUP_TRY(dev_alloc((void **)&d_D, (size_t)S * sizeof(double), s->stream), "allocate set-up");
-    SETUP_TRY(dev_alloc((void **)&d_tau, sizeof(unsigned long long) + 8, s->stream), "allocate set-up");
+    SETUP_TRY(dev_alloc((void **)&setup, setup_bytes, s->stream), "allocate set-up");
     alloc_lock.unlock();
-    SETUP_TRY(hipMemsetAsync(s->d_buf[0], 0, count_bytes, s->stream), "clear counts");
-    SETUP_TRY(hipMemsetAsync(s->d_buf[1], 0, count_bytes, s->stream), "clear counts");
-    SETUP_TRY(hipMemsetAsync(s->d_mask[0], 0, mask_bytes, s->stream), "clear occupancy");
-    SETUP_TRY(hipMemsetAsync(s->d_mask[1], 0, mask_bytes, s->stream), "clear occupancy");
-    SETUP_TRY(hipMemsetAsync(s->d_flags, 0, 64, s->stream), "clear flags");
+    double *d_xyz = reinterpret_cast<double *>(setup + at_xyz), *d_vol = reinterpret_cast<double *>(setup + at_vol),
+           *d_bc = reinterpret_cast<double *>(setup + at_bc), *d_area = reinterpret_cast<double *>(setup + at_area),
+           *d_D = reinterpret_cast<double *>(setup + at_D);
+    int32_t *d_tv = reinterpret_cast<int32_t *>(setup + at_tv), *d_nbr = reinterpret_cast<int32_t *>(setup + at_nbr),
+            *d_match_err = reinterpret_cast<int32_t *>(setup + at_err);
+    void *d_match = setup + at_match;
+    unsigned long long *d_tau = reinterpret_cast<unsigned long long *>(setup + at_tau);
+    SETUP_TRY(hipMemsetAsync(s->d_state, 0, 2 * (count_room + mask_room) + 64, s->stream), "clear counts");
     SETUP_TRY(hipMemsetAsync(d_tau, 0xff, sizeof(unsigned long long), s->stream), "clear tau");
     SETUP_TRY(hipMemcpyAsync(d_xyz, s->xyz.data(), s->xyz.size() * sizeof(double), hipMemcpyHostToDevice, s->stream),
               "upload vertices");
@@ -1027,32 +1146,13 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
         d.k[q] = r.k;
         if (r.rn == 0) d.zeroth = 1;
     }
-    // work list: one tile per 1024 tets of each realization
-    std::vector<Tile> tiles;
-    for (int32_t r = 0; r < s->Rz; ++r)
-        for (int32_t t0 = 0; t0 < T; t0 += kTetsPerTile)
-            tiles.push_back({0, r, t0, std::min<int32_t>(kTetsPerTile, T - t0)});
-    s->n_tiles = (int32_t)tiles.size();
-    hipError_t e;
-    {
-        std::lock_guard<std::mutex> g(device_api_mutex());
-        e = dev_alloc((void **)&s->d_tiles, tiles.size() * sizeof(Tile), s->stream);
-    }
-    if (e != hipSuccess) {
-        free_device(s);
-        return hip_fail(s, e, "allocate work list");
-    }
-    e = hipMemcpyAsync(s->d_tiles, tiles.data(), tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, s->stream);
-    if (e != hipSuccess) {
-        free_device(s);
-        return hip_fail(s, e, "upload work list");
-    }
-    e = set_queue_work(&s->queue, s->n_tiles, 1, s->stream);
-    if (e != hipSuccess) {
-        free_device(s);
-        return hip_fail(s, e, "queue header");
-    }
-    st = upload_desc(s);
+    // the work list (one tile per 1024 tets of each realization), its header
+    // and the descriptor, written by one kernel: nothing to upload and wait for
+    s->n_tiles = (int32_t)tiles_of(s);
+    st = RDOS_OK;
+    hipError_t e = launch_own_work(d, s->d_desc, queue_header(&s->queue, s->n_tiles, 1, 0), s->queue.hdr, s->d_tiles,
+                                   s->stream);
+    if (e != hipSuccess) st = hip_fail(s, e, "work list");
     if (st == RDOS_OK) st = plan_resident(s, cut_one(s), &s->resident_one);
     if (st == RDOS_OK) st = plan_resident(s, cut_many(s), &s->resident_many);
     if (st != RDOS_OK) {
@@ -1088,11 +1188,9 @@ rdos_status rdos_set_counts(rdos_sim *s, int32_t realization, int32_t species, c
     if (s->state == SimState::Created) return fail(s, RDOS_ESTATE, "set_counts needs a mesh");
     if (realization < 0 || realization >= s->Rz || species < 0 || species >= (int32_t)s->D.size() || !counts)
         return fail(s, RDOS_EINVAL, "realization or species out of range");
-    int64_t total = 0;
-    for (int32_t t = 0; t < s->T; ++t) {
-        if (counts[t] < 0) return fail(s, RDOS_EINVAL, "negative count at tet %d", t);
-        total += counts[t];
-    }
+    int64_t negative;
+    const int64_t total = sum_counts(counts, s->T, &negative);
+    if (negative >= 0) return fail(s, RDOS_EINVAL, "negative count at tet %d", (int32_t)negative);
     if (total > 0x3fffffff) return fail(s, RDOS_EOVERFLOW, "more than 2^30 molecules of one species");
     if ((int64_t)s->Rz * s->T > 0x7fffffff) return fail(s, RDOS_EINVAL, "realizations x tets exceeds 2^31");
     if (s->state == SimState::Meshed) {
@@ -1118,9 +1216,29 @@ rdos_status rdos_get_counts(rdos_sim *s, int32_t realization, int32_t species, i
     HIP_TRY(s, hipSetDevice(s->device), "set device");
     const int32_t *src =
         s->d_buf[s->step & 1] + ((int64_t)realization * (int64_t)s->D.size() + species) * padded_tets(s->T);
-    HIP_TRY(s, hipMemcpyAsync(out, src, (size_t)s->T * sizeof(int32_t), hipMemcpyDeviceToHost, s->stream),
-            "download counts");
-    return check_flags(s);
+    const size_t bytes = (size_t)s->T * sizeof(int32_t);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    (void)hipStreamIsCapturing(s->stream, &capture);
+    if (s->reads <= ReadBuffers::kFirstReads) s->reads += 1;
+    void *buffer = s->reads > ReadBuffers::kFirstReads && bytes + sizeof(int32_t) <= ReadBuffers::kReadBytes &&
+                           capture == hipStreamCaptureStatusNone
+                       ? read_buffers().take()
+                       : nullptr;
+    if (!buffer) {
+        HIP_TRY(s, hipMemcpyAsync(out, src, bytes, hipMemcpyDeviceToHost, s->stream), "download counts");
+        return check_flags(s);
+    }
+    int32_t *staged = static_cast<int32_t *>(buffer);
+    hipError_t e = launch_read_counts(src, s->d_flags, staged, s->T, s->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+    int32_t flags = 0;
+    if (e == hipSuccess) {
+        std::memcpy(out, staged, bytes);
+        flags = staged[s->T];
+    }
+    read_buffers().give(buffer);
+    HIP_TRY(s, e, "download counts");
+    return flags_status(s, flags);
 }
 
 rdos_status rdos_device_counts(rdos_sim *s, int32_t realization, int32_t species, int32_t **out)
@@ -1232,18 +1350,48 @@ rdos_status rdos_get_geometry(rdos_sim *s, int32_t *nbr, double *w, double *g, d
     if (!s) return RDOS_EINVAL;
     if (s->state != SimState::Ready) return fail(s, RDOS_ESTATE, "get_geometry before finalize");
     HIP_TRY(s, hipSetDevice(s->device), "set device");
-    std::vector<MeshRec> m((size_t)s->T);
-    HIP_TRY(s, hipMemcpyAsync(m.data(), s->d_mesh, m.size() * sizeof(MeshRec), hipMemcpyDeviceToHost, s->stream),
-            "download mesh tables");
-    HIP_TRY(s, hipStreamSynchronize(s->stream), "download mesh tables");
-    for (int32_t t = 0; t < s->T; ++t) {
-        for (int f = 0; f < 4; ++f) {
-            if (nbr) nbr[4 * (size_t)t + f] = m[t].nbr[f];
-            if (w) w[4 * (size_t)t + f] = f < 3 ? m[t].w[f] : m[t].w3;
-        }
-        if (g) g[t] = m[t].g;
-        if (nav) nav[t] = m[t].nav;
+    // the tables are laid out apart on the device and copied into the caller's
+    // arrays, not copied as records and taken apart on the host
+    const size_t T = (size_t)s->T;
+    const size_t at_w = 16 * T, at_g = at_w + 32 * T, at_nav = at_g + 8 * T;
+    char *tables = nullptr;
+    {
+        std::lock_guard<std::mutex> g2(device_api_mutex());
+        if (dev_alloc((void **)&tables, at_nav + 8 * T, s->stream) != hipSuccess) tables = nullptr;
     }
+    if (!tables) {  // no room beside the simulation
+        (void)hipGetLastError();
+        std::vector<MeshRec> m(T);
+        HIP_TRY(s, hipMemcpyAsync(m.data(), s->d_mesh, T * sizeof(MeshRec), hipMemcpyDeviceToHost, s->stream),
+                "download mesh tables");
+        HIP_TRY(s, hipStreamSynchronize(s->stream), "download mesh tables");
+        for (size_t t = 0; t < T; ++t) {
+            for (int f = 0; f < 4; ++f) {
+                if (nbr) nbr[4 * t + f] = m[t].nbr[f];
+                if (w) w[4 * t + f] = f < 3 ? m[t].w[f] : m[t].w3;
+            }
+            if (g) g[t] = m[t].g;
+            if (nav) nav[t] = m[t].nav;
+        }
+        return RDOS_OK;
+    }
+    hipError_t e = launch_unpack_mesh(s->d_mesh, s->T, reinterpret_cast<int32_t *>(tables),
+                                      reinterpret_cast<double *>(tables + at_w),
+                                      reinterpret_cast<double *>(tables + at_g),
+                                      reinterpret_cast<double *>(tables + at_nav), s->stream);
+    const auto copy = [&](void *to, size_t at, size_t bytes) {
+        if (to && e == hipSuccess) e = hipMemcpyAsync(to, tables + at, bytes, hipMemcpyDeviceToHost, s->stream);
+    };
+    copy(nbr, 0, 16 * T);
+    copy(w, at_w, 32 * T);
+    copy(g, at_g, 8 * T);
+    copy(nav, at_nav, 8 * T);
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+    {
+        std::lock_guard<std::mutex> g2(device_api_mutex());
+        dev_free(tables, s->stream);
+    }
+    HIP_TRY(s, e, "download mesh tables");
     return RDOS_OK;
 }
 
@@ -1266,6 +1414,7 @@ void rdos_destroy(rdos_sim *s)
     if (!s) return;
     free_device(s);
     delete s;
+    read_buffers().simulation_gone();
 }
 
 }  // extern "C"

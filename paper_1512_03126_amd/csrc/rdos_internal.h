@@ -194,6 +194,9 @@ inline int32_t scan_blocks_for(int64_t n_tiles)
     const int64_t b = (n_tiles + kBlock / 64 - 1) / (kBlock / 64);
     return (int32_t)(b < 1 ? 1 : (b > (1 << 20) ? (1 << 20) : b));
 }
+// The work list of one simulation alone: its descriptor, header and tiles.
+hipError_t launch_own_work(const DevSim &d, DevSim *desc, const WorkHeader &h, WorkHeader *hdr, Tile *tiles,
+                           hipStream_t st);
 hipError_t launch_advance(DevSim *sims, const WorkHeader *hdr, int64_t by, hipStream_t st);
 // Writes tiles[0 .. n_tiles) from n_units work units whose `first` fields
 // ascend from 0 and leave no gaps (each unit has at least one tile).
@@ -313,6 +316,11 @@ hipError_t launch_mask_build(const int32_t *counts, uint8_t *mask_cur, uint8_t *
 // Bytes of one species row of the occupancy map: one per four tets, padded
 // to 16 bytes so that the scan reads four bytes at a time.
 inline int32_t mask_stride(int64_t Tp) { return (int32_t)(((Tp / 4) + 15) & ~(int64_t)15); }
+// counts[0 .. T) and the flags word to out[0 .. T] (pinned host memory).
+hipError_t launch_read_counts(const int32_t *counts, const int32_t *flags, int32_t *out, int32_t T, hipStream_t st);
+// The mesh records taken apart: nbr[T][4], w[T][4], g[T], nav[T].
+hipError_t launch_unpack_mesh(const MeshRec *mesh, int32_t T, int32_t *nbr, double *w, double *g, double *nav,
+                              hipStream_t st);
 hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t st);
 // blocks x 256 lanes each split n molecules reps times, one-by-one or by
 // sequential binomials; sink holds blocks * 256 int64.

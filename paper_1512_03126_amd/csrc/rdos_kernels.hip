@@ -161,6 +161,27 @@ hipError_t launch_geometry(const double *xyz, const int32_t *tet_verts, const in
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void unpack_mesh_kernel(const MeshRec *__restrict__ mesh, int32_t T,
+                                                          int32_t *__restrict__ nbr, double *__restrict__ w,
+                                                          double *__restrict__ g, double *__restrict__ nav)
+{
+    const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= T) return;
+    const MeshRec m = mesh[t];
+    *reinterpret_cast<int4 *>(nbr + 4 * (int64_t)t) = make_int4(m.nbr[0], m.nbr[1], m.nbr[2], m.nbr[3]);
+    *reinterpret_cast<double2 *>(w + 4 * (int64_t)t) = make_double2(m.w[0], m.w[1]);
+    *reinterpret_cast<double2 *>(w + 4 * (int64_t)t + 2) = make_double2(m.w[2], m.w3);
+    g[t] = m.g;
+    nav[t] = m.nav;
+}
+
+hipError_t launch_unpack_mesh(const MeshRec *mesh, int32_t T, int32_t *nbr, double *w, double *g, double *nav,
+                              hipStream_t st)
+{
+    unpack_mesh_kernel<<<(T + 255) / 256, 256, 0, st>>>(mesh, T, nbr, w, g, nav);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Face matching (the neighbours of Sec. II.A's subvolumes): each face of a
 // cell becomes a key, its vertex ids sorted and packed (bits per id), with
@@ -1347,6 +1368,28 @@ hipError_t launch_expand_tiles(const WorkUnit *units, int32_t n_units, int32_t n
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void own_work_kernel(DevSim d, DevSim *__restrict__ desc, WorkHeader h,
+                                                       WorkHeader *__restrict__ hdr, Tile *__restrict__ tiles)
+{
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    const int32_t per = (d.T + kTetsPerTile - 1) / kTetsPerTile;
+    if (i < h.n_tiles) {
+        const int32_t t0 = (i % per) * kTetsPerTile;
+        tiles[i] = Tile{0, i / per, t0, min(kTetsPerTile, d.T - t0)};
+    }
+    if (i == 0) {
+        *desc = d;
+        *hdr = h;
+    }
+}
+
+hipError_t launch_own_work(const DevSim &d, DevSim *desc, const WorkHeader &h, WorkHeader *hdr, Tile *tiles,
+                           hipStream_t st)
+{
+    own_work_kernel<<<(h.n_tiles + 255) / 256, 256, 0, st>>>(d, desc, h, hdr, tiles);
+    return hipGetLastError();
+}
+
 template <bool OWNED>
 static void scan_for_species(const DevSim *sims, const Tile *tiles, int64_t iter, const Queue &q, int32_t qsel,
                              int32_t species, int32_t scan_grid, hipStream_t st)
@@ -1549,6 +1592,20 @@ hipError_t launch_mask_build(const int32_t *counts, uint8_t *mask_cur, uint8_t *
     if (n <= 0) return hipSuccess;
     mask_build_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(counts, mask_cur, mask_other, tag, Tp, stride,
                                                                     n);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void read_counts_kernel(const int32_t *__restrict__ counts,
+                                                          const int32_t *__restrict__ flags,
+                                                          int32_t *__restrict__ out, int32_t T)
+{
+    const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t <= T) out[t] = t < T ? counts[t] : flags[0];
+}
+
+hipError_t launch_read_counts(const int32_t *counts, const int32_t *flags, int32_t *out, int32_t T, hipStream_t st)
+{
+    read_counts_kernel<<<T / 256 + 1, 256, 0, st>>>(counts, flags, out, T);
     return hipGetLastError();
 }
 

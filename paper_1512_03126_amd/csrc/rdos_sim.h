@@ -59,6 +59,7 @@ struct rdos_sim {
     bool own_stream = false;
     rdos::MeshRec *d_mesh = nullptr;
     uint32_t *d_allowed = nullptr;  // per-tet reaction masks (only with regions)
+    char *d_state = nullptr;        // counts, maps and flags below: one allocation
     int32_t *d_buf[2] = {nullptr, nullptr};  // counts; the state of period k is d_buf[k & 1]
     uint8_t *d_mask[2] = {nullptr, nullptr};   // occupancy maps of d_buf[0], d_buf[1]
     bool mask_dirty = false;                 // counts were written from the host: rebuild d_mask
@@ -67,6 +68,7 @@ struct rdos_sim {
     rdos::Tile *d_tiles = nullptr;
     int32_t n_tiles = 0;
     rdos::QueueView queue{};      // occupied tets of one period (tet ids + counts + segment lengths)
+    int32_t reads = 0;            // of counts to the host, up to the number that makes a pinned buffer worth it
     int64_t launches = 0;         // periods launched on this handle (selects the queue length half)
     int32_t update_bps = 1;       // update blocks per queue segment
     int32_t launch_mode = 0;      // as rdos_set_launch_mode takes it
@@ -85,6 +87,7 @@ int64_t padded_tets(int32_t T);
 size_t state_bytes(const rdos_sim *s);
 size_t queue_bytes(int64_t n_tiles, int32_t n_species);
 hipError_t alloc_queue(rdos::QueueView *q, int64_t capacity_tiles, int32_t n_species, hipStream_t st);
+rdos::WorkHeader queue_header(rdos::QueueView *q, int64_t n_tiles, int32_t n_sims, int32_t tile0);
 hipError_t set_queue_work(rdos::QueueView *q, int64_t n_tiles, int32_t n_sims, hipStream_t st, int32_t tile0 = 0);
 void free_queue(rdos::QueueView *q, hipStream_t st);
 // Device memory from the per-device stream-ordered pool (ordered on st).
