@@ -224,30 +224,105 @@ ResidentCut resident_cut(int32_t T, int32_t S, int32_t R, int32_t max_blocks)
     const int32_t k = std::max(1, std::min(max_blocks, (T + 15) / 16));
     const int32_t len = k == 1 ? T : ((T + k - 1) / k + 15) & ~15;
     const int64_t ls = ((int64_t)len + 3) & ~(int64_t)3;
-    if (S * ls > 0xffff || resident_lds_bytes(S, R, (int32_t)ls, 64) > kResidentLdsMax) return c;
+    const int32_t rows = (int32_t)std::min<int64_t>(ls, 0xffff);
+    c.full = resident_lds_bytes(S, R, rows, true, rows, 64) <= kResidentLdsMax;
+    if (S * ls > 0xffff || resident_lds_bytes(S, R, rows, c.full, resident_least(rows), 64) > kResidentLdsMax) return c;
     c.len = len;
     c.blocks = (T + len - 1) / len;
     // a lane per (tet, species) pair, up to a block's limit
     c.threads = (int32_t)std::min<int64_t>(kResidentMaxThreads, (S * ls + 63) & ~(int64_t)63);
-    c.lds_bytes = std::min(kResidentLdsMax, resident_lds_bytes(S, R, (int32_t)ls, c.threads));
+    c.lds_bytes = c.full ? std::min(kResidentLdsMax, resident_lds_bytes(S, R, rows, true, rows, c.threads))
+                         : kResidentLdsMax;
     return c;
+}
+
+// Pairs that a realization is expected to hold: the counts last set, spread
+// evenly.
+static double expected_pairs(const rdos_sim *s)
+{
+    const int32_t S = (int32_t)s->D.size();
+    double pairs = 0.0;
+    for (int32_t m = 0; m < S; ++m) {
+        double total = 0.0;
+        for (int32_t r = 0; r < s->Rz; ++r) total += (double)s->totals[(size_t)r * S + m];
+        pairs += (double)s->T * (1.0 - std::exp(-total / ((double)s->Rz * s->T)));
+    }
+    return pairs;
+}
+
+// Whether the short layout's lists hold what a block is expected to, with room
+// to spare.  Blocks whose lists overflow move every molecule through memory,
+// which is slower than the two-launch path: us per period, two launches and
+// this, 998,250 tets of four species at 0.3 and 1 molecules per tet 71 and
+// 101, 121 and 167; below that, at 0.1 and 0.03: 44 and 25, 23 and 15.5.
+bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c)
+{
+    if (c.full) return true;
+    if (s->desc.zeroth) return false;  // every tet is listed for the SSA
+    const int32_t S = (int32_t)s->D.size(), R = (int32_t)s->rx.size(), ls = (c.len + 3) & ~3;
+    return expected_pairs(s) * c.len <= 0.5 * (double)s->T * S * resident_range(S, R, ls, c.lds_bytes);
+}
+
+// One block per realization, more of them (n) than compute units: the widest
+// blocks of which enough share a compute unit.  Narrower blocks finish later
+// but more run at once, which pays while a lane has a few pairs to itself and
+// the number of turns falls; a block that has its compute unit alone takes all
+// its lanes.  Measured, us per period with 512 lanes (two blocks per compute
+// unit), 256 (four) and 128 (eight): 600 realizations of 750 tets at 0.02
+// molecules per species and tet 8.3, 4.9 and 6.2, at 0.3 14.9, 12.5 and 18, at
+// 2 50, 69 and 89; 1500 of them at 0.02 13.4, 9.1 and 7.2.  1024 lanes against
+// 512, one block per compute unit: 1500 realizations of 1944 tets at 2
+// molecules 216 and 297.  Light blocks with a compute unit each are slower than
+// the sparse kernel (`light` false: left to it): 600 realizations of 6000 tets
+// of three species with 180 pairs in each 21.9 and 12.4, with 1200 36 and 33;
+// 400 of 3072 tets with 1900 pairs 25.8 and 49.5.
+bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int32_t cus, bool light,
+                      ResidentPlan *plan)
+{
+    double work = 0.0;  // items of the fullest block: pairs, and tets that always run the SSA
+    for (size_t i = 0; i < n_sims; ++i)
+        work = std::max(work, expected_pairs(sims[i]) + (sims[i]->desc.zeroth ? sims[i]->T : 0.0));
+    for (int32_t per_cu = 8; per_cu >= 1; per_cu /= 2) {
+        const int32_t threads = kResidentMaxThreads / per_cu;
+        if (per_cu == 1 && !light && work < 1500.0) break;
+        if (per_cu > 2 && (n <= (int64_t)cus * per_cu / 2 || work > (per_cu == 8 ? 2.0 : 4.0) * threads)) continue;
+        // whole units of the hardware's LDS allocation (1280 bytes)
+        const int32_t most = kResidentLdsMax / per_cu / 1280 * 1280, lanes = per_cu == 2 ? 128 : 64;
+        int32_t lds = 0, full = 1, widest = 0;
+        for (size_t i = 0; i < n_sims; ++i) {
+            const int32_t S = (int32_t)sims[i]->D.size(), R = (int32_t)sims[i]->rx.size(),
+                          rows = (sims[i]->T + 3) & ~3;
+            lds = std::max(lds, resident_lds_bytes(S, R, rows, true, rows, threads));
+            if (resident_lds_bytes(S, R, rows, true, rows, lanes) > most) full = 0;
+            widest = std::max(widest, (S * rows + 63) & ~63);
+        }
+        lds = full ? std::min(lds, most) : most;
+        bool fits = true;
+        for (size_t i = 0; i < n_sims && !full; ++i) {
+            const int32_t S = (int32_t)sims[i]->D.size(), R = (int32_t)sims[i]->rx.size(),
+                          rows = (sims[i]->T + 3) & ~3;
+            ResidentCut c;
+            c.len = sims[i]->T;
+            c.lds_bytes = lds;
+            fits &= resident_lds_bytes(S, R, rows, false, resident_least(rows), 64) <= lds &&
+                    resident_lists_hold(sims[i], c);
+        }
+        if (!fits) continue;
+        plan->threads = std::min(threads, widest);
+        plan->lds_bytes = lds;
+        plan->full = full;
+        return true;
+    }
+    return false;
 }
 
 // The cuts of a simulation's realizations for the resident kernel, alone and
 // over the device.  Several blocks per realization wait for each other, so
 // all must be on the device at once: no more than its compute units (a block
-// fills one).  With more blocks than compute units, blocks of half the size
-// share them: on 1000 realizations of the 750-tet cube 512 lanes took 18.0
-// us per period, 1024 lanes 25.5 and 256 lanes 19.8.
+// fills one).
 static ResidentCut cut_one(const rdos_sim *s)
 {
-    ResidentCut c = resident_cut(s->T, (int32_t)s->D.size(), (int32_t)s->rx.size(), 1);
-    if (c.blocks && s->Rz > compute_units(s->device) && c.threads > 512) {
-        c.threads = 512;
-        c.lds_bytes = std::min(c.lds_bytes, resident_lds_bytes((int32_t)s->D.size(), (int32_t)s->rx.size(),
-                                                               (s->T + 3) & ~3, 512));
-    }
-    return c;
+    return resident_cut(s->T, (int32_t)s->D.size(), (int32_t)s->rx.size(), 1);
 }
 static ResidentCut cut_many(const rdos_sim *s)
 {
@@ -275,6 +350,7 @@ static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan
     p.max_parts = c.blocks;
     p.threads = c.threads;
     p.lds_bytes = c.lds_bytes;
+    p.full = c.full;
     p.scaled = s->transfer_form == 1;
     void *memory = nullptr;
     {
@@ -297,21 +373,30 @@ static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan
 // molecules per tet 64 and 23.5.  A single period of a work list too large
 // for the one-launch path costs the same either way (0.51 ms with the
 // reading of 3 x 384,000 counts), without the cooperative launch.
-static const ResidentPlan *resident_for(const rdos_sim *s, int64_t n)
+static const ResidentPlan *resident_for(rdos_sim *s, int64_t n)
 {
     if (s->launch_mode != 0) return nullptr;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
         return nullptr;  // the period counters of a replay would start over
-    const ResidentPlan &one = s->resident_one, &many = s->resident_many;
-    if (many.blocks == 0) return one.blocks ? &one : nullptr;
-    if (one.blocks) {
+    const ResidentPlan *one = s->resident_one.blocks ? &s->resident_one : nullptr;
+    const ResidentPlan *many = s->resident_many.blocks ? &s->resident_many : nullptr;
+    const int32_t cus = compute_units(s->device);
+    if (one && s->Rz > cus) {
+        const rdos_sim *sim = s;
+        if (!resident_in_turn(&sim, 1, s->Rz, cus, true, &s->resident_one)) one = nullptr;
+    } else if (one && !one->full && !resident_lists_hold(s, cut_one(s))) {
+        one = nullptr;
+    }
+    if (many && !many->full && !resident_lists_hold(s, cut_many(s))) many = nullptr;
+    if (!many) return one;
+    if (one) {
         int64_t molecules = 0;
         for (int64_t t : s->totals) molecules += t;
         const int64_t pairs = (int64_t)s->T * (int64_t)s->D.size();
-        if (pairs <= kResidentMaxThreads && molecules <= 2 * pairs * s->Rz) return &one;
+        if (pairs <= kResidentMaxThreads && molecules <= 2 * pairs * s->Rz) return one;
     }
-    return n > 1 || s->n_tiles <= kPersistTiles ? &many : nullptr;
+    return n > 1 || s->n_tiles <= kPersistTiles ? many : nullptr;
 }
 
 static int64_t tiles_of(const rdos_sim *s) { return (int64_t)s->Rz * ((s->T + kTetsPerTile - 1) / kTetsPerTile); }

@@ -241,7 +241,12 @@ size_t tune_candidate(const rdos_engine *e)
 // Cuts every realization of the slots for the resident kernel, or returns
 // false where their counts do not fit the device's LDS.  Each gets the blocks
 // it needs, the rest of the compute units are shared out by tet-species.
-bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, ResidentPlan &plan)
+// Lists that fit only as several launches, one after the other, stay with the
+// queue: two simulations of 998,250 tets took 22 us per period either way, three
+// 34 and 26.
+// More realizations than compute units run one block each (see
+// resident_in_turn for `light`).
+bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, ResidentPlan &plan, bool light)
 {
     const int32_t cus = compute_units(e->device);
     struct Sim {
@@ -268,13 +273,15 @@ bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, Reside
     const int64_t spare = cus - need;
     units.clear();
     plan = ResidentPlan{};
+    plan.full = 1;
     for (size_t i = 0; i < sims.size(); ++i) {
         Sim &m = sims[i];
         const int32_t S = (int32_t)m.s->D.size(), R = (int32_t)m.s->rx.size();
         if (!alone) m.blocks += (int32_t)((double)spare * m.pairs / all);
         const ResidentCut c = resident_cut(m.s->T, S, R, m.blocks);
-        if (c.blocks == 0) return false;
-        plan.threads = std::max(plan.threads, alone ? std::min(c.threads, 512) : c.threads);
+        if (c.blocks == 0 || (!alone && !resident_lists_hold(m.s, c))) return false;
+        if (!c.full) plan.full = 0;
+        plan.threads = std::max(plan.threads, c.threads);
         plan.max_parts = std::max(plan.max_parts, c.blocks);
         if (m.s->desc.transfer_form == 1) plan.scaled = 1;
         for (int32_t r = 0; r < m.s->Rz; ++r) {
@@ -282,12 +289,18 @@ bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, Reside
             plan.blocks += c.blocks;
         }
     }
+    if (alone) {
+        std::vector<const rdos_sim *> all_sims;
+        for (const Sim &m : sims) all_sims.push_back(m.s);
+        return resident_in_turn(all_sims.data(), all_sims.size(), n_units, cus, light, &plan);
+    }
     for (const ResidentUnit &u : units) {
         const rdos_sim *s = sims[u.sim].s;
-        plan.lds_bytes = std::max(plan.lds_bytes, resident_lds_bytes((int32_t)s->D.size(), (int32_t)s->rx.size(),
-                                                                     (u.len + 3) & ~3, plan.threads));
+        const int32_t rows = (u.len + 3) & ~3;
+        plan.lds_bytes = std::max(plan.lds_bytes, resident_lds_bytes((int32_t)s->D.size(), (int32_t)s->rx.size(), rows,
+                                                                     true, rows, plan.threads));
     }
-    plan.lds_bytes = std::min(plan.lds_bytes, kResidentLdsMax);
+    plan.lds_bytes = plan.full ? std::min(plan.lds_bytes, kResidentLdsMax) : kResidentLdsMax;
     return true;
 }
 
@@ -425,7 +438,11 @@ rdos_status build_work(rdos_engine *e)
     e->lds_period_ms = 0.0;
     std::vector<ResidentUnit> runits;
     std::vector<WorkUnit> sunits;
-    if (!sims.empty() && cut_resident(e, runits, e->resident)) {
+    // light blocks with a compute unit each only after the sparse kernel
+    bool resident = !sims.empty() && cut_resident(e, runits, e->resident, false);
+    const bool sparse = !sims.empty() && !resident && plan_sparse(e, sunits, e->sparse);
+    if (!sims.empty() && !resident && !sparse) resident = cut_resident(e, runits, e->resident, true);
+    if (resident) {
         st = ensure(e, &e->d_runits, &e->cap_runits, (int64_t)runits.size(), "engine block units");
         if (st != RDOS_OK) return st;
         st = ensure(e, &e->d_resident, &e->cap_resident,
@@ -439,7 +456,7 @@ rdos_status build_work(rdos_engine *e)
                                              ResidentUnit{}, e->stream),
                    "engine blocks");
         e->lds_path = LdsPath::Resident;
-    } else if (!sims.empty() && plan_sparse(e, sunits, e->sparse)) {
+    } else if (sparse) {
         SparsePlan &p = e->sparse;
         st = ensure(e, &e->d_sunits, &e->cap_sunits, (int64_t)sunits.size(), "engine sparse units");
         if (st != RDOS_OK) return st;

@@ -242,6 +242,7 @@ struct ResidentPlan {
     int32_t max_parts;          // blocks of the realization with the most; above 1 the launches are cooperative
     int32_t threads;
     int32_t lds_bytes;
+    int32_t full;               // layout
     int32_t scaled;             // some simulation uses transfer form 1
 };
 constexpr int kResidentMaxThreads = 1024;
@@ -250,21 +251,40 @@ constexpr int64_t kResidentMaxUnits = 1 << 16;  // of an engine's work list
 constexpr int32_t kResidentLdsMax = 160 * 1024;
 constexpr int kResidentFlagStride = 16;  // 128 bytes between blocks' period counters
 constexpr int32_t kResidentHeadBytes = kMaxSpecies * 8 + kMaxReactions * 16 + 16;
-// LDS of a block whose species rows hold `ls` tets (a multiple of 4): two
-// count buffers, the list of pairs, and with reactions the rounded mean
-// populations and the list of tets for the SSA.
-__host__ __device__ inline int32_t resident_state_bytes(int32_t S, int32_t R, int32_t ls)
-{
-    const int32_t P = S * ls;
-    return kResidentHeadBytes + ((10 * P + (R > 0 ? 4 * P + 2 * ls : 0) + 15) & ~15);
-}
+// Two layouts of a block whose species rows hold `ls` tets (a multiple of 4).
+// Full: two count buffers and lists that hold every pair.  Short: one count
+// buffer, and lists for `range` tets, an eighth of the block's at least (whole
+// four-tet groups).
+__host__ __device__ inline int32_t resident_least(int32_t ls) { return 4 * ((ls / 4 + 7) / 8); }
 // A lane's share in the SSA: occupancy integrals, times, constants and
 // propensities.
 __host__ __device__ inline int32_t resident_lane_bytes(int32_t S, int32_t R) { return 16 * (S + R); }
-// Both, for `lanes` lanes in the SSA (64 at least).
-__host__ __device__ inline int32_t resident_lds_bytes(int32_t S, int32_t R, int32_t ls, int32_t lanes)
+// The lists for `range` tets: the pairs (short layout: and their counts), and
+// with reactions the rounded mean populations and the tets for the SSA.
+__host__ __device__ inline int32_t resident_list_bytes(int32_t S, int32_t R, bool full, int32_t range)
 {
-    return resident_state_bytes(S, R, ls) + (R > 0 ? resident_lane_bytes(S, R) * lanes : 0);
+    return (((full ? 2 * S : 6 * S) + (R > 0 ? 4 * S + 2 : 0)) * range + 15) & ~15;
+}
+// LDS with `lanes` lanes in the SSA (64 at least; none without reactions).
+__host__ __device__ inline int32_t resident_lds_bytes(int32_t S, int32_t R, int32_t ls, bool full, int32_t range,
+                                                      int32_t lanes)
+{
+    return kResidentHeadBytes + (full ? 8 : 4) * S * ls + resident_list_bytes(S, R, full, range) +
+           (R > 0 ? resident_lane_bytes(S, R) * lanes : 0);
+}
+// The tets the short layout's lists hold in `lds` bytes: up to 256 lanes in
+// the SSA (a wavefront per SIMD) come first.
+__host__ __device__ inline int32_t resident_range(int32_t S, int32_t R, int32_t ls, int32_t lds)
+{
+    const int32_t least = resident_least(ls);
+    int32_t left = lds - resident_lds_bytes(S, R, ls, false, least, 64);
+    if (R > 0) {
+        const int32_t more = (left / resident_lane_bytes(S, R)) & ~63;
+        left -= (more < 192 ? more : 192) * resident_lane_bytes(S, R);
+    }
+    if (left < 16) return least;
+    const int32_t range = least + ((left - 15) / (6 * S + (R > 0 ? 4 * S + 2 : 0)) & ~3);
+    return range < ls ? range : ls;
 }
 // Device memory of a plan, and its arrays' places in it (16-byte aligned).
 size_t resident_plan_bytes(int64_t blocks, int64_t max_parts);

@@ -22,15 +22,28 @@
 //     waiting for neighbours 2.5.  Nothing else is written during a run, so
 //     no cache has to be written back: all shared words are read and written
 //     by agent-scope atomics.
+//   * Layout.  Full: two count buffers in LDS and lists with room for every
+//     pair.  Where a block's tets need more than that, short: one buffer (the
+//     counts of listed pairs are taken out before any molecule moves) and
+//     lists with room for a part of its tets, which hold nearly twice as many
+//     tets, and slower where both fit (384,000 tets at 2%: full 8.7, short 9.4
+//     us per period).  A period whose pairs overflow short lists is
+//     worked through in parts, every addition through memory.
+//   * The list pass is bound by its instructions on large blocks (a wavefront
+//     takes 256 tets): a group's occupancy is one word with four bits per
+//     species, which a reaction tests for four tets at once (5,000 tets of
+//     three species in a block: 9,300 cycles with a word per tet, 7,200 so).
 //   * Two count buffers alternate by parity, as in memory.  A neighbour adds
 //     to the buffer of period k + 2 only after this block has published
 //     period k + 1, by when it has emptied that buffer of period k's arrivals.
 // Measured, us per period, two launches (or the queue-based one launch) and
 // this kernel: 750-tet cube 14.4 and 6.0; 1080-tet bar at 93 molecules per
-// tet 41.5 and 23.5; ten species on that bar 105 and 25; 1000 realizations of
-// the cube with production 33 and 18; 384,000 tets at 2% 14.8 and 8.9, with a
-// fourth species and jitter 20.3 and 11.7; 162,000 tets at 30 molecules per
-// species and tet 292 and 115.
+// tet 41.5 and 23.5; ten species on that bar 105 and 22.4; 1000 realizations
+// of the cube with production 33 and 18; 384,000 tets at 2% 14.8 and 8.6, with
+// a fourth species and jitter 20.3 and 11.4; 162,000 tets at 30 molecules per
+// species and tet 292 and 105.  Short layout: 998,250 tets of four species at
+// 0.03 and 0.1 molecules per tet 23.3 and 15.5, 43.9 and 24.7; 16 realizations
+// of 80,400 triangles 28 and 14.2.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -51,22 +64,43 @@ struct ResidentHead {
     int32_t n_ssa;    // tets listed for the SSA
     int32_t n_pairs;  // (tet, species) pairs listed for Step 3
     int32_t stop;     // a wait for other blocks failed
-    int32_t pad;
+    int32_t unused;
 };
 static_assert(sizeof(ResidentHead) == kResidentHeadBytes, "LDS head");
 
-// Moves what other blocks added to four tets into the block's counts d.
-__device__ __forceinline__ void take_arrivals(gptr<unsigned long long> p, int32_t *d)
+// What was added through memory to four tets: read, and moved into the block's
+// counts d.
+struct Arrivals {
+    gptr<unsigned long long> p;
+    unsigned long long lo, hi;
+    __device__ __forceinline__ explicit Arrivals(gptr<unsigned long long> at)
+        : p(at), lo(__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)),
+          hi(__hip_atomic_load(at + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    {
+    }
+    __device__ __forceinline__ void take(int32_t *d) const
+    {
+        if ((lo | hi) == 0) return;
+        __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        d[0] += (int32_t)(uint32_t)lo;
+        d[1] += (int32_t)(uint32_t)(lo >> 32);
+        d[2] += (int32_t)(uint32_t)hi;
+        d[3] += (int32_t)(uint32_t)(hi >> 32);
+    }
+};
+
+// Adds n molecules to tet t in the count buffer of `period`, and marks its
+// four-tet group.
+__device__ __forceinline__ void add_in_memory(const DevSim &sm, int64_t period, int64_t base, int64_t mbase,
+                                              int64_t Tp, int32_t s, int32_t t, int32_t n, bool mark)
 {
-    const unsigned long long lo = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long hi = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((lo | hi) == 0) return;
-    __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    d[0] += (int32_t)(uint32_t)lo;
-    d[1] += (int32_t)(uint32_t)(lo >> 32);
-    d[2] += (int32_t)(uint32_t)hi;
-    d[3] += (int32_t)(uint32_t)(hi >> 32);
+    const gptr<int32_t> next = global(sm.buf[period & 1]) + base;
+    __hip_atomic_fetch_add(next + (uint32_t)(s * (int32_t)Tp + t), n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!mark) return;
+    const gptr<uint8_t> marks = global(sm.mask[period & 1]) + mbase;
+    __hip_atomic_store(marks + (uint32_t)(s * sm.mstride + (t >> 2)), occupancy_tag(period), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Blocks of up to this many four-tet groups (over all species) read every
@@ -190,7 +224,7 @@ void resident_place(ResidentPlan *plan, void *memory)
 
 // n_periods periods of the block's part (parts[blockIdx.x]) of one
 // realization, the iterations iter0 .. of its simulation.
-template <bool ANY_SCALED>
+template <bool ANY_SCALED, bool FULL>
 __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
     const DevSim *__restrict__ sims, const ResidentPart *__restrict__ parts,
     const uint16_t *__restrict__ neighbours, int32_t max_parts, int64_t iter0, int32_t n_periods, int64_t partial,
@@ -213,13 +247,16 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
     const int32_t ls = (len + 3) & ~3;  // stride between species rows
     const int32_t P = S * ls;
     const uint32_t per_species = (uint32_t)(0xffffffffu / (uint32_t)ls + 1u);  // e / ls == umulhi(e, per_species)
-    int32_t *counts = reinterpret_cast<int32_t *>(lds + kResidentHeadBytes);   // [2][P]
-    int32_t *pop = counts + 2 * P;                                             // [P] when R > 0
-    uint16_t *list = reinterpret_cast<uint16_t *>(pop + (R > 0 ? P : 0));      // [P]
-    uint16_t *ssa_list = list + P;                                             // [ls] when R > 0
-    const int32_t used = resident_state_bytes(S, R, ls);
-    double *lane_state = reinterpret_cast<double *>(lds + used);
+    const int32_t range = FULL ? ls : resident_range(S, R, ls, lds_bytes);  // tets the lists are sure to hold
+    const int32_t room = S * range;                                         // pairs
+    const int32_t used = resident_lds_bytes(S, R, ls, FULL, range, 0);
     const int32_t lanes = R > 0 ? min(nt, ((lds_bytes - used) / resident_lane_bytes(S, R)) & ~63) : 0;
+    int32_t *counts = reinterpret_cast<int32_t *>(lds + kResidentHeadBytes);  // [2][P] or [P]
+    int32_t *taken = counts + (FULL ? 2 : 1) * P;  // [room] short: counts of the listed pairs from the nt-th on
+    int32_t *pop = taken + (FULL ? 0 : room);      // [room] rounded mean populations of the pairs the SSA listed
+    uint16_t *list = reinterpret_cast<uint16_t *>(pop + (R > 0 ? room : 0));  // [room] pairs
+    uint16_t *ssa_list = list + room;              // [range] tets
+    double *lane_state = reinterpret_cast<double *>(lds + used);
 
     const int64_t Tp = ((int64_t)sm.T + 3) & ~(int64_t)3;
     const int64_t base = (int64_t)pt.realization * S * Tp;
@@ -240,18 +277,25 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
             const int32_t s = (int32_t)__umulhi(4u * (uint32_t)v, per_species);
             const gptr<v4i> p = (gptr<v4i>)(src + s * Tp + (4 * v - s * ls));
             *reinterpret_cast<v4i *>(counts + 4 * v) = *p;
-            *reinterpret_cast<v4i *>(counts + P + 4 * v) = v4i{0, 0, 0, 0};
-            if (!alone) {  // neighbours add to this buffer from the second period on
+            if (FULL) *reinterpret_cast<v4i *>(counts + P + 4 * v) = v4i{0, 0, 0, 0};
+            if (!alone || !FULL) {  // additions through memory reach this buffer from the second period on
                 const gptr<unsigned long long> z = (gptr<unsigned long long>)p;
                 __hip_atomic_store(z, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(z + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }
+    if (!FULL) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the buffer is empty before additions to it
     __syncthreads();
 
-    // the species each reaction needs, reaction q's in lane q
-    const uint32_t need_of_lane = (int32_t)__lane_id() < R ? head.rx[__lane_id()].needed() : 0u;
+    // the reactants of reaction q in lane q, as shifts of a group's occupancy
+    // (four bits per species); a reaction without reactants: bit 16
+    uint32_t reactants = 0;
+    if ((int32_t)__lane_id() < R) {
+        const BlockReaction x = head.rx[__lane_id()];
+        const int a = x.order() > 0 ? x.species(0) : 0, b = x.order() > 1 ? x.species(1) : a;
+        reactants = x.order() > 0 ? (uint32_t)(4 * a) | (uint32_t)(4 * b) << 8 : 1u << 16;
+    }
 
     for (int32_t k = 0; k < n_periods; ++k) {
         // read the descriptor's fields in the period that uses them: held
@@ -262,179 +306,251 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         const int64_t period = first + k;
         const uint32_t period32 = (uint32_t)period;
         const double tau_k = period == partial ? tau_last : sm.tau;
-        int32_t *cur = counts + (k & 1) * P, *nxt = counts + ((k & 1) ^ 1) * P;
+        int32_t *cur = FULL ? counts + (k & 1) * P : counts;
+        int32_t *nxt = FULL ? counts + ((k & 1) ^ 1) * P : counts;
+        bool spill = false;  // short lists that would overflow
 
-        // List the (tet, species) pairs that hold molecules, and the tets
-        // where a reaction's reactants are all present.  A lane takes the
-        // four tets of a group, every species (one 16-byte LDS load each).
-        for (int32_t g0 = 0; g0 < ls / 4; g0 += nt) {
-            const int32_t i = 4 * (g0 + tid);
-            uint32_t held[4] = {0, 0, 0, 0};
-            if (i < ls) {
-                int32_t sign = 0;
-                for (int s0 = 0; s0 < S; s0 += 4) {  // four loads in flight; past the last species it repeats
-                    v4i c[4];
+        for (int32_t from = 0, to = ls; from < ls;) {
+            // List the tets where a reaction's reactants are all present, and
+            // the (tet, species) pairs that hold molecules in the others.  A
+            // lane takes the four tets of a group, every species (one 16-byte
+            // LDS load each).
+            for (int32_t i0 = from; i0 < to; i0 += 4 * nt) {
+                const int32_t i = i0 + 4 * tid;
+                uint64_t held = 0;  // bit 4 s + b: species s in tet i + b
+                if (i < to) {
+                    int32_t sign = 0;
+                    const auto group = [&sign](const v4i &c) {
+                        sign |= c.x | c.y | c.z | c.w;
+                        return min((uint32_t)c.x, 1u) | min((uint32_t)c.y, 1u) << 1 | min((uint32_t)c.z, 1u) << 2 |
+                               min((uint32_t)c.w, 1u) << 3;
+                    };
+                    int s0 = 0;
+                    for (; s0 + 1 < S; s0 += 4) {  // four loads in flight; past the last species it repeats
+                        v4i c[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        c[j] = *reinterpret_cast<const v4i *>(cur + min(s0 + j, S - 1) * ls + i);
+                        for (int j = 0; j < 4; ++j)
+                            c[j] = *reinterpret_cast<const v4i *>(cur + min(s0 + j, S - 1) * ls + i);
+                        uint32_t four = 0;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int s = min(s0 + j, S - 1);
-                        sign |= c[j].x | c[j].y | c[j].z | c[j].w;
-                        held[0] |= (uint32_t)(c[j].x != 0) << s;
-                        held[1] |= (uint32_t)(c[j].y != 0) << s;
-                        held[2] |= (uint32_t)(c[j].z != 0) << s;
-                        held[3] |= (uint32_t)(c[j].w != 0) << s;
+                        for (int j = 0; j < 4; ++j) four |= group(c[j]) << 4 * (min(s0 + j, S - 1) - s0);
+                        held |= (uint64_t)four << 4 * s0;
+                    }
+                    if (s0 < S) held |= (uint64_t)group(*reinterpret_cast<const v4i *>(cur + s0 * ls + i)) << 4 * s0;
+                    if (sign < 0) {  // a count wrapped by an overflowing addition: reported, and dropped
+                        atomicOr(sm.flags, 1);
+                        for (int s = 0; s < S; ++s)
+                            for (int b = 0; b < 4; ++b) cur[s * ls + i + b] = max(cur[s * ls + i + b], 0);
                     }
                 }
-                if (sign < 0) {  // a count wrapped by an overflowing addition: reported, and dropped
-                    atomicOr(sm.flags, 1);
-                    for (int s = 0; s < S; ++s)
-                        for (int b = 0; b < 4; ++b) cur[s * ls + i + b] = max(cur[s * ls + i + b], 0);
+                if (__ballot(held != 0) == 0 && !sm.zeroth) continue;  // uniform over the wavefront
+                int32_t total;
+                if (R > 0) {
+                    uint32_t fire = 0;  // the tets where some reaction may
+                    if (!sm.allowed) {
+                        for (int q = 0; q < R; ++q) {
+                            const uint32_t x = __builtin_amdgcn_readlane(reactants, q);
+                            fire |= ((uint32_t)(held >> (x & 63u)) & (uint32_t)(held >> (x >> 8 & 63u))) |
+                                    (x >> 16 ? 15u : 0u);
+                        }
+                    } else {
+                        for (int q = 0; q < R; ++q) {
+                            const uint32_t x = __builtin_amdgcn_readlane(reactants, q);
+                            const uint32_t f = ((uint32_t)(held >> (x & 63u)) & (uint32_t)(held >> (x >> 8 & 63u))) |
+                                               (x >> 16 ? 15u : 0u);
+                            for (int b = 0; b < 4; ++b)
+                                if ((f >> b & 1u) && i + b < len) fire |= (sm.allowed[t0 + i + b] >> q & 1u) << b;
+                        }
+                    }
+                    fire &= (1u << min(max(min(len, to) - i, 0), 4)) - 1u;
+                    const int32_t at = wave_prefix(__popc(fire), 3, &total);
+                    if (total > 0) {
+                        held &= ~(0x1111111111111111ull * fire);  // the SSA's lane lists them
+                        int32_t j = at + reserve(&head.n_ssa, total);
+                        for (; fire; fire &= fire - 1u, ++j)
+                            if (FULL || j < range) ssa_list[j] = (uint16_t)(i + __builtin_ctz(fire));
+                    }
                 }
-            }
-            int32_t total;
-            const uint32_t n = __popc(held[0]) + __popc(held[1]) + __popc(held[2]) + __popc(held[3]);
-            int32_t at = wave_prefix(n, 32 - __builtin_clz(4 * S), &total);
-            if (total > 0) {
-                at += reserve(&head.n_pairs, total);
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    for (uint32_t m = held[b]; m; m &= m - 1u) list[at++] = (uint16_t)(__builtin_ctz(m) * ls + i + b);
-            }
-            if (R > 0 && (total > 0 || sm.zeroth)) {
-                uint32_t can[4] = {0, 0, 0, 0};
-                for (int q = 0; q < R; ++q) {
-                    const uint32_t need = __builtin_amdgcn_readlane(need_of_lane, q);
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) can[b] |= (uint32_t)((held[b] & need) == need) << q;
-                }
-                uint32_t fire = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    if (i + b >= len) can[b] = 0;
-                    if (can[b] && sm.allowed) can[b] &= sm.allowed[t0 + i + b];
-                    fire |= (uint32_t)(can[b] != 0) << b;
-                }
-                at = wave_prefix(__popc(fire), 3, &total);
+                int32_t at = wave_prefix(__popcll(held), 32 - __builtin_clz(4 * S), &total);
                 if (total > 0) {
-                    at += reserve(&head.n_ssa, total);
-                    for (; fire; fire &= fire - 1u) ssa_list[at++] = (uint16_t)(i + __builtin_ctz(fire));
-                }
-            }
-        }
-        __syncthreads();
-
-        // Step 2
-        if (R > 0) {
-            const int32_t n_ssa = head.n_ssa;
-            if (n_ssa > 0) {  // uniform over the block
-                for (int32_t j = tid; j < n_ssa && tid < lanes; j += lanes) {
-                    const int32_t i = ssa_list[j], t = t0 + i;
-                    const BlockCell cell{cur + i, lane_state + tid, ls, lanes, S, R};
-                    uint32_t held = 0;
-                    for (int s = 0; s < S; ++s) held |= (uint32_t)(cell.n(s) != 0) << s;
-                    uint32_t touched = block_ssa(sm, head.rx, t, period32, tau_k, key1, cell);
-                    // the touched species that still hold molecules: eq. 2
-                    // and the stochastic rounding; bit 31 of the count tells
-                    // Step 3 to take them from pop[]
-                    for (; touched; touched &= touched - 1u) {
-                        const int s = __builtin_ctz(touched);
-                        const int32_t Ns = cell.n(s);
-                        if (Ns <= 0) continue;
-                        if (!((held >> s) & 1u)) list[atomicAdd(&head.n_pairs, 1)] = (uint16_t)(s * ls + i);
-                        if (sm.first_order || !((sm.diff_mask >> s) & 1u)) continue;
-                        const double nbar = mean_occupancy(cell, s, Ns, tau_k);
-                        int32_t ni = (int32_t)floor(nbar);
-                        const double frac = nbar - (double)ni;
-                        uint32_t drew = 0;
-                        if (frac > 0.0) {
-                            Stream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
-                            if (rng.uniform() < frac) ni += 1;
-                            drew = 0x80000000u;
+                    at += reserve(&head.n_pairs, total);
+                    const auto put = [&](uint32_t m, int s0) {
+                        for (; m; m &= m - 1u, ++at) {
+                            const int32_t bit = __builtin_ctz(m);
+                            if (FULL || at < room) list[at] = (uint16_t)((s0 + (bit >> 2)) * ls + i + (bit & 3));
                         }
-                        pop[s * ls + i] = (int32_t)((uint32_t)ni | drew);
-                        cell.n(s) = (int32_t)((uint32_t)Ns | 0x80000000u);
-                    }
+                    };
+                    put((uint32_t)held, 0);
+                    if (S > 8) put((uint32_t)(held >> 32), 8);
                 }
-                __syncthreads();
-                if (tid == 0) head.n_ssa = 0;
-            }
-        }
-
-        // Step 3: one lane per pair
-        const int32_t n_pairs = head.n_pairs;
-        for (int32_t j = tid; j < n_pairs; j += nt) {
-            const uint32_t e = list[j];
-            const int32_t s = (int32_t)__umulhi(e, per_species);
-            const int32_t t = t0 + (int32_t)e - s * ls;
-            const uint32_t raw = (uint32_t)cur[e];
-            cur[e] = 0;
-            const int32_t Ns = (int32_t)(raw & 0x7fffffffu);
-            int32_t stay = Ns;
-            if (Ns > 0 && ((sm.diff_mask >> s) & 1u)) {
-                const MeshRec *mr = sm.mesh + t;
-                const int4 n4 = *reinterpret_cast<const int4 *>(mr->nbr);
-                const int32_t nb[4] = {n4.x, n4.y, n4.z, n4.w};
-                const double w[4] = {mr->w[0], mr->w[1], mr->w[2], ANY_SCALED ? mr->w3 : 0.0};
-                const double g = mr->g;
-                PrimedStream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
-                int32_t ni = Ns;
-                if (raw >> 31) {
-                    const uint32_t code = (uint32_t)pop[e];
-                    ni = (int32_t)(code & 0x7fffffffu);
-                    if (code >> 31) (void)rng.uniform();  // the rounding's draw
-                }
-                double zeta = (tau_k * head.D[s]) * g;
-                if (zeta > 1.0) zeta = 1.0;
-                int32_t out[4];
-                const int32_t n = leave_and_split<ANY_SCALED>(ni, Ns, zeta, sm.transfer_form == 1, nb, w,
-                                                              sm.split_threshold, rng, out);
-                if (n > 0) {
-                    stay = Ns - n;
-#pragma unroll
-                    for (int f = 0; f < 4; ++f) {
-                        if (out[f] <= 0) continue;
-                        const int32_t i = nb[f] - t0;
-                        if ((uint32_t)i < (uint32_t)len) {
-                            atomicAdd(&nxt[s * ls + i], out[f]);
-                        } else {  // another block's tet
-                            const gptr<int32_t> next = global(sm.buf[(period + 1) & 1]) + base;
-                            __hip_atomic_fetch_add(next + (uint32_t)(s * (int32_t)Tp + nb[f]), out[f],
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            if (!direct) {
-                                const gptr<uint8_t> marks = global(sm.mask[(period + 1) & 1]) + mbase;
-                                __hip_atomic_store(marks + (uint32_t)(s * sm.mstride + (nb[f] >> 2)),
-                                                   occupancy_tag(period + 1), __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                            }
-                        }
-                    }
-                }
-            }
-            if (stay > 0) atomicAdd(&nxt[e], stay);
-        }
-        // additions for other blocks' tets reach memory before this block
-        // publishes the period
-        if (!alone) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) head.n_pairs = 0;
-        if (!alone) {
-            const unsigned long long target = epoch + (unsigned long long)k + 1ull;
-            if (tid < 64) {
-                if (tid == 0)
-                    __hip_atomic_store(&done[(int64_t)pt.part * kResidentFlagStride], target, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                if (!wait_neighbours(done, nlist, pt.neighbours, my_neighbour, target, fail) && tid == 0)
-                    head.stop = 1;
             }
             __syncthreads();
-            // what other blocks added to this block's tets
+            int32_t n_ssa = head.n_ssa;
+            if (!FULL && to - from > range) {
+                // over the whole range with short lists: where the pairs may
+                // not fit, go on in parts, every addition through memory
+                spill = n_ssa > range || head.n_pairs + S * n_ssa > room;
+                __syncthreads();  // all have read the lengths before the SSA adds to them
+                if (spill) {      // uniform over the block
+                    if (tid == 0) head.n_ssa = head.n_pairs = 0;
+                    __syncthreads();
+                    to = range;
+                    continue;
+                }
+            }
+            n_ssa = min(n_ssa, range);
+
+            // Step 2
+            if (R > 0) {
+                if (n_ssa > 0) {  // uniform over the block
+                    for (int32_t j = tid; j < n_ssa && tid < lanes; j += lanes) {
+                        const int32_t i = ssa_list[j], t = t0 + i;
+                        const BlockCell cell{cur + i, lane_state + tid, ls, lanes, S, R};
+                        const uint32_t touched = block_ssa(sm, head.rx, t, period32, tau_k, key1, cell);
+                        // its pairs, the wavefront's species by species: lanes
+                        // of Step 3 that share a species draw alike (162,000
+                        // tets at 30 molecules per species and tet: 150,000
+                        // cycles for Step 3 in the order of the tets, 118,000
+                        // so).  Touched: eq. 2 and the stochastic rounding;
+                        // bit 31 of the count tells Step 3 to take them from
+                        // pop[].
+                        uint32_t held = 0;
+                        int32_t total = 0;  // of the lanes that are here
+                        for (int s = 0; s < S; ++s) {
+                            const bool here = cell.n(s) > 0;
+                            held |= (uint32_t)here << s;
+                            total += (int32_t)__popcll(__ballot(here));
+                        }
+                        int32_t next_at = reserve(&head.n_pairs, total);
+                        for (int s = 0; s < S; ++s) {
+                            const bool here = (held >> s) & 1u;
+                            const int32_t at = next_at + wave_prefix(here ? 1u : 0u, 1, &total);
+                            next_at += total;
+                            if (!here) continue;
+                            list[at] = (uint16_t)(s * ls + i);
+                            if (!((touched >> s) & 1u) || sm.first_order || !((sm.diff_mask >> s) & 1u)) continue;
+                            const int32_t Ns = cell.n(s);
+                            const double nbar = mean_occupancy(cell, s, Ns, tau_k);
+                            int32_t ni = (int32_t)floor(nbar);
+                            const double frac = nbar - (double)ni;
+                            uint32_t drew = 0;
+                            if (frac > 0.0) {
+                                Stream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
+                                if (rng.uniform() < frac) ni += 1;
+                                drew = 0x80000000u;
+                            }
+                            pop[at] = (int32_t)((uint32_t)ni | drew);
+                            cell.n(s) = (int32_t)((uint32_t)Ns | 0x80000000u);
+                        }
+                    }
+                    __syncthreads();
+                }
+            }
+
+            // Step 3: one lane per pair.  Short layout: the counts of listed
+            // pairs are taken out first (the first nt stay in registers), so
+            // that what moves or stays is added to the same array.
+            const int32_t n_pairs = head.n_pairs;
+            uint32_t first_raw = 0;
+            if (!FULL && !spill) {
+                for (int32_t j = tid; j < n_pairs; j += nt) {
+                    const uint32_t e = list[j], c = (uint32_t)cur[e];
+                    cur[e] = 0;
+                    if (j < nt)
+                        first_raw = c;
+                    else
+                        taken[j] = (int32_t)c;
+                }
+                __syncthreads();
+            }
+            for (int32_t j = tid; j < n_pairs; j += nt) {
+                const uint32_t e = list[j];
+                const int32_t s = (int32_t)__umulhi(e, per_species);
+                const int32_t t = t0 + (int32_t)e - s * ls;
+                uint32_t raw;
+                if (FULL) {
+                    raw = (uint32_t)cur[e];
+                    cur[e] = 0;
+                } else {
+                    raw = spill ? (uint32_t)cur[e] : j < nt ? first_raw : (uint32_t)taken[j];
+                }
+                const int32_t Ns = (int32_t)(raw & 0x7fffffffu);
+                int32_t stay = Ns;
+                if (Ns > 0 && ((sm.diff_mask >> s) & 1u)) {
+                    const MeshRec *mr = sm.mesh + t;
+                    const int4 n4 = *reinterpret_cast<const int4 *>(mr->nbr);
+                    const int32_t nb[4] = {n4.x, n4.y, n4.z, n4.w};
+                    const double w[4] = {mr->w[0], mr->w[1], mr->w[2], ANY_SCALED ? mr->w3 : 0.0};
+                    const double g = mr->g;
+                    PrimedStream rng(sm.key0, key1, (uint32_t)s, (uint32_t)t, period32);
+                    int32_t ni = Ns;
+                    if (raw >> 31) {
+                        const uint32_t code = (uint32_t)pop[j];
+                        ni = (int32_t)(code & 0x7fffffffu);
+                        if (code >> 31) (void)rng.uniform();  // the rounding's draw
+                    }
+                    double zeta = (tau_k * head.D[s]) * g;
+                    if (zeta > 1.0) zeta = 1.0;
+                    int32_t out[4];
+                    const int32_t n = leave_and_split<ANY_SCALED>(ni, Ns, zeta, sm.transfer_form == 1, nb, w,
+                                                                  sm.split_threshold, rng, out);
+                    if (n > 0) {
+                        stay = Ns - n;
+#pragma unroll
+                        for (int f = 0; f < 4; ++f) {
+                            if (out[f] <= 0) continue;
+                            const int32_t i = nb[f] - t0;
+                            if ((uint32_t)i < (uint32_t)len && !spill)
+                                atomicAdd(&nxt[s * ls + i], out[f]);
+                            else  // another block's tet
+                                add_in_memory(sm, period + 1, base, mbase, Tp, s, nb[f], out[f], !direct);
+                        }
+                    }
+                }
+                if (stay > 0) {
+                    if (!spill)
+                        atomicAdd(&nxt[e], stay);
+                    else
+                        add_in_memory(sm, period + 1, base, mbase, Tp, s, t, stay, !direct);
+                }
+            }
+            __syncthreads();
+            if (tid == 0) head.n_ssa = head.n_pairs = 0;
+            if (FULL) break;
+            from = to;
+            to = min(ls, to + range);
+            if (from < ls) __syncthreads();
+        }
+        // additions through memory reach it before this block publishes the
+        // period
+        if (!alone || spill) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (spill)
+                for (int32_t v = tid; v < P / 4; v += nt) *reinterpret_cast<v4i *>(cur + 4 * v) = v4i{0, 0, 0, 0};
+            __syncthreads();
+            if (!alone) {
+                const unsigned long long target = epoch + (unsigned long long)k + 1ull;
+                if (tid < 64) {
+                    if (tid == 0)
+                        __hip_atomic_store(&done[(int64_t)pt.part * kResidentFlagStride], target, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                    if (!wait_neighbours(done, nlist, pt.neighbours, my_neighbour, target, fail) && tid == 0)
+                        head.stop = 1;
+                }
+                __syncthreads();
+            }
+            // what was added to this block's tets
             const gptr<int32_t> next = global(sm.buf[(period + 1) & 1]) + base + t0;
             if (direct) {
-                for (int32_t v = tid; v < P / 4; v += nt) {
-                    const int32_t s = (int32_t)__umulhi(4u * (uint32_t)v, per_species);
-                    take_arrivals((gptr<unsigned long long>)(next + s * Tp + (4 * v - s * ls)), nxt + 4 * v);
+                // two groups per pass, their loads in flight together
+                for (int32_t v = tid; v < P / 4; v += 2 * nt) {
+                    const int32_t u = min(v + nt, P / 4 - 1);
+                    const int32_t sv = (int32_t)__umulhi(4u * (uint32_t)v, per_species),
+                                  su = (int32_t)__umulhi(4u * (uint32_t)u, per_species);
+                    const Arrivals one((gptr<unsigned long long>)(next + sv * Tp + (4 * v - sv * ls))),
+                        two((gptr<unsigned long long>)(next + su * Tp + (4 * u - su * ls)));
+                    one.take(nxt + 4 * v);
+                    if (v + nt < P / 4) two.take(nxt + 4 * u);
                 }
             } else {
                 const gptr<uint8_t> marks = global(sm.mask[(period + 1) & 1]) + mbase + (t0 >> 2);
@@ -449,7 +565,8 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
                     for (int b = 0; b < 4; ++b) {
                         if (((m >> (8 * b)) & 0xffu) != mark) continue;
                         const int32_t i = 16 * wd + 4 * b;
-                        take_arrivals((gptr<unsigned long long>)(next + s * Tp + i), nxt + s * ls + i);
+                        const Arrivals here((gptr<unsigned long long>)(next + s * Tp + i));
+                        here.take(nxt + s * ls + i);
                     }
                 }
             }
@@ -460,7 +577,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
 
     // the state of the next period, its occupancy bytes, and an empty other buffer
     const int64_t end = first + n_periods;
-    const int32_t *fin = counts + (n_periods & 1) * P;
+    const int32_t *fin = FULL ? counts + (n_periods & 1) * P : counts;
     const gptr<int32_t> dst = global(sm.buf[end & 1]) + base + t0;
     const gptr<int32_t> other = global(sm.buf[(end & 1) ^ 1]) + base + t0;
     const gptr<uint8_t> mdst = global(sm.mask[end & 1]) + mbase + (t0 >> 2);
@@ -471,7 +588,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         const v4i c = *reinterpret_cast<const v4i *>(fin + 4 * v);
         *(gptr<v4i>)(dst + s * Tp + i) = c;
         mdst[(int64_t)s * sm.mstride + (i >> 2)] = (c.x | c.y | c.z | c.w) != 0 ? mark : (uint8_t)0;
-        if (alone && (n_periods & 1)) *(gptr<v4i>)(other + s * Tp + i) = v4i{0, 0, 0, 0};
+        if (alone && FULL && (n_periods & 1)) *(gptr<v4i>)(other + s * Tp + i) = v4i{0, 0, 0, 0};
     }
     if (head.stop && tid == 0) atomicOr(sm.flags, 8);
 }
@@ -483,8 +600,13 @@ hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t
     if (plan.blocks < 1 || plan.threads < 64 || plan.threads > kResidentMaxThreads ||
         plan.lds_bytes > kResidentLdsMax)
         return hipErrorInvalidValue;
-    const void *fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true>)
-                                 : reinterpret_cast<const void *>(&resident_kernel<false>);
+    const void *fn;
+    if (plan.full)
+        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, true>)
+                         : reinterpret_cast<const void *>(&resident_kernel<false, true>);
+    else
+        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, false>)
+                         : reinterpret_cast<const void *>(&resident_kernel<false, false>);
     uint32_t *fail = reinterpret_cast<uint32_t *>(plan.done + (int64_t)plan.blocks * kResidentFlagStride);
     const uint16_t *neighbours = plan.neighbours;
     int32_t max_parts = plan.max_parts;

@@ -97,8 +97,15 @@ void dev_free(void *p, hipStream_t st);
 // fit): at most max_blocks blocks of `len` tets (the last may hold fewer).
 struct ResidentCut {
     int32_t blocks = 0, len = 0, threads = 0, lds_bytes = 0;
+    bool full = false;  // layout
 };
 ResidentCut resident_cut(int32_t T, int32_t S, int32_t R, int32_t max_blocks);
+bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c);
+// Threads, LDS and layout of `plan` for n blocks, each a whole realization of
+// one of the sims, several sharing a compute unit where that pays; false where
+// they do not fit, or (light false) are light and would not share one.
+bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int32_t cus, bool light,
+                      rdos::ResidentPlan *plan);
 // Compute units of a device (0 when it cannot be asked).
 int32_t compute_units(int device);
 rdos_status match_parity(rdos_sim *s);

@@ -48,13 +48,16 @@ def chemistry(S, R):
     return D, rx
 
 
-def both(P, orc, shape, S, R, Rz, mean, seed=5, **method):
+def both(P, orc, shape, S, R, Rz, mean, seed=5, crowded=None, **method):
     xyz, tets = W.kuhn_box(*shape, 0.2e-6)
     T = tets.shape[0]
     D, rx = chemistry(S, R)
     rng = np.random.default_rng(seed)
     init = rng.poisson(mean, (Rz, S, T)).astype(np.int32)
-    init[:, 0, ::11] += 12
+    if crowded is None:
+        init[:, 0, ::11] += 12
+    else:
+        init[:, :, int(crowded * T):] = 0
     g = P.Simulation(xyz, tets, D, rx, seed=seed, n_realizations=Rz, **method)
     refs = {}
     for r in range(Rz):
@@ -81,9 +84,16 @@ def check(g, refs, what):
     ((5, 5, 5), 1, 0, 1, 0.5),      # 750 tets, light: one block
     ((5, 5, 5), 1, 2, 1, 60.0),     # the same, crowded: 47 blocks, rejection sampler
     ((5, 5, 5), 2, 4, 100, 0.2),    # two blocks per realization
-    ((3, 3, 3), 2, 4, 300, 0.5),    # more realizations than compute units
+    ((3, 3, 3), 2, 4, 300, 0.5),    # more realizations than compute units: two blocks share one
+    ((3, 3, 3), 2, 4, 700, 0.1),    # four share one
+    ((2, 2, 3), 3, 2, 1100, 0.1),   # eight share one
+    ((7, 6, 5), 3, 3, 600, 0.01),   # four share one, short lists
+    ((8, 6, 6), 3, 2, 260, 1.5),    # each has one to itself
     ((7, 5, 4), 10, 8, 1, 1.5),     # ten species
     ((4, 4, 3), 16, 32, 1, 0.7),    # the most species and reactions: 64 lanes in the SSA at a time
+    ((12, 12, 12), 1, 2, 150, 0.05),  # 10,368 tets in one block: short lists
+    ((9, 9, 10), 3, 3, 150, 0.02),  # the same with several species
+    ((16, 16, 8), 3, 0, 90, 0.02),  # two blocks, short lists, no reactions
     ((17, 16, 15), 4, 5, 1, 0.05),  # 24,480 tets, sparse: arrivals found by the occupancy bytes or directly
 ])
 def test_resident_runs_match_the_oracle(P, orc, shape, S, R, Rz, mean):
@@ -99,6 +109,21 @@ def test_resident_runs_match_the_oracle(P, orc, shape, S, R, Rz, mean):
     for o in refs.values():
         o.run_until(t)
     check(g, refs, "run_until")
+    g.close()
+
+
+@pytest.mark.parametrize("shape,Rz,mean,crowded", [
+    ((9, 9, 10), 150, 0.28, 1.0),  # one block of 4860 tets: lists for 2600 tets, 2200 of which react
+    ((16, 16, 8), 90, 0.34, 0.5),  # two of 6144 tets, the molecules in the first
+])
+def test_short_lists_overflow(P, orc, shape, Rz, mean, crowded):
+    note(f"resident: short lists that overflow, {shape} cells, {Rz} realizations")
+    g, refs = both(P, orc, shape, 3, 3, Rz, mean, crowded=crowded)
+    for n in (1, 2, 4):
+        g.step(n)
+        for o in refs.values():
+            o.run_steps(n)
+        check(g, refs, n)
     g.close()
 
 
