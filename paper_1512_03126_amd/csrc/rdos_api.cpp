@@ -355,7 +355,10 @@ static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan
     void *memory = nullptr;
     {
         std::lock_guard<std::mutex> g(device_api_mutex());
-        HIP_TRY(s, dev_alloc(&memory, resident_plan_bytes(p.blocks, p.max_parts), s->stream), "allocate block list");
+        if (dev_alloc(&memory, resident_plan_bytes(p.blocks, p.max_parts), s->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return RDOS_OK;  // no room: the queue runs the periods
+        }
     }
     resident_place(&p, memory);
     *plan = p;

@@ -223,6 +223,27 @@ rdos_status ensure(rdos_engine *e, T **buf, int64_t *cap, int64_t need, const ch
     return RDOS_OK;
 }
 
+// The same for what the paths with their state in LDS keep (no graph names
+// it): false where there is no room, and then the queue runs the periods.
+template <typename T>
+bool make_room(rdos_engine *e, T **buf, int64_t *cap, int64_t need)
+{
+    if (need <= *cap) return true;
+    if (hipStreamSynchronize(e->stream) != hipSuccess) return false;
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    if (*buf) (void)hipFree(*buf);
+    *buf = nullptr;
+    *cap = 0;
+    const int64_t n = std::max<int64_t>(need, need + need / 2);
+    if (hipMalloc(buf, (size_t)n * sizeof(T)) != hipSuccess) {
+        (void)hipGetLastError();
+        *buf = nullptr;
+        return false;
+    }
+    *cap = n;
+    return true;
+}
+
 // Species rows of the queue, which also size the scan's register arrays.
 int species_bound(int s)
 {
@@ -442,12 +463,9 @@ rdos_status build_work(rdos_engine *e)
     bool resident = !sims.empty() && cut_resident(e, runits, e->resident, false);
     const bool sparse = !sims.empty() && !resident && plan_sparse(e, sunits, e->sparse);
     if (!sims.empty() && !resident && !sparse) resident = cut_resident(e, runits, e->resident, true);
-    if (resident) {
-        st = ensure(e, &e->d_runits, &e->cap_runits, (int64_t)runits.size(), "engine block units");
-        if (st != RDOS_OK) return st;
-        st = ensure(e, &e->d_resident, &e->cap_resident,
-                    (int64_t)resident_plan_bytes(e->resident.blocks, e->resident.max_parts), "engine blocks");
-        if (st != RDOS_OK) return st;
+    if (resident && make_room(e, &e->d_runits, &e->cap_runits, (int64_t)runits.size()) &&
+        make_room(e, &e->d_resident, &e->cap_resident,
+                  (int64_t)resident_plan_bytes(e->resident.blocks, e->resident.max_parts))) {
         resident_place(&e->resident, e->d_resident);
         ENGINE_HIP(e, hipMemcpyAsync(e->d_runits, runits.data(), runits.size() * sizeof(ResidentUnit),
                                      hipMemcpyHostToDevice, e->stream),
@@ -458,19 +476,20 @@ rdos_status build_work(rdos_engine *e)
         e->lds_path = LdsPath::Resident;
     } else if (sparse) {
         SparsePlan &p = e->sparse;
-        st = ensure(e, &e->d_sunits, &e->cap_sunits, (int64_t)sunits.size(), "engine sparse units");
-        if (st != RDOS_OK) return st;
         const int64_t scratch = (int64_t)p.units * p.unit_bytes, counts = ((int64_t)p.units * 8 + 255) & ~(int64_t)255;
-        st = ensure(e, &e->d_sparse, &e->cap_sparse, scratch + counts + 256, "engine sparse scratch");
-        if (st != RDOS_OK) return st;
-        p.scratch = e->d_sparse;
-        p.counts = reinterpret_cast<int32_t *>(e->d_sparse + scratch);
-        p.fail = reinterpret_cast<uint32_t *>(e->d_sparse + scratch + counts);
-        ENGINE_HIP(e, hipMemsetAsync(p.fail, 0, sizeof(uint32_t), e->stream), "clear failure word");
-        ENGINE_HIP(e, hipMemcpyAsync(e->d_sunits, sunits.data(), sunits.size() * sizeof(WorkUnit),
-                                     hipMemcpyHostToDevice, e->stream),
-                   "upload sparse units");
-        e->lds_path = LdsPath::Sparse;
+        if (!make_room(e, &e->d_sunits, &e->cap_sunits, (int64_t)sunits.size()) ||
+            !make_room(e, &e->d_sparse, &e->cap_sparse, scratch + counts + 256))
+            p.units = 0;
+        if (p.units > 0) {
+            p.scratch = e->d_sparse;
+            p.counts = reinterpret_cast<int32_t *>(e->d_sparse + scratch);
+            p.fail = reinterpret_cast<uint32_t *>(e->d_sparse + scratch + counts);
+            ENGINE_HIP(e, hipMemsetAsync(p.fail, 0, sizeof(uint32_t), e->stream), "clear failure word");
+            ENGINE_HIP(e, hipMemcpyAsync(e->d_sunits, sunits.data(), sunits.size() * sizeof(WorkUnit),
+                                         hipMemcpyHostToDevice, e->stream),
+                       "upload sparse units");
+            e->lds_path = LdsPath::Sparse;
+        }
     }
     e->n_tiles = (int32_t)n_tiles;
     e->n_sims = (int32_t)sims.size();

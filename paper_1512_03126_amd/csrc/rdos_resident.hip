@@ -13,7 +13,8 @@
 //     of 93 molecules: 64, 33, 27, 23.5 us per period with 1, 8, 34 and 68
 //     blocks), sparse ones hardly lose (the 750-tet cube 6.0 us with one
 //     block, 6.5 with 47; 384,000 tets at 2% occupancy 10.2 us with 128
-//     blocks, 9.4 with 256).  Realizations beyond that run one block each.
+//     blocks, 9.4 with 256).  Realizations beyond that run one block each,
+//     up to eight on a compute unit.
 //   * Exchange.  Arrivals from other blocks are added to the realization's
 //     own count buffer of the next period (all zero until then) by agent-scope
 //     atomics; a block publishes the period it has finished, waits for the
@@ -37,11 +38,11 @@
 //     to the buffer of period k + 2 only after this block has published
 //     period k + 1, by when it has emptied that buffer of period k's arrivals.
 // Measured, us per period, two launches (or the queue-based one launch) and
-// this kernel: 750-tet cube 14.4 and 6.0; 1080-tet bar at 93 molecules per
-// tet 41.5 and 23.5; ten species on that bar 105 and 22.4; 1000 realizations
-// of the cube with production 33 and 18; 384,000 tets at 2% 14.8 and 8.6, with
-// a fourth species and jitter 20.3 and 11.4; 162,000 tets at 30 molecules per
-// species and tet 292 and 105.  Short layout: 998,250 tets of four species at
+// this kernel: 750-tet cube 14.4 and 5.2; 1080-tet bar at 93 molecules per
+// tet 41.5 and 23.4; ten species on that bar 105 and 21.8; 600 realizations of
+// the cube with production 26 and 8.4; 384,000 tets at 2% 14.8 and 8.5, with a
+// fourth species and jitter 20.3 and 11.3; 162,000 tets at 30 molecules per
+// species and tet 292 and 104.  Short layout: 998,250 tets of four species at
 // 0.03 and 0.1 molecules per tet 23.3 and 15.5, 43.9 and 24.7; 16 realizations
 // of 80,400 triangles 28 and 14.2.
 #include <hip/hip_runtime.h>
