@@ -767,26 +767,75 @@ int32_t persist_grid(rdos_sim *s)
     return s->persist_limit > 0 ? std::min(need, s->persist_limit) : 0;
 }
 
+// Launches with several blocks per realization are cooperative, and the
+// device runs one at a time.  A caller whose stream follows the last one's, or
+// finds it finished, launches; another waits for it (`wait`) or is told so
+// (hipErrorNotReady): a simulation stepped meanwhile from another thread runs
+// these periods over the queue, beside the other's kernel.
+hipError_t launch_resident_in_turn(int device, const DevSim *sims, const ResidentPlan &plan, int64_t iter0,
+                                   int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
+                                   hipStream_t st, bool wait)
+{
+    if (plan.max_parts <= 1)
+        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, st);
+    struct Turn {
+        hipEvent_t done = nullptr;
+        hipStream_t stream = nullptr;
+    };
+    static std::map<int, Turn> turns;  // guarded by device_api_mutex()
+    for (;;) {
+        hipEvent_t busy;
+        {
+            std::lock_guard<std::mutex> g(device_api_mutex());
+            Turn &t = turns[device];
+            hipError_t e = hipSuccess;
+            if (!t.done) {
+                e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
+                if (e != hipSuccess) {
+                    t.done = nullptr;
+                    return e;
+                }
+                t.stream = st;
+            }
+            if (t.stream != st) e = hipEventQuery(t.done);
+            if (e == hipSuccess) {
+                e = launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, st);
+                if (e == hipSuccess) e = hipEventRecord(t.done, st);
+                t.stream = st;
+                return e;
+            }
+            (void)hipGetLastError();
+            if (e != hipErrorNotReady || !wait) return e;
+            busy = t.done;
+        }
+        const hipError_t e = hipEventSynchronize(busy);
+        if (e != hipSuccess) return e;
+    }
+}
+
 // n periods from the current one; the last lasts tau_last when `partial`
 // (Algorithm 1, Step 1), all others tau.
 rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
 {
     if (n <= 0) return RDOS_OK;
+    bool beside = false;  // another simulation's cooperative launch
     if (const ResidentPlan *plan = resident_for(s, n)) {
         const int64_t partial_index = partial ? s->step + n - 1 : -1;
-        s->mask_dirty = false;  // the kernel reads the counts and writes the occupancy bytes
         while (n > 0) {
             const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
-            HIP_TRY(s, launch_resident(s->d_desc, *plan, s->step, len, partial_index, tau_last, s->resident_epoch,
-                                       s->stream),
-                    "launch periods");
+            const hipError_t e = launch_resident_in_turn(s->device, s->d_desc, *plan, s->step, len, partial_index,
+                                                         tau_last, s->resident_epoch, s->stream, false);
+            beside = e == hipErrorNotReady;
+            if (beside) break;
+            HIP_TRY(s, e, "launch periods");
+            s->mask_dirty = false;  // the kernel reads the counts and writes the occupancy bytes
             s->resident_epoch += len;
             s->step += len;
             n -= len;
         }
-        return RDOS_OK;
+        if (n <= 0) return RDOS_OK;
     }
-    const int32_t grid = persist_grid(s);
+    const int32_t grid = beside ? 0 : persist_grid(s);
     if (grid <= 0) {
         for (int64_t i = 0; i < n; ++i) {
             const bool last = partial && i == n - 1;

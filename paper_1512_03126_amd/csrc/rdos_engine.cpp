@@ -872,7 +872,8 @@ void worker_main(rdos_engine *e)
         hipError_t err = hipEventRecord(e->ev0, e->stream);
         if (err == hipSuccess) {
             if (lds == LdsPath::Resident) {
-                err = launch_resident(e->d_sims, e->resident, 0, len, -1, 0.0, e->resident_epoch, e->stream);
+                err = launch_resident_in_turn(e->device, e->d_sims, e->resident, 0, len, -1, 0.0, e->resident_epoch,
+                                              e->stream, true);
                 e->resident_epoch += len;
                 if (err == hipSuccess) err = launch_advance(e->d_sims, e->queue.hdr, len, e->stream);
             } else if (lds == LdsPath::Sparse) {

@@ -106,6 +106,10 @@ bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c);
 // they do not fit, or (light false) are light and would not share one.
 bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int32_t cus, bool light,
                       rdos::ResidentPlan *plan);
+// launch_resident, one at a time on the device where blocks wait for each other.
+hipError_t launch_resident_in_turn(int device, const rdos::DevSim *sims, const rdos::ResidentPlan &plan, int64_t iter0,
+                                   int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
+                                   hipStream_t st, bool wait);
 // Compute units of a device (0 when it cannot be asked).
 int32_t compute_units(int device);
 rdos_status match_parity(rdos_sim *s);
