@@ -310,7 +310,10 @@ bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int
         if (!fits) continue;
         plan->threads = std::min(threads, widest);
         plan->lds_bytes = lds;
-        plan->full = full;
+        plan->full = plan->every = full;
+        for (size_t i = 0; i < n_sims; ++i)
+            plan->every &= resident_every((int32_t)sims[i]->D.size(), (int32_t)sims[i]->rx.size(),
+                                          (sims[i]->T + 3) & ~3, plan->threads);
         return true;
     }
     return false;
@@ -351,6 +354,7 @@ static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan
     p.threads = c.threads;
     p.lds_bytes = c.lds_bytes;
     p.full = c.full;
+    p.every = c.full && resident_every((int32_t)s->D.size(), (int32_t)s->rx.size(), (c.len + 3) & ~3, c.threads);
     p.scaled = s->transfer_form == 1;
     void *memory = nullptr;
     {

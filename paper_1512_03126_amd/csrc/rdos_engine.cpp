@@ -321,6 +321,11 @@ bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, Reside
         plan.lds_bytes = std::max(plan.lds_bytes, resident_lds_bytes((int32_t)s->D.size(), (int32_t)s->rx.size(), rows,
                                                                      true, rows, plan.threads));
     }
+    plan.every = plan.full;
+    for (const ResidentUnit &u : units) {
+        const rdos_sim *s = sims[u.sim].s;
+        plan.every &= resident_every((int32_t)s->D.size(), (int32_t)s->rx.size(), (u.len + 3) & ~3, plan.threads);
+    }
     plan.lds_bytes = plan.full ? std::min(plan.lds_bytes, kResidentLdsMax) : kResidentLdsMax;
     return true;
 }

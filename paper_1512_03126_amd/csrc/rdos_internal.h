@@ -243,6 +243,7 @@ struct ResidentPlan {
     int32_t threads;
     int32_t lds_bytes;
     int32_t full;               // layout
+    int32_t every;              // no reactions, full, and a lane for every pair of a block
     int32_t scaled;             // some simulation uses transfer form 1
 };
 constexpr int kResidentMaxThreads = 1024;
@@ -285,6 +286,10 @@ __host__ __device__ inline int32_t resident_range(int32_t S, int32_t R, int32_t 
     if (left < 16) return least;
     const int32_t range = least + ((left - 15) / (6 * S + (R > 0 ? 4 * S + 2 : 0)) & ~3);
     return range < ls ? range : ls;
+}
+__host__ __device__ inline bool resident_every(int32_t S, int32_t R, int32_t ls, int32_t threads)
+{
+    return R == 0 && S * ls <= threads;
 }
 // Device memory of a plan, and its arrays' places in it (16-byte aligned).
 size_t resident_plan_bytes(int64_t blocks, int64_t max_parts);

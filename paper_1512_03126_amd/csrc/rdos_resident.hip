@@ -30,6 +30,9 @@
 //     tets, and slower where both fit (384,000 tets at 2%: full 8.7, short 9.4
 //     us per period).  A period whose pairs overflow short lists is
 //     worked through in parts, every addition through memory.
+//   * Diffusion alone, in blocks with a lane for every pair (EVERY): nothing is
+//     listed, an empty pair's lane idles.  The 750-tet cube 5.2 and 4.7 us per
+//     period with the list and without, a bar of 192 tets 3.9 and 3.2.
 //   * The list pass is bound by its instructions on large blocks (a wavefront
 //     takes 256 tets): a group's occupancy is one word with four bits per
 //     species, which a reaction tests for four tets at once (5,000 tets of
@@ -38,8 +41,8 @@
 //     to the buffer of period k + 2 only after this block has published
 //     period k + 1, by when it has emptied that buffer of period k's arrivals.
 // Measured, us per period, two launches (or the queue-based one launch) and
-// this kernel: 750-tet cube 14.4 and 5.2; 1080-tet bar at 93 molecules per
-// tet 41.5 and 23.4; ten species on that bar 105 and 21.8; 600 realizations of
+// this kernel: 750-tet cube 14.4 and 4.7; 1080-tet bar at 93 molecules per
+// tet 41.5 and 22.9; ten species on that bar 105 and 21.8; 600 realizations of
 // the cube with production 26 and 8.4; 384,000 tets at 2% 14.8 and 8.5, with a
 // fourth species and jitter 20.3 and 11.3; 162,000 tets at 30 molecules per
 // species and tet 292 and 104.  Short layout: 998,250 tets of four species at
@@ -225,7 +228,7 @@ void resident_place(ResidentPlan *plan, void *memory)
 
 // n_periods periods of the block's part (parts[blockIdx.x]) of one
 // realization, the iterations iter0 .. of its simulation.
-template <bool ANY_SCALED, bool FULL>
+template <bool ANY_SCALED, bool FULL, bool EVERY>
 __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
     const DevSim *__restrict__ sims, const ResidentPart *__restrict__ parts,
     const uint16_t *__restrict__ neighbours, int32_t max_parts, int64_t iter0, int32_t n_periods, int64_t partial,
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
             // the (tet, species) pairs that hold molecules in the others.  A
             // lane takes the four tets of a group, every species (one 16-byte
             // LDS load each).
-            for (int32_t i0 = from; i0 < to; i0 += 4 * nt) {
+            for (int32_t i0 = from; i0 < to && !EVERY; i0 += 4 * nt) {
                 const int32_t i = i0 + 4 * tid;
                 uint64_t held = 0;  // bit 4 s + b: species s in tet i + b
                 if (i < to) {
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
                     if (S > 8) put((uint32_t)(held >> 32), 8);
                 }
             }
-            __syncthreads();
+            if (!EVERY) __syncthreads();
             int32_t n_ssa = head.n_ssa;
             if (!FULL && to - from > range) {
                 // over the whole range with short lists: where the pairs may
@@ -451,7 +454,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
             // Step 3: one lane per pair.  Short layout: the counts of listed
             // pairs are taken out first (the first nt stay in registers), so
             // that what moves or stays is added to the same array.
-            const int32_t n_pairs = head.n_pairs;
+            const int32_t n_pairs = EVERY ? P : head.n_pairs;
             uint32_t first_raw = 0;
             if (!FULL && !spill) {
                 for (int32_t j = tid; j < n_pairs; j += nt) {
@@ -465,13 +468,17 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
                 __syncthreads();
             }
             for (int32_t j = tid; j < n_pairs; j += nt) {
-                const uint32_t e = list[j];
+                const uint32_t e = EVERY ? (uint32_t)j : list[j];
                 const int32_t s = (int32_t)__umulhi(e, per_species);
                 const int32_t t = t0 + (int32_t)e - s * ls;
                 uint32_t raw;
                 if (FULL) {
                     raw = (uint32_t)cur[e];
                     cur[e] = 0;
+                    if (EVERY && (int32_t)raw < 0) {  // as in the scan
+                        atomicOr(sm.flags, 1);
+                        raw = 0;
+                    }
                 } else {
                     raw = spill ? (uint32_t)cur[e] : j < nt ? first_raw : (uint32_t)taken[j];
                 }
@@ -602,12 +609,15 @@ hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t
         plan.lds_bytes > kResidentLdsMax)
         return hipErrorInvalidValue;
     const void *fn;
-    if (plan.full)
-        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, true>)
-                         : reinterpret_cast<const void *>(&resident_kernel<false, true>);
+    if (plan.full && plan.every)
+        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, true, true>)
+                         : reinterpret_cast<const void *>(&resident_kernel<false, true, true>);
+    else if (plan.full)
+        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, true, false>)
+                         : reinterpret_cast<const void *>(&resident_kernel<false, true, false>);
     else
-        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, false>)
-                         : reinterpret_cast<const void *>(&resident_kernel<false, false>);
+        fn = plan.scaled ? reinterpret_cast<const void *>(&resident_kernel<true, false, false>)
+                         : reinterpret_cast<const void *>(&resident_kernel<false, false, false>);
     uint32_t *fail = reinterpret_cast<uint32_t *>(plan.done + (int64_t)plan.blocks * kResidentFlagStride);
     const uint16_t *neighbours = plan.neighbours;
     int32_t max_parts = plan.max_parts;

@@ -81,7 +81,13 @@ def check(g, refs, what):
     ((1, 1, 1), 1, 0, 1, 3.0),      # 6 tets: one block of less than a wavefront
     ((1, 1, 3), 2, 2, 1, 3.0),      # 18 tets: a second block of 2 tets
     ((2, 2, 2), 3, 3, 1, 2.0),      # 48 tets: three full blocks
-    ((5, 5, 5), 1, 0, 1, 0.5),      # 750 tets, light: one block
+    ((5, 5, 5), 1, 0, 1, 0.5),      # 750 tets, light: one block, a lane for every pair
+    ((5, 5, 6), 3, 0, 1, 0.4),      # diffusion of three species, 2700 pairs: several blocks, a lane for every pair
+    ((13, 13, 13), 4, 0, 2, 0.1),   # 13,182 tets in 128 blocks each: 448 pairs in a block
+    ((11, 11, 11), 3, 0, 60, 0.1),  # 7986 tets in four blocks each: more pairs than lanes, listed
+    ((4, 4, 4), 2, 0, 300, 0.3),    # two blocks on a compute unit: 768 pairs, 512 lanes, listed
+    ((3, 3, 3), 2, 0, 600, 0.3),    # four: 324 pairs, 256 lanes, listed
+    ((3, 3, 2), 2, 0, 600, 0.3),    # four: 216 pairs, a lane for every pair
     ((5, 5, 5), 1, 2, 1, 60.0),     # the same, crowded: 47 blocks, rejection sampler
     ((5, 5, 5), 2, 4, 100, 0.2),    # two blocks per realization
     ((3, 3, 3), 2, 4, 300, 0.5),    # more realizations than compute units: two blocks share one
