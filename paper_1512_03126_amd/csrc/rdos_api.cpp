@@ -12,11 +12,13 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
 #include "rdos_internal.h"
 #include "rdos_sim.h"
+#include "rdos_turn.h"
 
 using namespace rdos;
 
@@ -771,50 +773,79 @@ int32_t persist_grid(rdos_sim *s)
     return s->persist_limit > 0 ? std::min(need, s->persist_limit) : 0;
 }
 
-// Launches with several blocks per realization are cooperative, and the
-// device runs one at a time.  A caller whose stream follows the last one's, or
-// finds it finished, launches; another waits for it (`wait`) or is told so
-// (hipErrorNotReady): a simulation stepped meanwhile from another thread runs
-// these periods over the queue, beside the other's kernel.
-hipError_t launch_resident_in_turn(int device, const DevSim *sims, const ResidentPlan &plan, int64_t iter0,
-                                   int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
-                                   hipStream_t st, bool wait)
+// The turns of the process's devices.  The books and the words that kernels
+// write stay until the process ends (a simulation destroyed at its exit finds
+// them); a device's word is made with its first finalized simulation or engine.
+namespace {
+constexpr int kTurnDevices = 64;
+struct Turns {
+    LaunchTurn turn[kTurnDevices];
+    unsigned long long *ended[kTurnDevices] = {};  // pinned host memory
+    StreamOwners owners;
+};
+Turns &turns()  // guarded by device_api_mutex()
+{
+    alignas(Turns) static unsigned char room[sizeof(Turns)];
+    static Turns &t = *new (room) Turns;
+    return t;
+}
+}  // namespace
+
+void prepare_turns(int device)
+{
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    Turns &t = turns();
+    if (device < 0 || device >= kTurnDevices || t.ended[device]) return;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(unsigned long long), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();  // without a word nobody has a turn, and the queue runs the periods
+        return;
+    }
+    t.ended[device] = static_cast<unsigned long long *>(p);
+    *t.ended[device] = 0;
+}
+
+uint64_t own_stream_owner()
+{
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    return turns().owners.own_stream();
+}
+
+// The simulation's number as an owner of turns, when it gets its stream, and
+// before it gives the stream up (drained).  The per-thread stream is another
+// one in every thread.
+static void join_stream(rdos_sim *s)
+{
+    if (s->own_stream || s->stream == hipStreamPerThread) {
+        s->turn_owner = own_stream_owner();
+        return;
+    }
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    s->turn_owner = turns().owners.join(s->stream);
+}
+static void leave_stream(rdos_sim *s)
+{
+    if (!s->stream || s->own_stream || s->stream == hipStreamPerThread) return;
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    turns().owners.leave(s->stream);
+}
+
+hipError_t launch_resident_in_turn(int device, uint64_t owner, const DevSim *sims, const ResidentPlan &plan,
+                                   int64_t iter0, int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
+                                   hipStream_t st)
 {
     if (plan.max_parts <= 1)
-        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, st);
-    struct Turn {
-        hipEvent_t done = nullptr;
-        hipStream_t stream = nullptr;
-    };
-    static std::map<int, Turn> turns;  // guarded by device_api_mutex()
-    for (;;) {
-        hipEvent_t busy;
-        {
-            std::lock_guard<std::mutex> g(device_api_mutex());
-            Turn &t = turns[device];
-            hipError_t e = hipSuccess;
-            if (!t.done) {
-                e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
-                if (e != hipSuccess) {
-                    t.done = nullptr;
-                    return e;
-                }
-                t.stream = st;
-            }
-            if (t.stream != st) e = hipEventQuery(t.done);
-            if (e == hipSuccess) {
-                e = launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, st);
-                if (e == hipSuccess) e = hipEventRecord(t.done, st);
-                t.stream = st;
-                return e;
-            }
-            (void)hipGetLastError();
-            if (e != hipErrorNotReady || !wait) return e;
-            busy = t.done;
-        }
-        const hipError_t e = hipEventSynchronize(busy);
-        if (e != hipSuccess) return e;
-    }
+        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, LaunchEnd{}, st);
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    Turns &t = turns();
+    if (device < 0 || device >= kTurnDevices || !t.ended[device]) return hipErrorNotReady;
+    LaunchEnd end;
+    end.word = t.ended[device];
+    end.number = t.turn[device].take(owner, __atomic_load_n(end.word, __ATOMIC_RELAXED));
+    if (end.number == 0) return hipErrorNotReady;
+    const hipError_t e = launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, end, st);
+    if (e != hipSuccess) t.turn[device].give_back();
+    return e;
 }
 
 // n periods from the current one; the last lasts tau_last when `partial`
@@ -827,8 +858,8 @@ rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
         const int64_t partial_index = partial ? s->step + n - 1 : -1;
         while (n > 0) {
             const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
-            const hipError_t e = launch_resident_in_turn(s->device, s->d_desc, *plan, s->step, len, partial_index,
-                                                         tau_last, s->resident_epoch, s->stream, false);
+            const hipError_t e = launch_resident_in_turn(s->device, s->turn_owner, s->d_desc, *plan, s->step, len,
+                                                         partial_index, tau_last, s->resident_epoch, s->stream);
             beside = e == hipErrorNotReady;
             if (beside) break;
             HIP_TRY(s, e, "launch periods");
@@ -873,6 +904,7 @@ void free_device(rdos_sim *s)
 {
     (void)hipSetDevice(s->device);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
+    leave_stream(s);
     std::lock_guard<std::mutex> g(device_api_mutex());
     void *ptrs[] = {s->d_mesh,           s->d_state, s->d_desc, s->d_tiles, s->d_allowed, s->resident_one.done,
                     s->resident_many.done};
@@ -1055,6 +1087,7 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
     if (!s->stream) {
         HIP_TRY(s, hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking), "create stream");
         s->own_stream = true;
+        join_stream(s);
     }
     // Face matching (step a0): the cached table of this connectivity, else
     // matching on the device in the set-up buffers below, else on the host.
@@ -1294,6 +1327,7 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
     hipError_t e = launch_own_work(d, s->d_desc, queue_header(&s->queue, s->n_tiles, 1, 0), s->queue.hdr, s->d_tiles,
                                    s->stream);
     if (e != hipSuccess) st = hip_fail(s, e, "work list");
+    prepare_turns(s->device);
     if (st == RDOS_OK) st = plan_resident(s, cut_one(s), &s->resident_one);
     if (st == RDOS_OK) st = plan_resident(s, cut_many(s), &s->resident_many);
     if (st != RDOS_OK) {
@@ -1472,13 +1506,17 @@ rdos_status rdos_set_stream(rdos_sim *s, void *hip_stream)
     CHECK_HANDLE(s);
     HIP_TRY(s, hipSetDevice(s->device), "set device");
     if (s->stream) HIP_TRY(s, hipStreamSynchronize(s->stream), "drain old stream");
+    leave_stream(s);
     if (s->stream && s->own_stream) (void)hipStreamDestroy(s->stream);
+    s->stream = nullptr;
     if (hip_stream) {
         s->stream = (hipStream_t)hip_stream;
         s->own_stream = false;
+        join_stream(s);
     } else if (s->state == SimState::Ready) {
         HIP_TRY(s, hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking), "create stream");
         s->own_stream = true;
+        join_stream(s);
     } else {
         s->stream = nullptr;
         s->own_stream = false;

@@ -152,6 +152,7 @@ struct rdos_engine {
     int64_t cap_sparse = 0;
     uint32_t *h_fail = nullptr;    // pinned copy of the failure word
     uint64_t resident_epoch = 0;
+    uint64_t turn_owner = 0;
     double lds_period_ms = 0.0;    // device time per period of the last run on such a path
     int32_t qphase = 0;            // queue half (qsel) of the next period; graphs start at 0
     bool graph_stale = true;  // a buffer the graphs name was reallocated
@@ -712,6 +713,7 @@ void worker_main(rdos_engine *e)
 {
     (void)hipSetDevice(e->device);
     std::unique_lock<std::mutex> lk(e->mu);
+    bool beside = false;  // another owner's launch took the device when the last chunk was to have its state in LDS
     while (!e->stop) {
         if (e->held) {  // rdos_engine_hold: admissions go on, no chunk starts
             e->cv_work.wait(lk);
@@ -812,7 +814,8 @@ void worker_main(rdos_engine *e)
         // chunk, or some milliseconds of device time: the sparse kernel's
         // runs are the longer ones, since each reads the state from memory and
         // writes it back.
-        const LdsPath lds = !timed && !tuning && !e->fixed_shape ? e->lds_path : LdsPath::None;
+        const LdsPath lds = !timed && !tuning && !e->fixed_shape && !beside ? e->lds_path : LdsPath::None;
+        beside = false;
         if (lds != LdsPath::None) {
             replay = false;
             const bool pending = !e->ready.empty() || !e->waiting.empty() || e->admitting > 0;
@@ -877,8 +880,13 @@ void worker_main(rdos_engine *e)
         hipError_t err = hipEventRecord(e->ev0, e->stream);
         if (err == hipSuccess) {
             if (lds == LdsPath::Resident) {
-                err = launch_resident_in_turn(e->device, e->d_sims, e->resident, 0, len, -1, 0.0, e->resident_epoch,
-                                              e->stream, true);
+                err = launch_resident_in_turn(e->device, e->turn_owner, e->d_sims, e->resident, 0, len, -1, 0.0,
+                                              e->resident_epoch, e->stream);
+                if (err == hipErrorNotReady) {  // the next chunk runs over the queue, then this path is tried again
+                    beside = true;
+                    lk.lock();
+                    continue;
+                }
                 e->resident_epoch += len;
                 if (err == hipSuccess) err = launch_advance(e->d_sims, e->queue.hdr, len, e->stream);
             } else if (lds == LdsPath::Sparse) {
@@ -1009,6 +1017,8 @@ rdos_status rdos_engine_create(rdos_engine **out, int device, size_t hbm_budget_
         delete e;
         return RDOS_EDEVICE;
     }
+    prepare_turns(device);
+    e->turn_owner = own_stream_owner();
     // Two-launch shapes only: the fused shape (update_bps 0) lost to them on every tuned size measured,
     // and under a profiler, which taxes each launch, it scored first; it stays available by set_shape.
     // One 32-period shape: fewer graph launches per period, at the cost of a longer wait to join.

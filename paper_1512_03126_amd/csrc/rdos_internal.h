@@ -211,6 +211,12 @@ int32_t persist_grid_limit(const QueueView &q);
 hipError_t launch_persist(const DevSim *sims, const Tile *tiles, int64_t iter0, int32_t n_periods, int32_t phase,
                           int64_t partial, double tau_last, const QueueView &q, int32_t grid, uint32_t *sync,
                           hipStream_t st);
+// Where a launch whose blocks wait for each other says that it has ended: its
+// last block writes `number` to *word (host memory; null: nobody asks).
+struct LaunchEnd {
+    unsigned long long *word = nullptr;
+    unsigned long long number = 0;
+};
 // State held in LDS (rdos_resident.hip).  A realization is cut into `parts`
 // ranges of consecutive tets, one block each; a block keeps its range's
 // counts in LDS for a whole run of periods.
@@ -235,7 +241,7 @@ struct ResidentUnit {
 };
 struct ResidentPlan {
     unsigned long long *done;   // [blocks][kResidentFlagStride] last period finished by each block, then the
-                                // failure word (device)
+                                // failure word and the number of blocks that have ended (device)
     ResidentPart *parts;        // [blocks] (device)
     uint16_t *neighbours;       // [blocks][max_parts] (device; max_parts > 1)
     int32_t blocks;
@@ -303,7 +309,8 @@ hipError_t launch_resident_layout(const DevSim *sims, const ResidentPlan &plan, 
 // (the period equal to `partial` lasts tau_last).  `epoch` is at least every
 // value in plan.done; the launch raises them to at most epoch + n_periods.
 hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t iter0, int32_t n_periods,
-                           int64_t partial, double tau_last, unsigned long long epoch, hipStream_t st);
+                           int64_t partial, double tau_last, unsigned long long epoch, const LaunchEnd &end,
+                           hipStream_t st);
 // Batches of sparse realizations (rdos_sparse.hip): one block per unit of the
 // work list keeps its occupied (tet, species) pairs in a hash table in LDS.
 struct SparsePlan {

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void resident_layout_kernel(const DevSim *__re
         pt.neighbours = n;
         plan.parts[b] = pt;
         plan.done[(int64_t)b * kResidentFlagStride] = 0;
-        if (b == 0) plan.done[(int64_t)plan.blocks * kResidentFlagStride] = 0;
+        if (b == 0) plan.done[(int64_t)plan.blocks * kResidentFlagStride] = 0;  // both words
     }
 }
 
@@ -232,7 +232,8 @@ template <bool ANY_SCALED, bool FULL, bool EVERY>
 __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
     const DevSim *__restrict__ sims, const ResidentPart *__restrict__ parts,
     const uint16_t *__restrict__ neighbours, int32_t max_parts, int64_t iter0, int32_t n_periods, int64_t partial,
-    double tau_last, unsigned long long *done_all, unsigned long long epoch, uint32_t *fail, int32_t lds_bytes)
+    double tau_last, unsigned long long *done_all, unsigned long long epoch, uint32_t *fail, int32_t lds_bytes,
+    LaunchEnd launch_end)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     ResidentHead &head = *reinterpret_cast<ResidentHead *>(lds);
@@ -244,7 +245,10 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
     const int32_t S = sm.S, R = sm.R;
     const int64_t first = sm.step0 + iter0;
     const int64_t left = sm.step_end - first;
-    if (left <= 0) return;  // uniform over the unit's blocks
+    if (left <= 0) {  // uniform over the unit's blocks
+        end_block(fail + 1, launch_end);
+        return;
+    }
     if (left < n_periods) n_periods = (int32_t)left;
 
     const int32_t len = pt.len, t0 = pt.t0;
@@ -599,10 +603,12 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         if (alone && FULL && (n_periods & 1)) *(gptr<v4i>)(other + s * Tp + i) = v4i{0, 0, 0, 0};
     }
     if (head.stop && tid == 0) atomicOr(sm.flags, 8);
+    end_block(fail + 1, launch_end);
 }
 
 hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t iter0, int32_t n_periods,
-                           int64_t partial, double tau_last, unsigned long long epoch, hipStream_t st)
+                           int64_t partial, double tau_last, unsigned long long epoch, const LaunchEnd &end,
+                           hipStream_t st)
 {
     if (n_periods <= 0) return hipSuccess;
     if (plan.blocks < 1 || plan.threads < 64 || plan.threads > kResidentMaxThreads ||
@@ -626,7 +632,8 @@ hipError_t launch_resident(const DevSim *sims, const ResidentPlan &plan, int64_t
     int32_t lds = plan.lds_bytes;
     void *args[] = {(void *)&sims,      (void *)&parts,   (void *)&neighbours, (void *)&max_parts,
                     (void *)&iter0,     (void *)&n_periods, (void *)&partial,  (void *)&tau_last,
-                    (void *)&done,      (void *)&epoch,   (void *)&fail,       (void *)&lds};
+                    (void *)&done,      (void *)&epoch,   (void *)&fail,       (void *)&lds,
+                    (void *)&end};
     if (plan.max_parts > 1)
         return hipLaunchCooperativeKernel(fn, dim3(plan.blocks), dim3(plan.threads), args, (unsigned)lds, st);
     return hipLaunchKernel(fn, dim3(plan.blocks), dim3(plan.threads), args, (size_t)lds, st);

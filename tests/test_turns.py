@@ -1,0 +1,26 @@
+"""The books that let one owner at a time launch kernels whose blocks wait for
+each other: who is refused, until when, and who counts as one owner (CPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1512_03126_amd", "csrc")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_turns_and_owners(tmp_path):
+    exe = str(tmp_path / "turns")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-Werror", "-fsanitize=address,undefined", "-I", CSRC,
+                    os.path.join(HERE, "helpers", "turn_driver.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_no_stream_or_event_is_asked_whose_turn_it_is():
+    """A launch in turn looks at its own books and at a word of host memory:
+    the stream of the last launch may be gone, or be captured by its owner."""
+    src = open(os.path.join(CSRC, "rdos_api.cpp")).read()
+    assert "hipEvent" not in src
