@@ -228,9 +228,11 @@ rdos_status rdos_step_static(rdos_sim *s, int64_t n_steps);
  * occupied-tet queue, the scan and update phases of each period separated by
  * grid-wide barriers, and larger ones launch a scan and an update kernel per
  * period.  1: always two launches per period.  2: always one cooperative
- * launch over the queue.  3: one fused launch per period (each wavefront
- * scans its tiles and updates the tets it queued, no queue in device memory;
- * simulations of more than 8 species launch two kernels instead).
+ * launch over the queue.  In modes 0 and 2, a launch whose blocks wait for
+ * each other gives way to two launches per period while one of another
+ * stream's is under way on the device.  3: one fused launch per period (each
+ * wavefront scans its tiles and updates the tets it queued, no queue in device
+ * memory; simulations of more than 8 species launch two kernels instead).
  * RDOS_EINVAL for other values. */
 rdos_status rdos_set_launch_mode(rdos_sim *s, int32_t mode);
 

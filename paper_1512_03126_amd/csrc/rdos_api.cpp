@@ -374,6 +374,12 @@ static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan
     return RDOS_OK;
 }
 
+static bool capturing(const rdos_sim *s)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+}
+
 // The resident launch for n periods, or null: the two-launch (or one-launch)
 // path.  Several blocks per realization, unless one does as well: light
 // tets (on average two molecules per pair or fewer, by the counts last set)
@@ -385,9 +391,7 @@ static rdos_status plan_resident(rdos_sim *s, const ResidentCut &c, ResidentPlan
 static const ResidentPlan *resident_for(rdos_sim *s, int64_t n)
 {
     if (s->launch_mode != 0) return nullptr;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
-        return nullptr;  // the period counters of a replay would start over
+    if (capturing(s)) return nullptr;  // the period counters of a replay would start over
     const ResidentPlan *one = s->resident_one.blocks ? &s->resident_one : nullptr;
     const ResidentPlan *many = s->resident_many.blocks ? &s->resident_many : nullptr;
     const int32_t cus = compute_units(s->device);
@@ -830,12 +834,10 @@ static void leave_stream(rdos_sim *s)
     turns().owners.leave(s->stream);
 }
 
-hipError_t launch_resident_in_turn(int device, uint64_t owner, const DevSim *sims, const ResidentPlan &plan,
-                                   int64_t iter0, int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
-                                   hipStream_t st)
+// Runs `launch` with the LaunchEnd of the owner's next turn.
+template <class Launch>
+static hipError_t launch_in_turn(int device, uint64_t owner, Launch launch)
 {
-    if (plan.max_parts <= 1)
-        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, LaunchEnd{}, st);
     std::lock_guard<std::mutex> g(device_api_mutex());
     Turns &t = turns();
     if (device < 0 || device >= kTurnDevices || !t.ended[device]) return hipErrorNotReady;
@@ -843,9 +845,31 @@ hipError_t launch_resident_in_turn(int device, uint64_t owner, const DevSim *sim
     end.word = t.ended[device];
     end.number = t.turn[device].take(owner, __atomic_load_n(end.word, __ATOMIC_RELAXED));
     if (end.number == 0) return hipErrorNotReady;
-    const hipError_t e = launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, end, st);
+    const hipError_t e = launch(end);
     if (e != hipSuccess) t.turn[device].give_back();
     return e;
+}
+
+hipError_t launch_resident_in_turn(int device, uint64_t owner, const DevSim *sims, const ResidentPlan &plan,
+                                   int64_t iter0, int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
+                                   hipStream_t st)
+{
+    if (plan.max_parts <= 1)
+        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, LaunchEnd{}, st);
+    return launch_in_turn(device, owner, [&](const LaunchEnd &end) {
+        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, end, st);
+    });
+}
+
+// len periods from the current one by the one-launch path over the queue.  A
+// captured launch runs when its owner replays it, out of turn.
+static hipError_t launch_persist_in_turn(rdos_sim *s, int32_t len, int64_t partial, double tau_last, int32_t grid)
+{
+    const auto launch = [&](const LaunchEnd &end) {
+        return launch_persist(s->d_desc, s->d_tiles, s->step, len, (int32_t)(s->launches & 1), partial, tau_last,
+                              s->queue, grid, s->queue.sync, end, s->stream);
+    };
+    return capturing(s) ? launch(LaunchEnd{}) : launch_in_turn(s->device, s->turn_owner, launch);
 }
 
 // n periods from the current one; the last lasts tau_last when `partial`
@@ -871,26 +895,25 @@ rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
         if (n <= 0) return RDOS_OK;
     }
     const int32_t grid = beside ? 0 : persist_grid(s);
-    if (grid <= 0) {
-        for (int64_t i = 0; i < n; ++i) {
-            const bool last = partial && i == n - 1;
-            rdos_status st = enqueue_period(s, s->step, last ? s->step : -1, last ? tau_last : 0.0);
-            if (st != RDOS_OK) return st;
-            s->step += 1;
+    if (grid > 0) {
+        const rdos_status st = ensure_mask(s);
+        if (st != RDOS_OK) return st;
+        const int64_t partial_index = partial ? s->step + n - 1 : -1;
+        while (n > 0) {
+            const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
+            const hipError_t e = launch_persist_in_turn(s, len, partial_index, tau_last, grid);
+            if (e == hipErrorNotReady) break;
+            HIP_TRY(s, e, "launch periods");
+            s->launches += len;
+            s->step += len;
+            n -= len;
         }
-        return RDOS_OK;
     }
-    rdos_status st = ensure_mask(s);
-    if (st != RDOS_OK) return st;
-    const int64_t partial_index = partial ? s->step + n - 1 : -1;
-    while (n > 0) {
-        const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
-        HIP_TRY(s, launch_persist(s->d_desc, s->d_tiles, s->step, len, (int32_t)(s->launches & 1), partial_index,
-                                  tau_last, s->queue, grid, s->queue.sync, s->stream),
-                "launch periods");
-        s->launches += len;
-        s->step += len;
-        n -= len;
+    for (int64_t i = 0; i < n; ++i) {
+        const bool last = partial && i == n - 1;
+        const rdos_status st = enqueue_period(s, s->step, last ? s->step : -1, last ? tau_last : 0.0);
+        if (st != RDOS_OK) return st;
+        s->step += 1;
     }
     return RDOS_OK;
 }

@@ -178,15 +178,4 @@ __device__ __forceinline__ int32_t reserve(int32_t *count, int32_t total)
     return __builtin_amdgcn_readfirstlane(base);
 }
 
-// A block's end (every thread of it): the launch's last one says so on the
-// host.  `ended` counts blocks, and is 0 between launches.
-__device__ __forceinline__ void end_block(uint32_t *ended, const LaunchEnd &end)
-{
-    if (!end.word) return;
-    __syncthreads();
-    if (threadIdx.x != 0 || atomicAdd(ended, 1u) + 1u != gridDim.x) return;
-    __hip_atomic_store(ended, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(end.word, end.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 }  // namespace rdos

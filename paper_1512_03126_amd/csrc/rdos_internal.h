@@ -94,6 +94,23 @@ inline std::mutex &device_api_mutex()
     return m;
 }
 
+// Where a launch whose blocks wait for each other says that it has ended: its
+// last block writes `number` to *word (host memory; null: nobody asks).
+struct LaunchEnd {
+    unsigned long long *word = nullptr;
+    unsigned long long number = 0;
+};
+// A block's end (every thread of it): the launch's last one says so on the
+// host.  `ended` counts blocks, and is 0 between launches.
+__device__ __forceinline__ void end_block(uint32_t *ended, const LaunchEnd &end)
+{
+    if (!end.word) return;
+    __syncthreads();
+    if (threadIdx.x != 0 || atomicAdd(ended, 1u) + 1u != gridDim.x) return;
+    __hip_atomic_store(ended, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(end.word, end.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Kernel launchers (rdos_kernels.hip).
 hipError_t launch_geometry(const double *xyz, const int32_t *tet_verts, const int32_t *nbr,
                            int32_t T, double *scratch_vol, double *scratch_bc,
@@ -145,7 +162,7 @@ struct QueueView {
     int64_t qcap;       // allocated entries per count row
     int32_t species;    // allocated count rows
     int32_t scaled;     // some simulation of the work list uses transfer form 1 (picks the update kernel)
-    uint32_t *sync;     // [kPersistSyncWords] grid-barrier counters and failure word of the one-launch path
+    uint32_t *sync;     // [kPersistSyncWords] of the one-launch path: grid-barrier counters, failure word, blocks ended
     unsigned long long *work;  // null, or [3] device totals the update kernel adds to: tets, count additions,
                                // additions that are transfers across a face
     int32_t owned;      // the work lists launched on it have a segment per tile and a scan wavefront per
@@ -153,7 +170,7 @@ struct QueueView {
                         // own count (checked again on the device)
 };
 constexpr int kMaxSegments = 1024;
-constexpr int kPersistSyncWords = 64 * 32 + 32;  // 64 barrier counters on lines of their own, the failure word
+constexpr int kPersistSyncWords = 64 * 32 + 32;  // 64 barrier counters on lines of their own, then two words
 constexpr int kLenStride = 32;  // 128 bytes between segment lengths: no two share a line
 
 // Queue geometry for a work list of n_tiles tiles: tiles ti with
@@ -210,13 +227,7 @@ hipError_t launch_expand_tiles(const WorkUnit *units, int32_t n_units, int32_t n
 int32_t persist_grid_limit(const QueueView &q);
 hipError_t launch_persist(const DevSim *sims, const Tile *tiles, int64_t iter0, int32_t n_periods, int32_t phase,
                           int64_t partial, double tau_last, const QueueView &q, int32_t grid, uint32_t *sync,
-                          hipStream_t st);
-// Where a launch whose blocks wait for each other says that it has ended: its
-// last block writes `number` to *word (host memory; null: nobody asks).
-struct LaunchEnd {
-    unsigned long long *word = nullptr;
-    unsigned long long number = 0;
-};
+                          const LaunchEnd &end, hipStream_t st);
 // State held in LDS (rdos_resident.hip).  A realization is cut into `parts`
 // ranges of consecutive tets, one block each; a block keeps its range's
 // counts in LDS for a whole run of periods.

@@ -1251,12 +1251,13 @@ __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t nblocks, ui
 // equal to `partial` lasting tau_last).  Block b scans the tiles of its
 // wavefronts (grid-stride) and updates the queue segments b, b + grid, ...
 // sync holds the barrier counters (kBarrierLines lines, zero at launch) and,
-// after them, the failure word.  Each queue segment is shared by
-// max(1, grid / segments) blocks.
+// after them, the failure word and the number of blocks that have ended.
+// Each queue segment is shared by max(1, grid / segments) blocks.
 template <bool ANY_SCALED, int KS>
 __global__ __launch_bounds__(kBlock) void persist_kernel(const DevSim *__restrict__ sims, const Tile *__restrict__ tiles,
                                                          Queue q, int32_t phase, int64_t iter0, int32_t n_periods,
-                                                         int64_t partial, double tau_last, uint32_t *sync)
+                                                         int64_t partial, double tau_last, uint32_t *sync,
+                                                         LaunchEnd launch_end)
 {
     __shared__ int32_t glist[kScanWaves][kTileGroups];
     __shared__ int32_t stage[kScanWaves][stage_rows<KS>()][kTileGroups];
@@ -1293,6 +1294,7 @@ __global__ __launch_bounds__(kBlock) void persist_kernel(const DevSim *__restric
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
         for (int32_t i = 0; i < h.n_sims; ++i) atomicOr(sims[i].flags, 8);
+    end_block(fail + 1, launch_end);
 }
 
 __global__ void sync_reset_kernel(uint32_t *sync)
@@ -1328,7 +1330,7 @@ int32_t persist_grid_limit(const QueueView &qv)
 
 hipError_t launch_persist(const DevSim *sims, const Tile *tiles, int64_t iter0, int32_t n_periods, int32_t phase,
                           int64_t partial, double tau_last, const QueueView &qv, int32_t grid, uint32_t *sync,
-                          hipStream_t st)
+                          const LaunchEnd &end, hipStream_t st)
 {
     if (n_periods <= 0) return hipSuccess;
     if (grid < 1 || !sync) return hipErrorInvalidValue;
@@ -1337,7 +1339,7 @@ hipError_t launch_persist(const DevSim *sims, const Tile *tiles, int64_t iter0, 
     if (e != hipSuccess) return e;
     Queue q{qv.tet, qv.counts, qv.len, qv.hdr, nullptr, qv.species};
     void *args[] = {(void *)&sims, (void *)&tiles, (void *)&q, (void *)&phase, (void *)&iter0, (void *)&n_periods,
-                    (void *)&partial, (void *)&tau_last, (void *)&sync};
+                    (void *)&partial, (void *)&tau_last, (void *)&sync, (void *)&end};
     return hipLaunchCooperativeKernel(persist_pick(qv.species, qv.scaled), dim3(grid), dim3(kBlock), args, 0, st);
 }
 

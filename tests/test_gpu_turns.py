@@ -145,3 +145,25 @@ def test_beside_a_run_under_way(P, orc):
     P.rdos_engine_destroy(e)
     for g in (a, b, c):
         g.close()
+
+
+@pytest.mark.parametrize("modes", [(0, 2), (2, 0), (2, 2)])
+def test_one_launch_over_the_queue_takes_its_turn(P, orc, modes):
+    note(f"turns: launch mode {modes[1]} beside a long run in launch mode {modes[0]}")
+    (a, oa), (b, ob) = pair(P, orc, (2, 2, 4), 60), pair(P, orc, (4, 4, 4), 61)
+    P.rdos_set_launch_mode(a.h, modes[0])
+    P.rdos_set_launch_mode(b.h, modes[1])
+    a.step(7000)  # two launches
+    t_end = b.time()[0] + 60.4 * b.tau
+    b.run_until(t_end)
+    ob.run_until(t_end)
+    check(b, ob, "beside")
+    a.synchronize()
+    for n in (3, 2):  # and in turn again
+        b.step(n)
+        ob.run_steps(n)
+    check(b, ob, "after")
+    oa.run_steps(7000)
+    check(a, oa, "the long run")
+    a.close()
+    b.close()

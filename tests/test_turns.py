@@ -1,6 +1,7 @@
 """The books that let one owner at a time launch kernels whose blocks wait for
 each other: who is refused, until when, and who counts as one owner (CPU)."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -24,3 +25,23 @@ def test_no_stream_or_event_is_asked_whose_turn_it_is():
     the stream of the last launch may be gone, or be captured by its owner."""
     src = open(os.path.join(CSRC, "rdos_api.cpp")).read()
     assert "hipEvent" not in src
+
+
+def test_every_launch_that_waits_for_its_blocks_takes_a_turn():
+    """Each kernel launched cooperatively says when it has ended, and its
+    launcher is called with a turn's number, or out of turn where its blocks
+    do not wait for each other or a graph will launch it."""
+    launchers = []
+    for f in sorted(os.listdir(CSRC)):
+        if not f.endswith(".hip"):
+            continue
+        src = open(os.path.join(CSRC, f)).read()
+        for at in (m.start() for m in re.finditer("hipLaunchCooperativeKernel", src)):
+            launchers.append(re.findall(r"\nhipError_t (\w+)\(([^{]*)\)\n\{", src[:at])[-1])
+        if launchers and launchers[-1][0] in src:
+            assert "end_block(" in src, f
+    assert sorted(name for name, _ in launchers) == ["launch_persist", "launch_resident"]
+    assert all("LaunchEnd" in args for _, args in launchers)
+    calls = [f for f in ("rdos_api.cpp", "rdos_engine.cpp")
+             if re.search(r"\blaunch_(persist|resident)\(", open(os.path.join(CSRC, f)).read())]
+    assert calls == ["rdos_api.cpp"]
