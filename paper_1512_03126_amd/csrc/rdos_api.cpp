@@ -785,6 +785,7 @@ constexpr int kTurnDevices = 64;
 struct Turns {
     LaunchTurn turn[kTurnDevices];
     unsigned long long *ended[kTurnDevices] = {};  // pinned host memory
+    hipEvent_t last[kTurnDevices] = {};            // behind the last launch, where its owner has one
     StreamOwners owners;
 };
 Turns &turns()  // guarded by device_api_mutex()
@@ -809,54 +810,92 @@ void prepare_turns(int device)
     *t.ended[device] = 0;
 }
 
-uint64_t own_stream_owner()
+void join_own_stream(TurnOwner *owner)
 {
     std::lock_guard<std::mutex> g(device_api_mutex());
-    return turns().owners.own_stream();
+    *owner = TurnOwner{};
+    owner->number = turns().owners.own_stream();
+    if (hipEventCreateWithFlags(&owner->event, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();  // without one, nobody waits for its launches on the device
+        owner->event = nullptr;
+    }
 }
 
-// The simulation's number as an owner of turns, when it gets its stream, and
-// before it gives the stream up (drained).  The per-thread stream is another
-// one in every thread.
+void leave_own_stream(TurnOwner *owner)
+{
+    std::lock_guard<std::mutex> g(device_api_mutex());
+    if (!owner->event) return;
+    for (hipEvent_t &last : turns().last)
+        if (last == owner->event) last = nullptr;
+    (void)hipEventDestroy(owner->event);
+    owner->event = nullptr;
+}
+
+// The simulation as an owner of turns, when it gets its stream, and before it
+// gives the stream up (drained).  The per-thread stream is another one in
+// every thread.
 static void join_stream(rdos_sim *s)
 {
-    if (s->own_stream || s->stream == hipStreamPerThread) {
-        s->turn_owner = own_stream_owner();
-        return;
-    }
+    if (s->own_stream) return join_own_stream(&s->turn);
     std::lock_guard<std::mutex> g(device_api_mutex());
-    s->turn_owner = turns().owners.join(s->stream);
+    StreamOwners &owners = turns().owners;
+    s->turn = TurnOwner{};
+    s->turn.number = s->stream == hipStreamPerThread ? owners.own_stream() : owners.join(s->stream);
 }
 static void leave_stream(rdos_sim *s)
 {
-    if (!s->stream || s->own_stream || s->stream == hipStreamPerThread) return;
+    if (!s->stream || s->own_stream) return leave_own_stream(&s->turn);
+    if (s->stream == hipStreamPerThread) return;
     std::lock_guard<std::mutex> g(device_api_mutex());
     turns().owners.leave(s->stream);
 }
 
-// Runs `launch` with the LaunchEnd of the owner's next turn.
+// Runs `launch`, of n_periods periods on the owner's stream, with the
+// LaunchEnd of its turn, or behind the last launch where it should wait and
+// that one's event can be waited for.
 template <class Launch>
-static hipError_t launch_in_turn(int device, uint64_t owner, Launch launch)
+static hipError_t launch_in_turn(int device, TurnOwner *owner, bool wait, int32_t n_periods, hipStream_t st,
+                                 Launch launch)
 {
     std::lock_guard<std::mutex> g(device_api_mutex());
     Turns &t = turns();
     if (device < 0 || device >= kTurnDevices || !t.ended[device]) return hipErrorNotReady;
+    LaunchTurn &turn = t.turn[device];
     LaunchEnd end;
     end.word = t.ended[device];
-    end.number = t.turn[device].take(owner, __atomic_load_n(end.word, __ATOMIC_RELAXED));
-    if (end.number == 0) return hipErrorNotReady;
+    const uint64_t ended = __atomic_load_n(end.word, __ATOMIC_RELAXED);
+    end.number = turn.take(owner->number, ended, n_periods);
+    if (end.number == 0) {
+        // only streams of the library's own wait, for each other: nothing else can hold them up
+        if (!wait || !owner->event || !t.last[device] || !turn.worth_waiting(ended, owner->last, n_periods))
+            return hipErrorNotReady;
+        if (hipStreamWaitEvent(st, t.last[device], 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return hipErrorNotReady;
+        }
+        end.number = turn.take_behind(owner->number, n_periods);
+    }
     const hipError_t e = launch(end);
-    if (e != hipSuccess) t.turn[device].give_back();
-    return e;
+    if (e != hipSuccess) {
+        turn.give_back();
+        return e;
+    }
+    owner->last = end.number;
+    t.last[device] = owner->event;
+    if (owner->event && hipEventRecord(owner->event, st) != hipSuccess) {
+        (void)hipGetLastError();
+        t.last[device] = nullptr;  // others run over the queue until the launch has ended
+    }
+    return hipSuccess;
 }
 
-hipError_t launch_resident_in_turn(int device, uint64_t owner, const DevSim *sims, const ResidentPlan &plan,
-                                   int64_t iter0, int32_t n_periods, int64_t partial, double tau_last, uint64_t epoch,
-                                   hipStream_t st)
+hipError_t launch_resident_in_turn(int device, TurnOwner *owner, bool wait, const DevSim *sims,
+                                   const ResidentPlan &plan, int64_t iter0, int32_t n_periods, int64_t partial,
+                                   double tau_last, uint64_t epoch, hipStream_t st)
 {
     if (plan.max_parts <= 1)
         return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, LaunchEnd{}, st);
-    return launch_in_turn(device, owner, [&](const LaunchEnd &end) {
+    return launch_in_turn(device, owner, wait, n_periods, st, [&](const LaunchEnd &end) {
         return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, end, st);
     });
 }
@@ -869,51 +908,58 @@ static hipError_t launch_persist_in_turn(rdos_sim *s, int32_t len, int64_t parti
         return launch_persist(s->d_desc, s->d_tiles, s->step, len, (int32_t)(s->launches & 1), partial, tau_last,
                               s->queue, grid, s->queue.sync, end, s->stream);
     };
-    return capturing(s) ? launch(LaunchEnd{}) : launch_in_turn(s->device, s->turn_owner, launch);
+    return capturing(s) ? launch(LaunchEnd{}) : launch_in_turn(s->device, &s->turn, true, len, s->stream, launch);
 }
 
 // n periods from the current one; the last lasts tau_last when `partial`
-// (Algorithm 1, Step 1), all others tau.
+// (Algorithm 1, Step 1), all others tau.  Where another's launch has the
+// device, this one's waits for it on the device or leaves a few periods to the
+// queue and asks again.  That is so for one thread that steps several
+// simulations too, since calls return before their periods have run.  Two
+// simulations stepped in turn, 100 periods a call, us for a call of each, with
+// all of the second's periods over the queue, with both over the queue, and
+// so: 2058 tets of three species 11900, 9770 and 4130; 384,000 tets 3560, 3240
+// and 2520; the bar of 1080 tets 10500, 12800 and 4490.
+constexpr int64_t kBesidePeriods = 8;
 rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
 {
     if (n <= 0) return RDOS_OK;
-    bool beside = false;  // another simulation's cooperative launch
-    if (const ResidentPlan *plan = resident_for(s, n)) {
-        const int64_t partial_index = partial ? s->step + n - 1 : -1;
-        while (n > 0) {
+    const int64_t partial_index = partial ? s->step + n - 1 : -1;
+    const ResidentPlan *plan = resident_for(s, n);
+    const int32_t grid = plan ? 0 : persist_grid(s);
+    while (n > 0) {
+        int64_t over_queue = n;  // by two launches per period (or mode 3's one)
+        if (plan || grid > 0) {
             const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
-            const hipError_t e = launch_resident_in_turn(s->device, s->turn_owner, s->d_desc, *plan, s->step, len,
-                                                         partial_index, tau_last, s->resident_epoch, s->stream);
-            beside = e == hipErrorNotReady;
-            if (beside) break;
-            HIP_TRY(s, e, "launch periods");
-            s->mask_dirty = false;  // the kernel reads the counts and writes the occupancy bytes
-            s->resident_epoch += len;
-            s->step += len;
-            n -= len;
+            hipError_t e;
+            if (plan) {
+                e = launch_resident_in_turn(s->device, &s->turn, true, s->d_desc, *plan, s->step, len, partial_index,
+                                            tau_last, s->resident_epoch, s->stream);
+            } else {
+                const rdos_status st = ensure_mask(s);
+                if (st != RDOS_OK) return st;
+                e = launch_persist_in_turn(s, len, partial_index, tau_last, grid);
+            }
+            if (e == hipSuccess) {
+                if (plan) {
+                    s->mask_dirty = false;  // the kernel reads the counts and writes the occupancy bytes
+                    s->resident_epoch += len;
+                } else {
+                    s->launches += len;
+                }
+                s->step += len;
+                n -= len;
+                continue;
+            }
+            if (e != hipErrorNotReady) return hip_fail(s, e, "launch periods");
+            over_queue = std::min(n, kBesidePeriods);
         }
-        if (n <= 0) return RDOS_OK;
-    }
-    const int32_t grid = beside ? 0 : persist_grid(s);
-    if (grid > 0) {
-        const rdos_status st = ensure_mask(s);
-        if (st != RDOS_OK) return st;
-        const int64_t partial_index = partial ? s->step + n - 1 : -1;
-        while (n > 0) {
-            const int32_t len = (int32_t)std::min<int64_t>(n, kPersistPeriods);
-            const hipError_t e = launch_persist_in_turn(s, len, partial_index, tau_last, grid);
-            if (e == hipErrorNotReady) break;
-            HIP_TRY(s, e, "launch periods");
-            s->launches += len;
-            s->step += len;
-            n -= len;
+        for (; over_queue > 0; --over_queue, --n) {
+            const bool last = s->step == partial_index;
+            const rdos_status st = enqueue_period(s, s->step, last ? s->step : -1, last ? tau_last : 0.0);
+            if (st != RDOS_OK) return st;
+            s->step += 1;
         }
-    }
-    for (int64_t i = 0; i < n; ++i) {
-        const bool last = partial && i == n - 1;
-        const rdos_status st = enqueue_period(s, s->step, last ? s->step : -1, last ? tau_last : 0.0);
-        if (st != RDOS_OK) return st;
-        s->step += 1;
     }
     return RDOS_OK;
 }

@@ -152,7 +152,7 @@ struct rdos_engine {
     int64_t cap_sparse = 0;
     uint32_t *h_fail = nullptr;    // pinned copy of the failure word
     uint64_t resident_epoch = 0;
-    uint64_t turn_owner = 0;
+    TurnOwner turn;
     double lds_period_ms = 0.0;    // device time per period of the last run on such a path
     int32_t qphase = 0;            // queue half (qsel) of the next period; graphs start at 0
     bool graph_stale = true;  // a buffer the graphs name was reallocated
@@ -880,7 +880,7 @@ void worker_main(rdos_engine *e)
         hipError_t err = hipEventRecord(e->ev0, e->stream);
         if (err == hipSuccess) {
             if (lds == LdsPath::Resident) {
-                err = launch_resident_in_turn(e->device, e->turn_owner, e->d_sims, e->resident, 0, len, -1, 0.0,
+                err = launch_resident_in_turn(e->device, &e->turn, false, e->d_sims, e->resident, 0, len, -1, 0.0,
                                               e->resident_epoch, e->stream);
                 if (err == hipErrorNotReady) {  // the next chunk runs over the queue, then this path is tried again
                     beside = true;
@@ -1018,7 +1018,7 @@ rdos_status rdos_engine_create(rdos_engine **out, int device, size_t hbm_budget_
         return RDOS_EDEVICE;
     }
     prepare_turns(device);
-    e->turn_owner = own_stream_owner();
+    join_own_stream(&e->turn);
     // Two-launch shapes only: the fused shape (update_bps 0) lost to them on every tuned size measured,
     // and under a profiler, which taxes each launch, it scored first; it stays available by set_shape.
     // One 32-period shape: fewer graph launches per period, at the cost of a longer wait to join.
@@ -1382,6 +1382,7 @@ void rdos_engine_destroy(rdos_engine *e)
     if (e->stream2) (void)hipStreamDestroy(e->stream2);
     if (e->ev0) (void)hipEventDestroy(e->ev0);
     if (e->ev1) (void)hipEventDestroy(e->ev1);
+    leave_own_stream(&e->turn);
     if (e->stream) (void)hipStreamDestroy(e->stream);
     delete e;
 }

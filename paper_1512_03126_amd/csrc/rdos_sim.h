@@ -24,6 +24,19 @@ struct Reaction {
 
 }  // namespace rdos
 
+namespace rdos {
+// An owner of turns to launch blocks that wait for each other (rdos_turn.h).
+// The event is recorded behind each launch on a stream of the library's own;
+// others' launches may wait for it on the device until the owner leaves the
+// stream, which is then drained.  A caller's stream has none: what it waits
+// for, and whether it is being captured, is not known here.
+struct TurnOwner {
+    uint64_t number = 0;
+    uint64_t last = 0;  // its last launch
+    hipEvent_t event = nullptr;
+};
+}  // namespace rdos
+
 struct rdos_sim {
     int device = 0;
     uint64_t seed = 0;
@@ -57,7 +70,7 @@ struct rdos_sim {
     // device
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    uint64_t turn_owner = 0;  // of turns to launch blocks that wait for each other (by stream)
+    rdos::TurnOwner turn;  // for launches whose blocks wait for each other
     rdos::MeshRec *d_mesh = nullptr;
     uint32_t *d_allowed = nullptr;  // per-tet reaction masks (only with regions)
     char *d_state = nullptr;        // counts, maps and flags below: one allocation
@@ -107,17 +120,19 @@ bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c);
 // they do not fit, or (light false) are light and would not share one.
 bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int32_t cus, bool light,
                       rdos::ResidentPlan *plan);
-// launch_resident, one owner's at a time on the device where blocks wait for
-// each other: hipErrorNotReady, and nothing is launched, while another
-// owner's launch may still be under way.  The caller then runs periods over
-// the queue, which waits for nobody.
-hipError_t launch_resident_in_turn(int device, uint64_t owner, const rdos::DevSim *sims,
+// launch_resident, one at a time on the device where blocks wait for each
+// other: hipErrorNotReady, and nothing is launched, while another owner's
+// launch may still be under way and this one is not to wait for it.  The
+// caller then runs periods over the queue, which waits for nobody.
+hipError_t launch_resident_in_turn(int device, rdos::TurnOwner *owner, bool wait, const rdos::DevSim *sims,
                                    const rdos::ResidentPlan &plan, int64_t iter0, int32_t n_periods, int64_t partial,
                                    double tau_last, uint64_t epoch, hipStream_t st);
-// Makes what turns on a device need; a number for the owner of a stream that
-// nobody else uses.
+// Makes what turns on a device need.
 void prepare_turns(int device);
-uint64_t own_stream_owner();
+// The owner of a stream of the library's own, and before it is destroyed
+// (drained).
+void join_own_stream(rdos::TurnOwner *owner);
+void leave_own_stream(rdos::TurnOwner *owner);
 // Compute units of a device (0 when it cannot be asked).
 int32_t compute_units(int device);
 rdos_status match_parity(rdos_sim *s);

@@ -167,3 +167,25 @@ def test_one_launch_over_the_queue_takes_its_turn(P, orc, modes):
     check(a, oa, "the long run")
     a.close()
     b.close()
+
+
+def test_runs_wait_on_the_device(P, orc):
+    note("turns: three simulations stepped in turn without a wait, one of them with a long run between")
+    sims = [pair(P, orc, cells, 70 + i) for i, cells in enumerate([(4, 4, 4), (4, 4, 5), (2, 2, 4)])]
+    for n in (40, 1, 25, 60):
+        for i, (g, o) in enumerate(sims):
+            k = 900 if n == 25 and i == 1 else n  # the others' next runs are too short to wait for it
+            g.step(k)
+            o.run_steps(k)
+    g, o = pair(P, orc, (4, 4, 4), 80)  # a simulation closed while the others' runs are under way
+    g.step(30)
+    o.run_steps(30)
+    check(g, o, "closed")
+    g.close()
+    for i, (g, o) in enumerate(sims):
+        t_end = g.time()[0] + 20.4 * g.tau
+        g.run_until(t_end)
+        o.run_until(t_end)
+    for i, (g, o) in enumerate(sims):
+        check(g, o, i)
+        g.close()

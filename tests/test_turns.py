@@ -24,7 +24,7 @@ def test_no_stream_or_event_is_asked_whose_turn_it_is():
     """A launch in turn looks at its own books and at a word of host memory:
     the stream of the last launch may be gone, or be captured by its owner."""
     src = open(os.path.join(CSRC, "rdos_api.cpp")).read()
-    assert "hipEvent" not in src
+    assert "hipEventQuery" not in src and "hipEventSynchronize" not in src
 
 
 def test_every_launch_that_waits_for_its_blocks_takes_a_turn():
