@@ -222,8 +222,8 @@ rdos_status rdos_step_static(rdos_sim *s, int64_t n_steps);
  * held in LDS, where a realization's counts fit the LDS of the device's
  * compute units divided among the realizations (one block per realization:
  * about 10,000 tet-species; a single realization: about 2.5 million);
- * otherwise, for a single period of a larger work list, and on a stream that
- * is being captured: a work list of at most 8 tiles (1024 tets per
+ * otherwise, for up to three periods of a larger work list, by how much of it
+ * is occupied, and on a stream that is being captured: a work list of at most 8 tiles (1024 tets per
  * realization and tile) runs its periods in one cooperative launch over the
  * occupied-tet queue, the scan and update phases of each period separated by
  * grid-wide barriers, and larger ones launch a scan and an update kernel per

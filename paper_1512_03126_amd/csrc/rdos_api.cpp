@@ -245,8 +245,7 @@ static double expected_pairs(const rdos_sim *s)
     const int32_t S = (int32_t)s->D.size();
     double pairs = 0.0;
     for (int32_t m = 0; m < S; ++m) {
-        double total = 0.0;
-        for (int32_t r = 0; r < s->Rz; ++r) total += (double)s->totals[(size_t)r * S + m];
+        const double total = (double)s->species_totals[m];
         pairs += (double)s->T * (1.0 - std::exp(-total / ((double)s->Rz * s->T)));
     }
     return pairs;
@@ -380,14 +379,33 @@ static bool capturing(const rdos_sim *s)
     return hipStreamIsCapturing(s->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
 }
 
+// Whether n periods pay for the reading and writing of every count around them
+// (and, with several blocks, for the cooperative launch), which the queue does
+// not need: it reads the occupancy bytes and the counts of occupied tets.
+// Lists of at most kPersistTiles tiles always do, and four periods.  Of larger
+// ones, by the share of pairs that hold molecules, us for n periods and the
+// wait, over the queue and in LDS, at so many molecules per pair.  Several
+// blocks, n = 2: 12,096 tets at 0.01 40 and 46, 2,058,000 at 0.01 43 and 58, at
+// 0.1 65 and 65, 262,440 of three species at 0.1 104 and 72; n = 3: 2,058,000
+// at 0.01 54 and 65, 384,000 of three species at 0.02 90 and 80; n = 4:
+// 2,058,000 at 0.01 78 and 72.  A block each, n = 1: 3000 realizations of 162
+// tets at 0.01 32 and 38, 200 of 4374 at 0.001 39 and 43, at 0.1 71 and 59; n =
+// 2: 3000 of 162 45 and 42, 200 of 4374 at 0.001 55 and 50.
+static bool long_enough(const rdos_sim *s, int64_t n, bool several_blocks)
+{
+    if (s->n_tiles <= kPersistTiles || n >= 4) return true;
+    const double cells = (double)s->T * (double)s->D.size();
+    const double share = s->desc.zeroth ? 1.0 : expected_pairs(s) / cells;
+    if (several_blocks) return n >= (share >= 0.08 ? 2 : share >= 0.015 ? 3 : 4);
+    return n >= (share >= 0.08 ? 1 : 2);
+}
+
 // The resident launch for n periods, or null: the two-launch (or one-launch)
 // path.  Several blocks per realization, unless one does as well: light
 // tets (on average two molecules per pair or fewer, by the counts last set)
 // with a lane each.  Measured: the cube of 750 tets at 1.3 molecules per tet
 // 6.0 us per period with one block, 6.5 with 47; a bar of 1080 tets at 93
-// molecules per tet 64 and 23.5.  A single period of a work list too large
-// for the one-launch path costs the same either way (0.51 ms with the
-// reading of 3 x 384,000 counts), without the cooperative launch.
+// molecules per tet 64 and 23.5.
 static const ResidentPlan *resident_for(rdos_sim *s, int64_t n)
 {
     if (s->launch_mode != 0) return nullptr;
@@ -402,14 +420,17 @@ static const ResidentPlan *resident_for(rdos_sim *s, int64_t n)
         one = nullptr;
     }
     if (many && !many->full && !resident_lists_hold(s, cut_many(s))) many = nullptr;
-    if (!many) return one;
-    if (one) {
+    if (one && many) {
         int64_t molecules = 0;
-        for (int64_t t : s->totals) molecules += t;
+        for (int64_t t : s->species_totals) molecules += t;
         const int64_t pairs = (int64_t)s->T * (int64_t)s->D.size();
-        if (pairs <= kResidentMaxThreads && molecules <= 2 * pairs * s->Rz) return one;
+        if (pairs > kResidentMaxThreads || molecules > 2 * pairs * s->Rz)
+            one = nullptr;
+        else
+            many = nullptr;
     }
-    return n > 1 || s->n_tiles <= kPersistTiles ? many : nullptr;
+    const ResidentPlan *plan = many ? many : one;
+    return plan && long_enough(s, n, many != nullptr) ? plan : nullptr;
 }
 
 static int64_t tiles_of(const rdos_sim *s) { return (int64_t)s->Rz * ((s->T + kTetsPerTile - 1) / kTetsPerTile); }
@@ -1409,6 +1430,7 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
     s->anchor_step = 0;
     s->anchor_t = 0.0;
     s->totals.assign((size_t)s->Rz * S, 0);
+    s->species_totals.assign((size_t)S, 0);
     // counts staged before finalize
     for (auto &kv : s->staged) {
         const int32_t r = kv.first / kMaxSpecies, m = kv.first % kMaxSpecies;
@@ -1416,6 +1438,7 @@ rdos_status rdos_finalize(rdos_sim *s, double tau_scale, double *out_tau)
         HIP_TRY(s, hipMemcpyAsync(dst, kv.second.data(), (size_t)T * sizeof(int32_t), hipMemcpyHostToDevice, s->stream),
                 "upload counts");
         for (int32_t c : kv.second) s->totals[(size_t)r * S + m] += c;
+        s->species_totals[m] += s->totals[(size_t)r * S + m];
     }
     HIP_TRY(s, hipStreamSynchronize(s->stream), "upload counts");
     s->mask_dirty = true;
@@ -1447,7 +1470,9 @@ rdos_status rdos_set_counts(rdos_sim *s, int32_t realization, int32_t species, c
             "upload counts");
     HIP_TRY(s, hipStreamSynchronize(s->stream), "upload counts");
     s->mask_dirty = true;
-    s->totals[(size_t)realization * s->D.size() + species] = total;
+    int64_t &last = s->totals[(size_t)realization * s->D.size() + species];
+    s->species_totals[species] += total - last;
+    last = total;
     return RDOS_OK;
 }
 

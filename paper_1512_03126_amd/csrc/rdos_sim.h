@@ -91,6 +91,7 @@ struct rdos_sim {
     rdos::ResidentPlan resident_many{};  // as many as the device holds (blocks 0: does not apply)
     uint64_t resident_epoch = 0;         // periods launched with several blocks (their counters' value)
     std::vector<int64_t> totals;         // molecules last set, per realization and species
+    std::vector<int64_t> species_totals; // and over the realizations: rules ask on each call
     rdos::DevSim desc{};
 };
 
