@@ -240,7 +240,7 @@ ResidentCut resident_cut(int32_t T, int32_t S, int32_t R, int32_t max_blocks)
 
 // Pairs that a realization is expected to hold: the counts last set, spread
 // evenly.
-static double expected_pairs(const rdos_sim *s)
+double expected_pairs(const rdos_sim *s)
 {
     const int32_t S = (int32_t)s->D.size();
     double pairs = 0.0;

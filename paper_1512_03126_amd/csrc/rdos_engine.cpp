@@ -389,6 +389,29 @@ bool plan_sparse(const rdos_engine *e, std::vector<WorkUnit> &units, SparsePlan 
     return true;
 }
 
+// Whether the slots' runs are long enough to lay the list out for a path with
+// its state in LDS, and to read and write every count around them.  Lists of
+// at most kPersistTiles tiles and occupied ones are from one or two periods
+// on; others, us from submission to the end, over the queue and in LDS: ten
+// realizations of 48,000 tets of three species at 0.01 molecules per pair, 4
+// periods 159 and 173, 8 240 and 217; one of 998,250 tets of four species at
+// 0.001, 4 periods 147 and 176, 8 217 and 214; 3000 of 162 tets, 4 periods 145
+// and 169, 12 245 and 218.
+bool long_enough(const rdos_engine *e, int64_t n_tiles)
+{
+    int64_t left = 0;
+    double pairs = 0.0, cells = 0.0;
+    for (uint64_t id : e->slots) {
+        const Ticket &tk = e->tickets.at(id);
+        const rdos_sim *s = tk.sim;
+        left = std::max<int64_t>(left, tk.end_step - s->step);
+        const double all = (double)s->T * (double)s->D.size();
+        cells += s->Rz * all;
+        pairs += s->Rz * (s->desc.zeroth ? all : expected_pairs(s));
+    }
+    return n_tiles <= kPersistTiles || left >= (pairs >= 0.08 * cells ? 2 : 8);
+}
+
 // Rewrites the device work list for the current slots (lock held).
 rdos_status build_work(rdos_engine *e)
 {
@@ -466,9 +489,10 @@ rdos_status build_work(rdos_engine *e)
     std::vector<ResidentUnit> runits;
     std::vector<WorkUnit> sunits;
     // light blocks with a compute unit each only after the sparse kernel
-    bool resident = !sims.empty() && cut_resident(e, runits, e->resident, false);
-    const bool sparse = !sims.empty() && !resident && plan_sparse(e, sunits, e->sparse);
-    if (!sims.empty() && !resident && !sparse) resident = cut_resident(e, runits, e->resident, true);
+    const bool planned = !sims.empty() && long_enough(e, n_tiles);
+    bool resident = planned && cut_resident(e, runits, e->resident, false);
+    const bool sparse = planned && !resident && plan_sparse(e, sunits, e->sparse);
+    if (planned && !resident && !sparse) resident = cut_resident(e, runits, e->resident, true);
     if (resident && make_room(e, &e->d_runits, &e->cap_runits, (int64_t)runits.size()) &&
         make_room(e, &e->d_resident, &e->cap_resident,
                   (int64_t)resident_plan_bytes(e->resident.blocks, e->resident.max_parts))) {

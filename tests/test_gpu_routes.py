@@ -56,3 +56,34 @@ def test_short_runs_of_sparse_lists(shape, S, Rz, mean, n):
     least = least_times(P, g, n, 40)
     assert least[0] <= 1.12 * least[1], least
     g.close()
+
+
+@pytest.mark.parametrize("shape,S,Rz,mean,n", [
+    ((20, 20, 20), 3, 10, 0.01, 3),
+    ((55, 55, 55), 4, 1, 0.001, 4),
+])
+def test_short_requests_of_sparse_lists(orc, shape, S, Rz, mean, n):
+    import paper_1512_03126_amd as P
+
+    note(f"routes: requests of {n} periods, {shape} cells, {S} species, {Rz} realizations at {mean}")
+    g, (xyz, tets, init) = box(P, shape, S, mean, Rz)
+    engines = [P.rdos_engine_create(0, 0) for _ in range(2)]
+    P.rdos_engine_set_shape(engines[1], 32, 2048, 1, 1)  # a fixed shape runs over the queue
+    least = [np.inf, np.inf]
+    for i in range(43):
+        for j, e in enumerate(engines):
+            t = time.perf_counter()
+            ticket = P.rdos_engine_submit(e, g.h, n, 1.0)
+            P.rdos_engine_drain(e)
+            P.rdos_engine_release(e, ticket)
+            if i >= 3:
+                least[j] = min(least[j], time.perf_counter() - t)
+    for e in engines:
+        P.rdos_engine_destroy(e)
+    assert least[0] <= 1.12 * least[1], least
+    o = orc.OracleSim(xyz, tets, [1e-12] * S, [], seed=6, realization=Rz - 1)
+    for s in range(S):
+        o.set_counts(s, init[Rz - 1, s])
+    o.run_steps(2 * 43 * n)
+    assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts())
+    g.close()
