@@ -255,10 +255,15 @@ double expected_pairs(const rdos_sim *s)
 // to spare.  Blocks whose lists overflow move every molecule through memory,
 // which is slower than the two-launch path: us per period, two launches and
 // this, 998,250 tets of four species at 0.3 and 1 molecules per tet 71 and
-// 101, 121 and 167; below that, at 0.1 and 0.03: 44 and 25, 23 and 15.5.
+// 101, 121 and 167; below that, at 0.1 and 0.03: 44 and 25, 23 and 15.5.  What
+// is expected goes by the counts last set: where they were written through a
+// device view, or grew, the kernel raises kFlagCrowded (998,250 tets of four
+// species, written with one molecule per pair: 221 us per period, 195 over
+// the queue).
 bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c)
 {
     if (c.full) return true;
+    if (s->crowded) return false;
     if (s->desc.zeroth) return false;  // every tet is listed for the SSA
     const int32_t S = (int32_t)s->D.size(), R = (int32_t)s->rx.size(), ls = (c.len + 3) & ~3;
     return expected_pairs(s) * c.len <= 0.5 * (double)s->T * S * resident_range(S, R, ls, c.lds_bytes);
@@ -686,6 +691,7 @@ rdos_status ensure_mask(rdos_sim *s)
 
 static rdos_status flags_status(rdos_sim *s, int32_t flags)
 {
+    if (flags & kFlagCrowded) s->crowded = true;
     if (flags & 1) return fail(s, RDOS_EOVERFLOW, "a molecule count overflowed int32");
     if (flags & 4) return fail(s, RDOS_EDEVICE, "occupied-tet queue overflowed (internal error)");
     if (flags & 8)
@@ -963,6 +969,7 @@ rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
             }
             if (e == hipSuccess) {
                 if (plan) {
+                    s->short_run |= !plan->full;
                     s->mask_dirty = false;  // the kernel reads the counts and writes the occupancy bytes
                     s->resident_epoch += len;
                 } else {
@@ -1468,7 +1475,9 @@ rdos_status rdos_set_counts(rdos_sim *s, int32_t realization, int32_t species, c
     int32_t *dst = s->d_buf[s->step & 1] + ((int64_t)realization * (int64_t)s->D.size() + species) * padded_tets(s->T);
     HIP_TRY(s, hipMemcpyAsync(dst, counts, (size_t)s->T * sizeof(int32_t), hipMemcpyHostToDevice, s->stream),
             "upload counts");
+    if (s->short_run) HIP_TRY(s, launch_clear_flags(s->d_flags, kFlagCrowded, s->stream), "clear flags");
     HIP_TRY(s, hipStreamSynchronize(s->stream), "upload counts");
+    s->short_run = s->crowded = false;
     s->mask_dirty = true;
     int64_t &last = s->totals[(size_t)realization * s->D.size() + species];
     s->species_totals[species] += total - last;

@@ -150,7 +150,7 @@ struct rdos_engine {
     int64_t cap_sunits = 0;
     char *d_sparse = nullptr;      // its scratch, counts and failure word
     int64_t cap_sparse = 0;
-    uint32_t *h_fail = nullptr;    // pinned copy of the failure word
+    uint32_t *h_fail = nullptr;    // pinned copy of its failure word, or of the resident plan's crowded word
     uint64_t resident_epoch = 0;
     TurnOwner turn;
     double lds_period_ms = 0.0;    // device time per period of the last run on such a path
@@ -913,6 +913,10 @@ void worker_main(rdos_engine *e)
                 }
                 e->resident_epoch += len;
                 if (err == hipSuccess) err = launch_advance(e->d_sims, e->queue.hdr, len, e->stream);
+                *e->h_fail = 0u;
+                if (err == hipSuccess && !e->resident.full)
+                    err = hipMemcpyAsync(e->h_fail, resident_crowded(e->resident), sizeof(uint32_t),
+                                         hipMemcpyDeviceToHost, e->stream);
             } else if (lds == LdsPath::Sparse) {
                 err = launch_sparse(e->d_sims, e->d_sunits, 0, len, e->sparse, e->stream);
                 if (err == hipSuccess)
@@ -947,6 +951,15 @@ void worker_main(rdos_engine *e)
             e->lds_path = LdsPath::None;
             e->busy_s += ms * 1e-3;
             continue;
+        }
+        if (lds == LdsPath::Resident && !e->resident.full) {
+            const bool crowded = *e->h_fail != 0u;  // short lists overflowed: over the queue from here on
+            for (uint64_t id : e->slots) {
+                rdos_sim *s = e->tickets.at(id).sim;
+                s->short_run = true;
+                s->crowded |= crowded;
+            }
+            if (crowded) e->lds_path = LdsPath::None;
         }
         if (!fused && lds == LdsPath::None) e->qphase = (phase + len) & 1;
         if (timed) {

@@ -43,7 +43,8 @@ struct alignas(16) DevSim {
     uint8_t *mask[2];          // [Rz][S][mstride] occupancy of buf[k & 1]: byte t >> 2 of row (r, s)
                                // equals occupancy_tag(k) when species s of tets 4 (t >> 2) .. + 3 may
                                // be non-zero in period k
-    int32_t *flags;            // bit 0: count overflow; bit 1: SSA event cap; bit 2: queue overflow
+    int32_t *flags;            // bit 0: count overflow; bit 1: SSA event cap; bit 2: queue overflow; bit 3: a
+                               // wait between blocks failed; bit 4: kFlagCrowded
     int32_t T, S, R, Rz;
     int32_t mstride;           // occupancy bytes per species row (Tp / 4 rounded up to 16)
     uint32_t key0, key1;       // Philox key words before the realization is mixed in
@@ -252,7 +253,8 @@ struct ResidentUnit {
 };
 struct ResidentPlan {
     unsigned long long *done;   // [blocks][kResidentFlagStride] last period finished by each block, then the
-                                // failure word and the number of blocks that have ended (device)
+                                // failure word, the number of blocks that have ended and whether short lists
+                                // overflowed (resident_crowded) (device)
     ResidentPart *parts;        // [blocks] (device)
     uint16_t *neighbours;       // [blocks][max_parts] (device; max_parts > 1)
     int32_t blocks;
@@ -267,6 +269,9 @@ constexpr int kResidentMaxThreads = 1024;
 constexpr int kResidentMaxParts = 1024;
 constexpr int64_t kResidentMaxUnits = 1 << 16;  // of an engine's work list
 constexpr int32_t kResidentLdsMax = 160 * 1024;
+// Raised by a run whose short lists overflowed in over a quarter of its
+// periods: no error, but the queue is faster then.
+constexpr int32_t kFlagCrowded = 16;
 constexpr int kResidentFlagStride = 16;  // 128 bytes between blocks' period counters
 constexpr int32_t kResidentHeadBytes = kMaxSpecies * 8 + kMaxReactions * 16 + 16;
 // Two layouts of a block whose species rows hold `ls` tets (a multiple of 4).
@@ -311,6 +316,11 @@ __host__ __device__ inline bool resident_every(int32_t S, int32_t R, int32_t ls,
 // Device memory of a plan, and its arrays' places in it (16-byte aligned).
 size_t resident_plan_bytes(int64_t blocks, int64_t max_parts);
 void resident_place(ResidentPlan *plan, void *memory);
+// The word of a plan that is not zero once kFlagCrowded was raised in a run.
+inline const uint32_t *resident_crowded(const ResidentPlan &plan)
+{
+    return reinterpret_cast<const uint32_t *>(plan.done + (int64_t)plan.blocks * kResidentFlagStride + 1);
+}
 // Fills the arrays of a plan: its blocks are those of n_units units whose
 // `first` fields ascend from 0 without gaps, or (units null) of the
 // realizations of one simulation, each cut like `same`.
@@ -361,6 +371,8 @@ hipError_t launch_mask_build(const int32_t *counts, uint8_t *mask_cur, uint8_t *
 inline int32_t mask_stride(int64_t Tp) { return (int32_t)(((Tp / 4) + 15) & ~(int64_t)15); }
 // counts[0 .. T) and the flags word to out[0 .. T] (pinned host memory).
 hipError_t launch_read_counts(const int32_t *counts, const int32_t *flags, int32_t *out, int32_t T, hipStream_t st);
+// Takes `bits` off the flags word.
+hipError_t launch_clear_flags(int32_t *flags, int32_t bits, hipStream_t st);
 // The mesh records taken apart: nbr[T][4], w[T][4], g[T], nav[T].
 hipError_t launch_unpack_mesh(const MeshRec *mesh, int32_t T, int32_t *nbr, double *w, double *g, double *nav,
                               hipStream_t st);

@@ -1611,6 +1611,14 @@ hipError_t launch_read_counts(const int32_t *counts, const int32_t *flags, int32
     return hipGetLastError();
 }
 
+__global__ void clear_flags_kernel(int32_t *flags, int32_t bits) { atomicAnd(flags, ~bits); }
+
+hipError_t launch_clear_flags(int32_t *flags, int32_t bits, hipStream_t st)
+{
+    clear_flags_kernel<<<1, 1, 0, st>>>(flags, bits);
+    return hipGetLastError();
+}
+
 // After a chunk of periods: every simulation's period index moves on.
 __global__ void advance_kernel(DevSim *sims, const WorkHeader *hdr, int64_t by)
 {

@@ -198,7 +198,8 @@ __global__ __launch_bounds__(256) void resident_layout_kernel(const DevSim *__re
         pt.neighbours = n;
         plan.parts[b] = pt;
         plan.done[(int64_t)b * kResidentFlagStride] = 0;
-        if (b == 0) plan.done[(int64_t)plan.blocks * kResidentFlagStride] = 0;  // both words
+        if (b == 0)  // the failure word and those after it
+            for (int k = 0; k < 2; ++k) plan.done[(int64_t)plan.blocks * kResidentFlagStride + k] = 0;
     }
 }
 
@@ -305,6 +306,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         reactants = x.order() > 0 ? (uint32_t)(4 * a) | (uint32_t)(4 * b) << 8 : 1u << 16;
     }
 
+    int32_t spills = 0;  // periods in which short lists overflowed
     for (int32_t k = 0; k < n_periods; ++k) {
         // read the descriptor's fields in the period that uses them: held
         // across the loop they are more than the scalar registers hold
@@ -535,6 +537,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         }
         // additions through memory reach it before this block publishes the
         // period
+        if (!FULL && spill) ++spills;
         if (!alone || spill) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (spill)
@@ -603,6 +606,10 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         if (alone && FULL && (n_periods & 1)) *(gptr<v4i>)(other + s * Tp + i) = v4i{0, 0, 0, 0};
     }
     if (head.stop && tid == 0) atomicOr(sm.flags, 8);
+    if (!FULL && 4 * (int64_t)spills > n_periods && tid == 0) {
+        atomicOr(sm.flags, kFlagCrowded);
+        atomicOr(fail + 2, 1u);
+    }
     end_block(fail + 1, launch_end);
 }
 

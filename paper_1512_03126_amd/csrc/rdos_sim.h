@@ -90,6 +90,8 @@ struct rdos_sim {
     rdos::ResidentPlan resident_one{};   // state-in-LDS launches with one block per realization, and with
     rdos::ResidentPlan resident_many{};  // as many as the device holds (blocks 0: does not apply)
     uint64_t resident_epoch = 0;         // periods launched with several blocks (their counters' value)
+    bool short_run = false;              // launched with short lists since counts were last set
+    bool crowded = false;                // and they overflowed: not again until counts are set
     std::vector<int64_t> totals;         // molecules last set, per realization and species
     std::vector<int64_t> species_totals; // and over the realizations: rules ask on each call
     rdos::DevSim desc{};

@@ -87,3 +87,88 @@ def test_short_requests_of_sparse_lists(orc, shape, S, Rz, mean, n):
     o.run_steps(2 * 43 * n)
     assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts())
     g.close()
+
+
+def test_crowded_views_leave_the_short_lists():
+    """Counts that a device view made crowded, after they were set sparse: the
+    first run finds its lists too short, later ones go over the queue until
+    counts are set again."""
+    import torch
+
+    import paper_1512_03126_amd as P
+
+    note("routes: 998,250 tets of four species set at 0.01 and written through a view at 1 molecule per pair")
+    g, (_, tets, init) = box(P, (55, 55, 55), 4, 0.01)
+    crowd = torch.from_numpy(np.random.default_rng(3).poisson(1.0, tets.shape[0]).astype(np.int32))
+    for s in range(4):
+        g.device_counts(s, 0).copy_(crowd)
+    torch.cuda.synchronize()
+    g.step(8)
+    g.synchronize()
+    least = least_times(P, g, 8, 12)
+    assert least[0] <= 1.1 * least[1], least
+    for s in range(4):
+        g.set_counts(s, init[0, s])
+    least = least_times(P, g, 8, 12)
+    assert least[0] <= 0.9 * least[1], least  # LDS again
+    g.close()
+
+
+def test_crowded_views_in_the_engine(orc):
+    """The same through an engine, with a look at every count: a run whose
+    lists overflow, one over the queue, and one in LDS after counts are set."""
+    import torch
+
+    import paper_1512_03126_amd as P
+
+    Rz = 150
+    note(f"routes: {Rz} realizations of 4860 tets written crowded through views, engine and plain")
+    xyz, tets = W.kuhn_box(9, 9, 10, 0.2e-6)
+    T = tets.shape[0]
+    rx = [([0, 1], [2], 2e8), ([2], [0, 1], 60.0)]
+    D = [1e-12, 0.5e-12, 0.8e-12]
+    rng = np.random.default_rng(4)
+    g = P.Simulation(xyz, tets, D, rx, seed=9, n_realizations=Rz, tau_scale=None)
+    e = P.rdos_engine_create(0, 0)
+    sparse = (rng.random((3, T)) < 0.01).astype(np.int32)
+    crowd = rng.poisson(0.5, (3, T)).astype(np.int32)
+    o = orc.OracleSim(xyz, tets, D, rx, seed=9, realization=Rz - 1)
+
+    def request(n):
+        t = P.rdos_engine_submit(e, g.h, n, 1.0)
+        P.rdos_engine_drain(e)
+        P.rdos_engine_release(e, t)
+        o.run_steps(n)
+        assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts()), n
+
+    def sets(counts, view):
+        for r in range(Rz):
+            for s in range(3):
+                if view:
+                    g.device_counts(s, r).copy_(torch.from_numpy(counts[s]))
+                else:
+                    g.set_counts(s, counts[s], realization=r)
+        torch.cuda.synchronize()
+        for s in range(3):
+            o.set_counts(s, counts[s])
+
+    sets(sparse, False)
+    request(9)
+    sets(crowd, True)
+    request(11)
+    request(12)
+    g.step(5)
+    o.run_steps(5)
+    sets(sparse, False)
+    sets(crowd, True)
+    for n in (3, 4, 2):  # in LDS, and not looked at between
+        g.step(n)
+        o.run_steps(n)
+    assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts())
+    sets(sparse, False)
+    request(10)
+    g.step(6)
+    o.run_steps(6)
+    assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts())
+    P.rdos_engine_destroy(e)
+    g.close()
