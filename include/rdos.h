@@ -263,7 +263,8 @@ void rdos_destroy(rdos_sim *s);
 /* ------------------------------------------------------------------------ */
 
 /* An engine on `device` that admits simulations while their device memory
- * fits in hbm_budget_bytes (0 = 90% of the free device memory). */
+ * fits in hbm_budget_bytes (0 = 90% of the free device memory).  What is left
+ * of it may hold scratch, which an admission takes back. */
 rdos_status rdos_engine_create(rdos_engine **out, int device, size_t hbm_budget_bytes);
 
 /* Queues n_steps full periods of `sim`.  The simulation may be finalized

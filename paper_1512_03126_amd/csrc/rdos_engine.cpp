@@ -19,6 +19,7 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <string>
@@ -148,8 +149,11 @@ struct rdos_engine {
     int64_t cap_runits = 0;
     WorkUnit *d_sunits = nullptr;  // the sparse kernel's units, largest first
     int64_t cap_sunits = 0;
-    char *d_sparse = nullptr;      // its scratch, counts and failure word
+    // its scratch, counts and failure word, within the budget's rest: an
+    // admission that needs the memory has the worker give it back first
+    char *d_sparse = nullptr;
     int64_t cap_sparse = 0;
+    bool give_back = false;
     uint32_t *h_fail = nullptr;    // pinned copy of its failure word, or of the resident plan's crowded word
     uint64_t resident_epoch = 0;
     TurnOwner turn;
@@ -225,17 +229,20 @@ rdos_status ensure(rdos_engine *e, T **buf, int64_t *cap, int64_t need, const ch
 }
 
 // The same for what the paths with their state in LDS keep (no graph names
-// it): false where there is no room, and then the queue runs the periods.
+// it), up to `most`: false where there is no room, and then the queue runs the
+// periods.
 template <typename T>
-bool make_room(rdos_engine *e, T **buf, int64_t *cap, int64_t need)
+bool make_room(rdos_engine *e, T **buf, int64_t *cap, int64_t need,
+               int64_t most = std::numeric_limits<int64_t>::max())
 {
     if (need <= *cap) return true;
+    if (need > most) return false;
     if (hipStreamSynchronize(e->stream) != hipSuccess) return false;
     std::lock_guard<std::mutex> g(device_api_mutex());
     if (*buf) (void)hipFree(*buf);
     *buf = nullptr;
     *cap = 0;
-    const int64_t n = std::max<int64_t>(need, need + need / 2);
+    const int64_t n = std::min<int64_t>(most, need + need / 2);
     if (hipMalloc(buf, (size_t)n * sizeof(T)) != hipSuccess) {
         (void)hipGetLastError();
         *buf = nullptr;
@@ -508,7 +515,8 @@ rdos_status build_work(rdos_engine *e)
         SparsePlan &p = e->sparse;
         const int64_t scratch = (int64_t)p.units * p.unit_bytes, counts = ((int64_t)p.units * 8 + 255) & ~(int64_t)255;
         if (!make_room(e, &e->d_sunits, &e->cap_sunits, (int64_t)sunits.size()) ||
-            !make_room(e, &e->d_sparse, &e->cap_sparse, scratch + counts + 256))
+            !make_room(e, &e->d_sparse, &e->cap_sparse, scratch + counts + 256,
+                       (int64_t)(e->budget - std::min(e->used, e->budget))))
             p.units = 0;
         if (p.units > 0) {
             p.scratch = e->d_sparse;
@@ -676,6 +684,12 @@ void admitter_main(rdos_engine *e)
                 const double tau_scale = tk.tau_scale;
                 rdos_status st = RDOS_OK;
                 std::string err;
+                while (e->cap_sparse > 0 && e->used + (size_t)e->cap_sparse > e->budget && !e->stop &&
+                       !e->worker_dead) {
+                    e->give_back = true;
+                    e->cv_work.notify_all();
+                    e->cv_admit.wait(lk);
+                }
                 lk.unlock();
                 if (s->state != SimState::Ready) {
                     s->engine_owned = false;
@@ -739,6 +753,21 @@ void worker_main(rdos_engine *e)
     std::unique_lock<std::mutex> lk(e->mu);
     bool beside = false;  // another owner's launch took the device when the last chunk was to have its state in LDS
     while (!e->stop) {
+        if (e->give_back) {  // the list is laid out again, within what the budget leaves then
+            e->give_back = false;
+            (void)hipStreamSynchronize(e->stream);
+            {
+                std::lock_guard<std::mutex> g(device_api_mutex());
+                if (e->d_sparse) (void)hipFree(e->d_sparse);
+            }
+            e->d_sparse = nullptr;
+            e->cap_sparse = 0;
+            if (e->lds_path == LdsPath::Sparse) {
+                e->lds_path = LdsPath::None;
+                e->rebuild = true;
+            }
+            e->cv_admit.notify_all();
+        }
         if (e->held) {  // rdos_engine_hold: admissions go on, no chunk starts
             e->cv_work.wait(lk);
             continue;
@@ -1021,6 +1050,7 @@ void worker_main(rdos_engine *e)
         e->slots.swap(keep);
     }
     e->worker_dead = !e->stop;
+    e->cv_admit.notify_all();
     e->cv_done.notify_all();
 }
 

@@ -349,7 +349,9 @@ struct SparsePlan {
 };
 constexpr int kSparseMaxThreads = 1024;
 constexpr int kSparseTetBits = 27;        // tets below 2^27 - 1
-constexpr size_t kSparseMaxUnits = 2048;  // about a gigabyte of scratch
+// Their scratch is (24 + 4 S) bytes a slot: 1.2 GB for 2048 units of 16,384 slots
+// and three species, 2.4 GB for twelve.
+constexpr size_t kSparseMaxUnits = 2048;
 constexpr int32_t kSparseHeadBytes = kMaxSpecies * 8 + kMaxReactions * 16 + 32;
 // The table and lane state for units of up to S species, R reactions and
 // about `pairs` occupied pairs, and for more or fewer units than the device
