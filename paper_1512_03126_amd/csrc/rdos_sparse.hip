@@ -603,9 +603,10 @@ hipError_t launch_sparse(const DevSim *sims, const WorkUnit *units, int64_t iter
 bool sparse_shape(int32_t S, int32_t R, int64_t pairs, bool many_units, SparsePlan *plan)
 {
     const int32_t lane = R > 0 ? resident_lane_bytes(S, R) + 4 * S : 0;
-    for (int32_t step = 1; step <= 5; ++step) {
+    // 16,384 slots at most: 20,480 do not fit beside the head
+    for (int32_t step = 1; step <= 4; ++step) {
         const int32_t slots = 4096 * step;
-        if (pairs > slots * 6 / 10 && step < 5) continue;
+        if (pairs > slots * 6 / 10) continue;
         // the filters: some 16 bits of `seen` a pair where they fit
         int32_t filter = R > 0 && S > 1 ? (step == 1 ? 512 : 2048) : 4;
         if (kSparseHeadBytes + 8 * slots + 12 * filter + 64 * lane > kResidentLdsMax) filter = min(filter, 1024);
