@@ -269,6 +269,49 @@ bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c)
     return expected_pairs(s) * c.len <= 0.5 * (double)s->T * S * resident_range(S, R, ls, c.lds_bytes);
 }
 
+// Tets of a block of `len` that may react, at most: those expected to hold a
+// pair, or all.
+static double expected_tets(const rdos_sim *s, int32_t len)
+{
+    if (s->desc.zeroth) return len;
+    return std::min((double)len, expected_pairs(s) * len / s->T);
+}
+
+// Whether blocks of `len` tets of a simulation, which have the device `turns`
+// times one after the other (1: all at once), are faster than the queue.  A
+// compute unit has 768 of the queue's lanes in the SSA (512 above ten species)
+// whatever the model, and as many of a block's as the LDS holds beside its
+// counts: 64 at 16 species and 32 reactions.  Many reactions over few lanes,
+// or many turns for little work, leave these paths behind.  Measured, us per
+// period, two launches and this path, with so many passes of the lanes over
+// the tets: one turn, 20 realizations of 10,368 tets, 16 reactions, 7 passes
+// 217 and 124, 24 reactions, 13 passes 344 and 408; 200 of 750 tets, 24
+// reactions, 12 passes 276 and 354; two turns, 1000 of 384 tets, 16 reactions, 3
+// passes 131 and 119; 400 of 750, 24 reactions, 12 passes 298 and 685; three,
+// 3000 of 162 tets, 8 reactions, 2.5 passes 92 and 80, 16 reactions 142 and 153;
+// four, 1000 of 384 tets, 32 reactions, 6 passes 385 and 699.  More turns: 10,000
+// realizations of 162 tets, 3 species and 2 reactions, five turns, 126 pairs in a
+// block 72 and 36, 5 pairs 23 and 23; 20,000 of 48 tets, ten turns, one pair 25
+// and 37; 30,000 of 6 tets, eight turns 45 and 80.
+static bool resident_pays(const rdos_sim *s, int32_t len, double turns, int32_t lanes)
+{
+    const int32_t R = (int32_t)s->rx.size();
+    const double tets = expected_tets(s, len), pairs = s->desc.zeroth ? len : expected_pairs(s) * len / s->T;
+    if (turns > 4.0 && !(R == 0 && turns <= 5.0) && !(R <= 6 && turns <= 10.0 && pairs >= 100.0)) return false;
+    if (R < 8) return true;
+    const double passes = std::max(1.0, tets / std::max(lanes, 1));
+    if (turns <= 1.0) return passes <= 8.0;
+    return turns * passes * R <= (turns <= 2.0 ? 104.0 : 72.0);
+}
+
+bool resident_pays(const rdos_sim *s, const ResidentCut &c)
+{
+    const int32_t S = (int32_t)s->D.size(), R = (int32_t)s->rx.size(), ls = (c.len + 3) & ~3;
+    const int32_t range = c.full ? ls : resident_range(S, R, ls, c.lds_bytes);
+    const int32_t used = resident_lds_bytes(S, R, ls, c.full, range, 0);
+    return resident_pays(s, c.len, 1.0, resident_lanes(S, R, c.lds_bytes, used, c.threads));
+}
+
 // One block per realization, more of them (n) than compute units: the widest
 // blocks of which enough share a compute unit.  Narrower blocks finish later
 // but more run at once, which pays while a lane has a few pairs to itself and
@@ -314,7 +357,16 @@ bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int
                     resident_lists_hold(sims[i], c);
         }
         if (!fits) continue;
-        plan->threads = std::min(threads, widest);
+        const int32_t used_threads = std::min(threads, widest);
+        const int32_t together = std::min(kResidentLdsMax / lds, kResidentMaxThreads / used_threads);
+        for (size_t i = 0; i < n_sims; ++i) {
+            const int32_t S = (int32_t)sims[i]->D.size(), R = (int32_t)sims[i]->rx.size(),
+                          rows = (sims[i]->T + 3) & ~3, range = full ? rows : resident_range(S, R, rows, lds);
+            const int32_t lanes_of =
+                resident_lanes(S, R, lds, resident_lds_bytes(S, R, rows, full, range, 0), used_threads);
+            if (!resident_pays(sims[i], sims[i]->T, (double)n / ((double)cus * together), lanes_of)) return false;
+        }
+        plan->threads = used_threads;
         plan->lds_bytes = lds;
         plan->full = plan->every = full;
         for (size_t i = 0; i < n_sims; ++i)
@@ -421,10 +473,14 @@ static const ResidentPlan *resident_for(rdos_sim *s, int64_t n)
     if (one && s->Rz > cus) {
         const rdos_sim *sim = s;
         if (!resident_in_turn(&sim, 1, s->Rz, cus, true, &s->resident_one)) one = nullptr;
-    } else if (one && !one->full && !resident_lists_hold(s, cut_one(s))) {
-        one = nullptr;
+    } else if (one) {
+        const ResidentCut c = cut_one(s);
+        if (!resident_lists_hold(s, c) || !resident_pays(s, c)) one = nullptr;
     }
-    if (many && !many->full && !resident_lists_hold(s, cut_many(s))) many = nullptr;
+    if (many) {
+        const ResidentCut c = cut_many(s);
+        if (!resident_lists_hold(s, c) || !resident_pays(s, c)) many = nullptr;
+    }
     if (one && many) {
         int64_t molecules = 0;
         for (int64_t t : s->species_totals) molecules += t;

@@ -308,7 +308,7 @@ bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, Reside
         const int32_t S = (int32_t)m.s->D.size(), R = (int32_t)m.s->rx.size();
         if (!alone) m.blocks += (int32_t)((double)spare * m.pairs / all);
         const ResidentCut c = resident_cut(m.s->T, S, R, m.blocks);
-        if (c.blocks == 0 || (!alone && !resident_lists_hold(m.s, c))) return false;
+        if (c.blocks == 0 || (!alone && !(resident_lists_hold(m.s, c) && resident_pays(m.s, c)))) return false;
         if (!c.full) plan.full = 0;
         plan.threads = std::max(plan.threads, c.threads);
         plan.max_parts = std::max(plan.max_parts, c.blocks);

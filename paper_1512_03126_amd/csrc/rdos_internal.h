@@ -309,6 +309,13 @@ __host__ __device__ inline int32_t resident_range(int32_t S, int32_t R, int32_t 
     const int32_t range = least + ((left - 15) / (6 * S + (R > 0 ? 4 * S + 2 : 0)) & ~3);
     return range < ls ? range : ls;
 }
+// The lanes of the SSA with `used` of the LDS taken by the rest.
+__host__ __device__ inline int32_t resident_lanes(int32_t S, int32_t R, int32_t lds, int32_t used, int32_t threads)
+{
+    if (R == 0) return 0;
+    const int32_t most = ((lds - used) / resident_lane_bytes(S, R)) & ~63;
+    return most < threads ? most : threads;
+}
 __host__ __device__ inline bool resident_every(int32_t S, int32_t R, int32_t ls, int32_t threads)
 {
     return R == 0 && S * ls <= threads;

@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
     const int32_t range = FULL ? ls : resident_range(S, R, ls, lds_bytes);  // tets the lists are sure to hold
     const int32_t room = S * range;                                         // pairs
     const int32_t used = resident_lds_bytes(S, R, ls, FULL, range, 0);
-    const int32_t lanes = R > 0 ? min(nt, ((lds_bytes - used) / resident_lane_bytes(S, R)) & ~63) : 0;
+    const int32_t lanes = resident_lanes(S, R, lds_bytes, used, nt);
     int32_t *counts = reinterpret_cast<int32_t *>(lds + kResidentHeadBytes);  // [2][P] or [P]
     int32_t *taken = counts + (FULL ? 2 : 1) * P;  // [room] short: counts of the listed pairs from the nt-th on
     int32_t *pop = taken + (FULL ? 0 : room);      // [room] rounded mean populations of the pairs the SSA listed

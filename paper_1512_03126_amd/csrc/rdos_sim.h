@@ -118,6 +118,7 @@ struct ResidentCut {
 };
 ResidentCut resident_cut(int32_t T, int32_t S, int32_t R, int32_t max_blocks);
 bool resident_lists_hold(const rdos_sim *s, const ResidentCut &c);
+bool resident_pays(const rdos_sim *s, const ResidentCut &c);
 // Pairs that a realization is expected to hold, by the counts last set.
 double expected_pairs(const rdos_sim *s);
 // Threads, LDS and layout of `plan` for n blocks, each a whole realization of

@@ -89,6 +89,42 @@ def test_short_requests_of_sparse_lists(orc, shape, S, Rz, mean, n):
     g.close()
 
 
+def chain(S, R):
+    """R reactions over S species that keep the number of molecules."""
+    rx = []
+    for q in range(R):
+        a, b, c = q % S, (q + 1) % S, (q + 2) % S
+        rx.append([([a, b], [c, a], 2e8), ([a], [b], 60.0), ([a, a], [b, c], 1e8), ([b], [c], 90.0)][q % 4])
+    return rx
+
+
+@pytest.mark.parametrize("shape,S,R,Rz,mean", [
+    ((4, 4, 4), 16, 32, 1000, 0.3),  # 64 lanes of a compute unit in the SSA, in four turns
+    ((5, 5, 5), 10, 24, 200, 0.3),   # as few in a block of 750 tets
+    ((2, 2, 2), 3, 2, 12000, 0.01),  # many turns with nearly nothing to do
+])
+def test_models_that_leave_lds_behind(orc, shape, S, R, Rz, mean):
+    import paper_1512_03126_amd as P
+
+    note(f"routes: {Rz} realizations, {shape} cells, {S} species, {R} reactions at {mean}")
+    xyz, tets = W.kuhn_box(*shape, 0.2e-6)
+    T = tets.shape[0]
+    rng = np.random.default_rng(8)
+    D = [1e-12 * (0.3 + 0.1 * s) for s in range(S)]
+    g = P.Simulation(xyz, tets, D, chain(S, R), seed=8, n_realizations=Rz)
+    o = orc.OracleSim(xyz, tets, D, chain(S, R), seed=8, realization=Rz - 1)
+    init = rng.poisson(mean, (S, T)).astype(np.int32)
+    for s in range(S):
+        for r in range(Rz):
+            g.set_counts(s, init[s], realization=r)
+        o.set_counts(s, init[s])
+    least = least_times(P, g, 10, 12)
+    assert least[0] <= 1.12 * least[1], least
+    o.run_steps(2 * 15 * 10)
+    assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts())
+    g.close()
+
+
 def test_crowded_views_leave_the_short_lists():
     """Counts that a device view made crowded, after they were set sparse: the
     first run finds its lists too short, later ones go over the queue until
