@@ -868,7 +868,7 @@ constexpr int kTurnDevices = 64;
 struct Turns {
     LaunchTurn turn[kTurnDevices];
     unsigned long long *ended[kTurnDevices] = {};  // pinned host memory
-    hipEvent_t last[kTurnDevices] = {};            // behind the last launch, where its owner has one
+    const TurnOwner *last[kTurnDevices] = {};      // of the last launch, where others may wait for it
     StreamOwners owners;
 };
 Turns &turns()  // guarded by device_api_mutex()
@@ -893,11 +893,12 @@ void prepare_turns(int device)
     *t.ended[device] = 0;
 }
 
-void join_own_stream(TurnOwner *owner)
+void join_own_stream(TurnOwner *owner, hipStream_t stream)
 {
     std::lock_guard<std::mutex> g(device_api_mutex());
     *owner = TurnOwner{};
     owner->number = turns().owners.own_stream();
+    owner->stream = stream;
     if (hipEventCreateWithFlags(&owner->event, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();  // without one, nobody waits for its launches on the device
         owner->event = nullptr;
@@ -907,10 +908,9 @@ void join_own_stream(TurnOwner *owner)
 void leave_own_stream(TurnOwner *owner)
 {
     std::lock_guard<std::mutex> g(device_api_mutex());
-    if (!owner->event) return;
-    for (hipEvent_t &last : turns().last)
-        if (last == owner->event) last = nullptr;
-    (void)hipEventDestroy(owner->event);
+    for (const TurnOwner *&last : turns().last)
+        if (last == owner) last = nullptr;
+    if (owner->event) (void)hipEventDestroy(owner->event);
     owner->event = nullptr;
 }
 
@@ -919,7 +919,7 @@ void leave_own_stream(TurnOwner *owner)
 // every thread.
 static void join_stream(rdos_sim *s)
 {
-    if (s->own_stream) return join_own_stream(&s->turn);
+    if (s->own_stream) return join_own_stream(&s->turn, s->stream);
     std::lock_guard<std::mutex> g(device_api_mutex());
     StreamOwners &owners = turns().owners;
     s->turn = TurnOwner{};
@@ -950,9 +950,11 @@ static hipError_t launch_in_turn(int device, TurnOwner *owner, bool wait, int32_
     end.number = turn.take(owner->number, ended, n_periods);
     if (end.number == 0) {
         // only streams of the library's own wait, for each other: nothing else can hold them up
-        if (!wait || !owner->event || !t.last[device] || !turn.worth_waiting(ended, owner->last, n_periods))
+        const TurnOwner *last = t.last[device];
+        if (!wait || !owner->event || !last || !turn.worth_waiting(ended, owner->last, n_periods))
             return hipErrorNotReady;
-        if (hipStreamWaitEvent(st, t.last[device], 0) != hipSuccess) {
+        if (hipEventRecord(last->event, last->stream) != hipSuccess ||
+            hipStreamWaitEvent(st, last->event, 0) != hipSuccess) {
             (void)hipGetLastError();
             return hipErrorNotReady;
         }
@@ -964,23 +966,19 @@ static hipError_t launch_in_turn(int device, TurnOwner *owner, bool wait, int32_
         return e;
     }
     owner->last = end.number;
-    t.last[device] = owner->event;
-    if (owner->event && hipEventRecord(owner->event, st) != hipSuccess) {
-        (void)hipGetLastError();
-        t.last[device] = nullptr;  // others run over the queue until the launch has ended
-    }
+    t.last[device] = owner->event ? owner : nullptr;
     return hipSuccess;
 }
 
 hipError_t launch_resident_in_turn(int device, TurnOwner *owner, bool wait, const DevSim *sims,
                                    const ResidentPlan &plan, int64_t iter0, int32_t n_periods, int64_t partial,
-                                   double tau_last, uint64_t epoch, hipStream_t st)
+                                   double tau_last, uint64_t epoch, hipStream_t st, uint32_t *crowded)
 {
-    if (plan.max_parts <= 1)
-        return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, LaunchEnd{}, st);
-    return launch_in_turn(device, owner, wait, n_periods, st, [&](const LaunchEnd &end) {
+    const auto launch = [&](LaunchEnd end) {
+        end.crowded = crowded;
         return launch_resident(sims, plan, iter0, n_periods, partial, tau_last, epoch, end, st);
-    });
+    };
+    return plan.max_parts <= 1 ? launch(LaunchEnd{}) : launch_in_turn(device, owner, wait, n_periods, st, launch);
 }
 
 // len periods from the current one by the one-launch path over the queue.  A
@@ -1017,7 +1015,7 @@ rdos_status enqueue_run(rdos_sim *s, int64_t n, bool partial, double tau_last)
             hipError_t e;
             if (plan) {
                 e = launch_resident_in_turn(s->device, &s->turn, true, s->d_desc, *plan, s->step, len, partial_index,
-                                            tau_last, s->resident_epoch, s->stream);
+                                            tau_last, s->resident_epoch, s->stream, nullptr);
             } else {
                 const rdos_status st = ensure_mask(s);
                 if (st != RDOS_OK) return st;

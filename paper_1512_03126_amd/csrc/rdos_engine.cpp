@@ -154,7 +154,7 @@ struct rdos_engine {
     char *d_sparse = nullptr;
     int64_t cap_sparse = 0;
     bool give_back = false;
-    uint32_t *h_fail = nullptr;    // pinned copy of its failure word, or of the resident plan's crowded word
+    uint32_t *h_fail = nullptr;    // pinned: a copy of its failure word, or what a resident run writes (crowded)
     uint64_t resident_epoch = 0;
     TurnOwner turn;
     double lds_period_ms = 0.0;    // device time per period of the last run on such a path
@@ -933,8 +933,9 @@ void worker_main(rdos_engine *e)
         hipError_t err = hipEventRecord(e->ev0, e->stream);
         if (err == hipSuccess) {
             if (lds == LdsPath::Resident) {
+                *e->h_fail = 0u;
                 err = launch_resident_in_turn(e->device, &e->turn, false, e->d_sims, e->resident, 0, len, -1, 0.0,
-                                              e->resident_epoch, e->stream);
+                                              e->resident_epoch, e->stream, e->h_fail);
                 if (err == hipErrorNotReady) {  // the next chunk runs over the queue, then this path is tried again
                     beside = true;
                     lk.lock();
@@ -942,10 +943,6 @@ void worker_main(rdos_engine *e)
                 }
                 e->resident_epoch += len;
                 if (err == hipSuccess) err = launch_advance(e->d_sims, e->queue.hdr, len, e->stream);
-                *e->h_fail = 0u;
-                if (err == hipSuccess && !e->resident.full)
-                    err = hipMemcpyAsync(e->h_fail, resident_crowded(e->resident), sizeof(uint32_t),
-                                         hipMemcpyDeviceToHost, e->stream);
             } else if (lds == LdsPath::Sparse) {
                 err = launch_sparse(e->d_sims, e->d_sunits, 0, len, e->sparse, e->stream);
                 if (err == hipSuccess)
@@ -982,7 +979,7 @@ void worker_main(rdos_engine *e)
             continue;
         }
         if (lds == LdsPath::Resident && !e->resident.full) {
-            const bool crowded = *e->h_fail != 0u;  // short lists overflowed: over the queue from here on
+            const bool crowded = __atomic_load_n(e->h_fail, __ATOMIC_RELAXED) != 0u;  // short lists overflowed: over the queue from here on
             for (uint64_t id : e->slots) {
                 rdos_sim *s = e->tickets.at(id).sim;
                 s->short_run = true;
@@ -1085,7 +1082,7 @@ rdos_status rdos_engine_create(rdos_engine **out, int device, size_t hbm_budget_
         return RDOS_EDEVICE;
     }
     prepare_turns(device);
-    join_own_stream(&e->turn);
+    join_own_stream(&e->turn, e->stream);
     // Two-launch shapes only: the fused shape (update_bps 0) lost to them on every tuned size measured,
     // and under a profiler, which taxes each launch, it scored first; it stays available by set_shape.
     // One 32-period shape: fewer graph launches per period, at the cost of a longer wait to join.

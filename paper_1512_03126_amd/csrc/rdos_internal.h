@@ -95,11 +95,13 @@ inline std::mutex &device_api_mutex()
     return m;
 }
 
-// Where a launch whose blocks wait for each other says that it has ended: its
-// last block writes `number` to *word (host memory; null: nobody asks).
+// What a launch says in host memory (pinned; null: nobody asks).  One whose
+// blocks wait for each other: its last block to end writes `number` to *word.
+// One with short lists: it writes 1 to *crowded where it raises kFlagCrowded.
 struct LaunchEnd {
     unsigned long long *word = nullptr;
     unsigned long long number = 0;
+    uint32_t *crowded = nullptr;
 };
 // A block's end (every thread of it): the launch's last one says so on the
 // host.  `ended` counts blocks, and is 0 between launches.
@@ -253,8 +255,7 @@ struct ResidentUnit {
 };
 struct ResidentPlan {
     unsigned long long *done;   // [blocks][kResidentFlagStride] last period finished by each block, then the
-                                // failure word, the number of blocks that have ended and whether short lists
-                                // overflowed (resident_crowded) (device)
+                                // failure word and the number of blocks that have ended (device)
     ResidentPart *parts;        // [blocks] (device)
     uint16_t *neighbours;       // [blocks][max_parts] (device; max_parts > 1)
     int32_t blocks;
@@ -323,11 +324,6 @@ __host__ __device__ inline bool resident_every(int32_t S, int32_t R, int32_t ls,
 // Device memory of a plan, and its arrays' places in it (16-byte aligned).
 size_t resident_plan_bytes(int64_t blocks, int64_t max_parts);
 void resident_place(ResidentPlan *plan, void *memory);
-// The word of a plan that is not zero once kFlagCrowded was raised in a run.
-inline const uint32_t *resident_crowded(const ResidentPlan &plan)
-{
-    return reinterpret_cast<const uint32_t *>(plan.done + (int64_t)plan.blocks * kResidentFlagStride + 1);
-}
 // Fills the arrays of a plan: its blocks are those of n_units units whose
 // `first` fields ascend from 0 without gaps, or (units null) of the
 // realizations of one simulation, each cut like `same`.

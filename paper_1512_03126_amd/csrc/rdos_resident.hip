@@ -68,7 +68,7 @@ struct ResidentHead {
     int32_t n_ssa;    // tets listed for the SSA
     int32_t n_pairs;  // (tet, species) pairs listed for Step 3
     int32_t stop;     // a wait for other blocks failed
-    int32_t unused;
+    int32_t spills;   // periods in which short lists overflowed
 };
 static_assert(sizeof(ResidentHead) == kResidentHeadBytes, "LDS head");
 
@@ -198,8 +198,7 @@ __global__ __launch_bounds__(256) void resident_layout_kernel(const DevSim *__re
         pt.neighbours = n;
         plan.parts[b] = pt;
         plan.done[(int64_t)b * kResidentFlagStride] = 0;
-        if (b == 0)  // the failure word and those after it
-            for (int k = 0; k < 2; ++k) plan.done[(int64_t)plan.blocks * kResidentFlagStride + k] = 0;
+        if (b == 0) plan.done[(int64_t)plan.blocks * kResidentFlagStride] = 0;  // both words
     }
 }
 
@@ -279,7 +278,7 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
 
     if (tid < S) head.D[tid] = sm.D[tid];
     if (tid < R) head.rx[tid] = pack_reaction(sm, tid);
-    if (tid == 0) head.n_ssa = head.n_pairs = head.stop = 0;
+    if (tid == 0) head.n_ssa = head.n_pairs = head.stop = head.spills = 0;
     {
         const gptr<int32_t> src = global(sm.buf[first & 1]) + base + t0;
         for (int32_t v = tid; v < P / 4; v += nt) {
@@ -306,7 +305,6 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         reactants = x.order() > 0 ? (uint32_t)(4 * a) | (uint32_t)(4 * b) << 8 : 1u << 16;
     }
 
-    int32_t spills = 0;  // periods in which short lists overflowed
     for (int32_t k = 0; k < n_periods; ++k) {
         // read the descriptor's fields in the period that uses them: held
         // across the loop they are more than the scalar registers hold
@@ -402,7 +400,10 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
                 spill = n_ssa > range || head.n_pairs + S * n_ssa > room;
                 __syncthreads();  // all have read the lengths before the SSA adds to them
                 if (spill) {      // uniform over the block
-                    if (tid == 0) head.n_ssa = head.n_pairs = 0;
+                    if (tid == 0) {
+                        head.n_ssa = head.n_pairs = 0;
+                        head.spills += 1;
+                    }
                     __syncthreads();
                     to = range;
                     continue;
@@ -537,7 +538,6 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         }
         // additions through memory reach it before this block publishes the
         // period
-        if (!FULL && spill) ++spills;
         if (!alone || spill) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (spill)
@@ -606,9 +606,10 @@ __global__ __launch_bounds__(kResidentMaxThreads) void resident_kernel(
         if (alone && FULL && (n_periods & 1)) *(gptr<v4i>)(other + s * Tp + i) = v4i{0, 0, 0, 0};
     }
     if (head.stop && tid == 0) atomicOr(sm.flags, 8);
-    if (!FULL && 4 * (int64_t)spills > n_periods && tid == 0) {
+    if (!FULL && tid == 0 && 4 * (int64_t)head.spills > n_periods) {
         atomicOr(sm.flags, kFlagCrowded);
-        atomicOr(fail + 2, 1u);
+        if (launch_end.crowded)
+            __hip_atomic_store(launch_end.crowded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     end_block(fail + 1, launch_end);
 }

@@ -26,13 +26,15 @@ struct Reaction {
 
 namespace rdos {
 // An owner of turns to launch blocks that wait for each other (rdos_turn.h).
-// The event is recorded behind each launch on a stream of the library's own;
-// others' launches may wait for it on the device until the owner leaves the
-// stream, which is then drained.  A caller's stream has none: what it waits
-// for, and whether it is being captured, is not known here.
+// On a stream of the library's own, others' launches may wait for its last one
+// on the device, by an event that is recorded when the first of them does
+// (recorded behind every launch it cost 4 us a call), until the owner leaves
+// the stream, which is then drained.  A caller's stream has none: what it
+// waits for, and whether it is being captured, is not known here.
 struct TurnOwner {
     uint64_t number = 0;
     uint64_t last = 0;  // its last launch
+    hipStream_t stream = nullptr;
     hipEvent_t event = nullptr;
 };
 }  // namespace rdos
@@ -132,12 +134,12 @@ bool resident_in_turn(const rdos_sim *const *sims, size_t n_sims, int64_t n, int
 // caller then runs periods over the queue, which waits for nobody.
 hipError_t launch_resident_in_turn(int device, rdos::TurnOwner *owner, bool wait, const rdos::DevSim *sims,
                                    const rdos::ResidentPlan &plan, int64_t iter0, int32_t n_periods, int64_t partial,
-                                   double tau_last, uint64_t epoch, hipStream_t st);
+                                   double tau_last, uint64_t epoch, hipStream_t st, uint32_t *crowded);
 // Makes what turns on a device need.
 void prepare_turns(int device);
 // The owner of a stream of the library's own, and before it is destroyed
 // (drained).
-void join_own_stream(rdos::TurnOwner *owner);
+void join_own_stream(rdos::TurnOwner *owner, hipStream_t stream);
 void leave_own_stream(rdos::TurnOwner *owner);
 // Compute units of a device (0 when it cannot be asked).
 int32_t compute_units(int device);
