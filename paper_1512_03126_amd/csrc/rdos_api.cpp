@@ -1531,7 +1531,7 @@ rdos_status rdos_set_counts(rdos_sim *s, int32_t realization, int32_t species, c
             "upload counts");
     if (s->short_run) HIP_TRY(s, launch_clear_flags(s->d_flags, kFlagCrowded, s->stream), "clear flags");
     HIP_TRY(s, hipStreamSynchronize(s->stream), "upload counts");
-    s->short_run = s->crowded = false;
+    s->short_run = s->crowded = s->queue_faster = false;
     s->mask_dirty = true;
     int64_t &last = s->totals[(size_t)realization * s->D.size() + species];
     s->species_totals[species] += total - last;

@@ -143,6 +143,11 @@ struct rdos_engine {
     LdsPath lds_path = LdsPath::None;
     ResidentPlan resident{};
     SparsePlan sparse{};
+    // What the queue would take per period: guessed with the sparse plan, and
+    // measured in a few periods (`try_queue`) where the sparse kernel's own
+    // time is above the guess; the faster of the two keeps the list.
+    double queue_guess_ms = 0.0, queue_ms = 0.0;
+    bool try_queue = false;
     char *d_resident = nullptr;    // the resident plan's arrays
     int64_t cap_resident = 0;
     ResidentUnit *d_runits = nullptr;
@@ -348,15 +353,18 @@ bool cut_resident(const rdos_engine *e, std::vector<ResidentUnit> &units, Reside
 // (the update).  A+B<->C at 2% occupancy, sparse and queue: 24 realizations
 // of 162,000 tets 22 and 20 us, 64 of them 22 and 31, 128 of 384,000 tets 46
 // and 109, the batch of 256 + 64 realizations 63 and 228; 64 realizations of
-// 162,000 tets with a decaying fourth species 64 and 49.
-bool plan_sparse(const rdos_engine *e, std::vector<WorkUnit> &units, SparsePlan &plan)
+// 162,000 tets with a decaying fourth species 64 and 49.  Events and clustered
+// molecules are not in it: 260 realizations of 14,196 tets of three species
+// whose molecules react within a few periods 172 and 90.  So the first runs are
+// compared with the guess, and the queue is tried where they take longer.
+bool plan_sparse(rdos_engine *e, std::vector<WorkUnit> &units, SparsePlan &plan)
 {
     const int32_t cus = std::max(compute_units(e->device), 1);
     plan = SparsePlan{};
     int32_t S = 1, R = 0;
     for (uint64_t id : e->slots) {
         const rdos_sim *s = e->tickets.at(id).sim;
-        if (s->desc.zeroth) return false;
+        if (s->desc.zeroth || s->queue_faster) return false;
         S = std::max(S, (int32_t)s->D.size());
         R = std::max(R, (int32_t)s->rx.size());
         if (s->desc.transfer_form == 1) plan.scaled = 1;
@@ -392,6 +400,7 @@ bool plan_sparse(const rdos_engine *e, std::vector<WorkUnit> &units, SparsePlan 
     const double sparse_us = 7.0 + std::max(most_load, all_load / cus);
     const double queue_us = 12.0 + 0.33e-6 * cells + 76e-6 * all;
     if (sparse_us > queue_us) return false;
+    e->queue_guess_ms = 1e-3 * queue_us;
     std::stable_sort(units.begin(), units.end(), [](const WorkUnit &a, const WorkUnit &b) { return a.T > b.T; });
     return true;
 }
@@ -492,7 +501,8 @@ rdos_status build_work(rdos_engine *e)
                    "expand tiles");
     }
     e->lds_path = LdsPath::None;
-    e->lds_period_ms = 0.0;
+    e->lds_period_ms = e->queue_ms = 0.0;
+    e->try_queue = false;
     std::vector<ResidentUnit> runits;
     std::vector<WorkUnit> sunits;
     // light blocks with a compute unit each only after the sparse kernel
@@ -867,8 +877,14 @@ void worker_main(rdos_engine *e)
         // chunk, or some milliseconds of device time: the sparse kernel's
         // runs are the longer ones, since each reads the state from memory and
         // writes it back.
-        const LdsPath lds = !timed && !tuning && !e->fixed_shape && !beside ? e->lds_path : LdsPath::None;
+        const bool trial = e->try_queue && !timed && !tuning;
+        e->try_queue = false;
+        const LdsPath lds = !timed && !tuning && !e->fixed_shape && !beside && !trial ? e->lds_path : LdsPath::None;
         beside = false;
+        if (trial) {
+            replay = false;
+            len = (int32_t)std::min<int64_t>(left_max, 16);
+        }
         if (lds != LdsPath::None) {
             replay = false;
             const bool pending = !e->ready.empty() || !e->waiting.empty() || e->admitting > 0;
@@ -1002,6 +1018,14 @@ void worker_main(rdos_engine *e)
         }
         if (replay && tail == 0) e->last_chunk_ms = (double)ms / reps;
         if (lds != LdsPath::None) e->lds_period_ms = (double)ms / len;
+        if (trial && len >= 8) e->queue_ms = (double)ms / len;
+        if (e->lds_path == LdsPath::Sparse && (trial || (lds != LdsPath::None && len >= 16))) {
+            if (e->queue_ms > 0.0 && e->queue_ms < e->lds_period_ms) {
+                e->lds_path = LdsPath::None;
+                for (uint64_t id : e->slots) e->tickets.at(id).sim->queue_faster = true;
+            }
+            e->try_queue = e->queue_ms == 0.0 && e->lds_period_ms > e->queue_guess_ms;
+        }
         if (tuning && replay) {  // only full graph-replayed chunks are scored
             const size_t m = e->candidates.size();
             if (e->trial >= 2 * m || (e->trial & 1)) e->trial_ms[e->trial >= 2 * m][tune_candidate(e)] = ms / len;

@@ -94,6 +94,7 @@ struct rdos_sim {
     uint64_t resident_epoch = 0;         // periods launched with several blocks (their counters' value)
     bool short_run = false;              // launched with short lists since counts were last set
     bool crowded = false;                // and they overflowed: not again until counts are set
+    bool queue_faster = false;           // than an engine's sparse kernel, by trial: until counts are set
     std::vector<int64_t> totals;         // molecules last set, per realization and species
     std::vector<int64_t> species_totals; // and over the realizations: rules ask on each call
     rdos::DevSim desc{};

@@ -54,7 +54,7 @@ CASES = {
 @pytest.mark.parametrize("name", list(CASES))
 def test_sparse_batch(P, orc, name):
     c = CASES[name]
-    S, Rz, seed = c["S"], 300 if c["cells"] != WIDE else 260, 17
+    S, Rz, seed = c["S"], 300, 17
     xyz, tets = W.kuhn_box(*c["cells"], 0.2e-6)
     T = tets.shape[0]
     note(f"sparse batch: {name}, {Rz} realizations of {T} tets, {S} species, {len(c['rx'])} reactions")
