@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -208,14 +209,12 @@ static int64_t sum_counts(const int32_t *v, int64_t n, int64_t *bad)
 
 int32_t compute_units(int device)
 {
-    static std::mutex mu;
-    static std::map<int, int> known;
-    std::lock_guard<std::mutex> g(mu);
-    auto it = known.find(device);
-    if (it != known.end()) return it->second;
-    int n = 0;
+    static std::atomic<int32_t> known[64] = {};
+    if (device < 0 || device >= 64) return 0;
+    int32_t n = known[device].load(std::memory_order_relaxed);
+    if (n > 0) return n;
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
-    known[device] = n;
+    known[device].store(n, std::memory_order_relaxed);
     return n;
 }
 
@@ -821,9 +820,12 @@ private:
     int made_ = 0;
     int64_t alive_ = 0;
 };
+// Not destroyed: simulations may be, at the end of the process, after what was
+// made with the first of them.
 static ReadBuffers &read_buffers()
 {
-    static ReadBuffers b;
+    alignas(ReadBuffers) static unsigned char room[sizeof(ReadBuffers)];
+    static ReadBuffers &b = *new (room) ReadBuffers;
     return b;
 }
 
