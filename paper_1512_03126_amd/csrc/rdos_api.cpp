@@ -1688,17 +1688,24 @@ rdos_status rdos_get_geometry(rdos_sim *s, int32_t *nbr, double *w, double *g, d
     if (!s) return RDOS_EINVAL;
     if (s->state != SimState::Ready) return fail(s, RDOS_ESTATE, "get_geometry before finalize");
     HIP_TRY(s, hipSetDevice(s->device), "set device");
-    // the tables are laid out apart on the device and copied into the caller's
-    // arrays, not copied as records and taken apart on the host
+    // The tables of large meshes are laid out apart on the device and copied
+    // into the caller's arrays, not copied as records and taken apart on the
+    // host.  Small ones are: one copy and a wait against four (750 tets 36 us
+    // against 112, 10,368 73 and 119, 20,250 153 and 132; a million 15,900 and
+    // 3600).  The first copy into an array is slower, by the pinning of its
+    // pages: of 162,000 tets 1310 and 2130 then, and 1110 and 620 into the same
+    // arrays again; a million 20,200 and 7200.
     const size_t T = (size_t)s->T;
     const size_t at_w = 16 * T, at_g = at_w + 32 * T, at_nav = at_g + 8 * T;
     char *tables = nullptr;
-    {
+    if (s->T >= 16384) {
         std::lock_guard<std::mutex> g2(device_api_mutex());
-        if (dev_alloc((void **)&tables, at_nav + 8 * T, s->stream) != hipSuccess) tables = nullptr;
+        if (dev_alloc((void **)&tables, at_nav + 8 * T, s->stream) != hipSuccess) {
+            (void)hipGetLastError();  // no room beside the simulation
+            tables = nullptr;
+        }
     }
-    if (!tables) {  // no room beside the simulation
-        (void)hipGetLastError();
+    if (!tables) {
         std::vector<MeshRec> m(T);
         HIP_TRY(s, hipMemcpyAsync(m.data(), s->d_mesh, T * sizeof(MeshRec), hipMemcpyDeviceToHost, s->stream),
                 "download mesh tables");

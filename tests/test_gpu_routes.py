@@ -256,3 +256,30 @@ def test_reacting_batches_leave_the_sparse_kernel(orc):
     assert np.array_equal(g.get_counts(None, realization=Rz - 1), o.get_counts())
     g.close()
     assert least[0] <= 1.15 * least[1], least
+
+
+def test_geometry_of_small_meshes_by_one_copy(orc):
+    """On both sides of the size from which the device takes the tables apart
+    (16,384 tets), against the oracle's; a small mesh's cost no more than a few
+    waits."""
+    import paper_1512_03126_amd as P
+
+    for shape in ((5, 5, 5), (13, 14, 15), (14, 14, 14)):
+        xyz, tets = W.kuhn_box(*shape, 0.2e-6)
+        note(f"routes: geometry of {tets.shape[0]} tets")
+        g = P.Simulation(xyz, tets, [1e-12], [], seed=1)
+        o = orc.OracleSim(xyz, tets, [1e-12], [], seed=1)
+        got, want = g.geometry(), o.geometry()
+        assert np.array_equal(got["nbr"], want["nbr"])
+        for k in ("w", "g", "nav"):
+            np.testing.assert_allclose(got[k], want[k], rtol=1e-13)
+        if tets.shape[0] == 750:
+            def least(call):
+                times = []
+                for _ in range(40):
+                    t = time.perf_counter()
+                    call()
+                    times.append(time.perf_counter() - t)
+                return min(times)
+            assert least(g.geometry) <= 2.5 * least(g.synchronize)
+        g.close()
