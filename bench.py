@@ -3,8 +3,9 @@
 
 Default workload (batched): 256 realizations of the A+B<->C system on the
 40^3 x 6 Kuhn lattice (384,000 tets, 3 species) plus 64 realizations of its
-20^3 x 6 variant (48,000 tets), advanced together by the batching engine
-(hipGraph-captured chunks of periods).  A "step" is one period tau of every
+20^3 x 6 variant (48,000 tets), advanced together by the batching engine (runs
+of periods with the occupied pairs in LDS; with --shape hipGraph-captured
+chunks of periods over the queue).  A "step" is one period tau of every
 realization.  Prints one JSON line.
 
   python bench.py [--steps K] [--warmup W] [--workload batched|plain]
@@ -503,7 +504,7 @@ def run_jittered(P, W, periods):
     sim.synchronize()
     dt = time.perf_counter() - t0
     tau = sim.tau
-    # the same simulation through the engine: graph-replayed chunks of periods
+    # the same simulation through the engine
     e = P.rdos_engine_create(0, 0)
     run_engine(P, e, [sim], 32)
     t1 = time.perf_counter()
@@ -731,7 +732,10 @@ def main():
         up["additions_per_launch"] = round(work["additions"] / n_upd, 1)
         up["transfers_per_launch"] = round(work["transfers"] / n_upd, 1)
         up["avg_launch_ms_tallying"] = round(tallied_ms, 4)
-        # the roofline: the update (the longer kernel) in the method's units
+        # the roofline: the update (the longer kernel of the queue's, in the
+        # timing pass) in the method's units, and the timed periods in the
+        # same units.  Without a fixed shape those keep the state in LDS,
+        # where the batch takes less than half of the two kernels' time.
         alg = method_bytes(work, models[0].n_species, mesh_tets * n_upd) / n_upd
         ach = alg / (upd_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "kernel": "update_kernel", "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS,
@@ -741,8 +745,15 @@ def main():
                 "avg_launch_ms": up["avg_launch_ms"], "kernels": kern,
                 "dense_bytes_per_period": bytes_per_period,
                 "dense_period_frac": round(bytes_per_period / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)}
+        in_lds = not args.shape and ms_step < 0.5 * (scan_ms + upd_ms)
+        timed = alg / (ms_step * 1e-3) / 1e9
+        roof["measured"] = "timing pass of the queue's kernels" + ("; the timed periods do not run them" if in_lds else "")
+        roof["timed_periods"] = {"kernel": "sparse_kernel" if in_lds else "scan_kernel + update_kernel",
+                                 "bound": "vector instructions and latency" if in_lds else "hbm",
+                                 "achieved": round(timed, 1), "unit": "GB/s",
+                                 "frac": round(timed / HBM_PEAK_GBPS, 4)}
         log(f"update_kernel: {alg:.4g} algorithmic B per launch (method units), {ach:.1f} GB/s, "
-            f"frac {roof['frac']}")
+            f"frac {roof['frac']}; the timed periods {timed:.1f} GB/s in the same units")
         try:
             roof["copy_probe_GBps"] = round(P.rdos_bandwidth_probe(0, 1 << 30, 20), 1)
         except Exception as ex:  # informational only
@@ -764,7 +775,8 @@ def main():
         for x in sims:
             x.close()
         workload = ("batched A+B<->C: 256 realizations x 40^3x6 Kuhn lattice (384000 tets) + 64 x 20^3x6 "
-                    "(48000 tets), 3 species, hipGraph-captured chunks of periods")
+                    "(48000 tets), 3 species, " +
+                    ("occupied pairs in LDS for a run of periods" if in_lds else "hipGraph-captured chunks of periods"))
         config = {"workload": workload, "tets": [384000, 48000], "realizations": [256, 64], "species": 3,
                   "periods": K, "tau_s": 2.958758547680654e-4, "updates_per_period": upd_per_period,
                   "realizations_per_s": round(320.0 / (ms_step * 1e-3 * 338), 3),

@@ -220,20 +220,22 @@ rdos_status rdos_step_static(rdos_sim *s, int64_t n_steps);
 /* How rdos_step and rdos_run_until launch the periods (results never depend
  * on it).  0 (default): all periods of a call in one launch with the counts
  * held in LDS, where a realization's counts fit the LDS of the device's
- * compute units divided among the realizations (one block per realization:
- * about 10,000 tet-species; a single realization: about 2.5 million);
- * otherwise, for up to three periods of a larger work list, by how much of it
- * is occupied, and on a stream that is being captured: a work list of at most 8 tiles (1024 tets per
- * realization and tile) runs its periods in one cooperative launch over the
- * occupied-tet queue, the scan and update phases of each period separated by
- * grid-wide barriers, and larger ones launch a scan and an update kernel per
- * period.  1: always two launches per period.  2: always one cooperative
- * launch over the queue.  In modes 0 and 2, a launch whose blocks wait for
- * each other gives way to two launches per period while one of another
- * stream's is under way on the device.  3: one fused launch per period (each
- * wavefront scans its tiles and updates the tets it queued, no queue in device
- * memory; simulations of more than 8 species launch two kernels instead).
- * RDOS_EINVAL for other values. */
+ * compute units divided among the realizations and that is expected to be
+ * faster.  A compute unit holds about 10,000 tet-species, or 30,000 where few
+ * of them are expected to be occupied (by the counts last set); a single
+ * realization may take all of them (2.5 to 7.5 million).  Otherwise (among
+ * others: up to three periods of a large sparse work list, many reactions in
+ * many realizations, a stream that is being captured) a work list of at most 8
+ * tiles (1024 tets per realization and tile) runs its periods in one
+ * cooperative launch over the occupied-tet queue, the scan and update phases
+ * of each period separated by grid-wide barriers, and larger ones launch a
+ * scan and an update kernel per period.  1: always two launches per period.
+ * 2: always one cooperative launch over the queue.  3: one fused launch per
+ * period (each wavefront scans its tiles and updates the tets it queued, no
+ * queue in device memory; simulations of more than 8 species launch two
+ * kernels instead).  In modes 0 and 2 a launch whose blocks wait for each other
+ * waits on the device for another simulation's, or leaves its periods to two
+ * launches each while that is under way.  RDOS_EINVAL for other values. */
 rdos_status rdos_set_launch_mode(rdos_sim *s, int32_t mode);
 
 /* Waits for all queued work; reports RDOS_EOVERFLOW if raised. */

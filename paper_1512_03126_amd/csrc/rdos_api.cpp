@@ -770,8 +770,10 @@ rdos_status check_flags(rdos_sim *s)
 // into one, and a single wait replaces two copies with theirs (the 750-tet
 // cube, one period and its counts: 41 us a pass, 62 with the copies).  At most
 // kReadBuffers of kReadBytes each while simulations are alive, taken and
-// returned under a lock; a caller that finds none free copies instead, as does
-// a simulation in its first reads (making a buffer costs as much as several).
+// returned under a lock; a caller that finds none free copies instead.  Making
+// one costs as much as several reads, so a simulation copies in its first four,
+// also where a buffer made for another is free (a new simulation's first such
+// pass 56 us, 91 with the queue's kernels and the copies).
 class ReadBuffers {
 public:
     static constexpr int kReadBuffers = 16, kFirstReads = 4;
