@@ -995,7 +995,8 @@ void worker_main(rdos_engine *e)
             continue;
         }
         if (lds == LdsPath::Resident && !e->resident.full) {
-            const bool crowded = __atomic_load_n(e->h_fail, __ATOMIC_RELAXED) != 0u;  // short lists overflowed: over the queue from here on
+            // short lists that overflowed: over the queue from here on
+            const bool crowded = __atomic_load_n(e->h_fail, __ATOMIC_RELAXED) != 0u;
             for (uint64_t id : e->slots) {
                 rdos_sim *s = e->tickets.at(id).sim;
                 s->short_run = true;
